@@ -474,6 +474,8 @@ Sampling sampling_of(const wo_optics* o) {
   s.dz = o->dz;
   s.dy = o->dy;
   s.dx = o->dx;
+  s.Ly = (double)o->ny * o->dy;
+  s.Lx = (double)o->nx * o->dx;
   return s;
 }
 
@@ -793,6 +795,11 @@ struct TuneGroup {
   double work;
   int ab = 0;            // aberration-aware kernels (an aberrated patch, or dL/dc wanted)
   LatSupport sup;        // the fields' columns for every theta the tune may reach
+  // The iterations' grid (tune_band): the loss band's own sampling of the field
+  // of view, its support and the frequencies the loss visits.
+  Sampling bsm;
+  LatSupport bsup;
+  BandPlanes band;
 };
 
 // Lateral support of the auto-tune's fields: whatever NA and tilt the tune
@@ -825,7 +832,7 @@ std::vector<TuneGroup> tune_groups(const wo_optics* o, int32_t n, int32_t starts
   for (int i = 0; i < n; ++i) {
     size_t k = 0;
     while (k < g.size() && !same_sampling(g[k].rep, &o[i])) ++k;
-    if (k == g.size()) g.push_back(TuneGroup{&o[i], {}, TuneLayout{}, 0, 0.0, 0, LatSupport{}});
+    if (k == g.size()) g.push_back(TuneGroup{&o[i], {}, TuneLayout{}, 0, 0.0, 0, LatSupport{}, Sampling{}, LatSupport{}, BandPlanes{}});
     g[k].idx.push_back(i);
     if (aberrated(o[i])) g[k].ab = 1;
   }
@@ -839,6 +846,68 @@ std::vector<TuneGroup> tune_groups(const wo_optics* o, int32_t n, int32_t starts
   }
   if (total) *total = b;
   return g;
+}
+
+// The grid of a group's iterations.  The loss reads the transfer function only
+// at |nu| <= nu_c/4, far below the grid's Nyquist frequency (0.78 of 5 cycles
+// per um on the 0.1 um tiles), and the gradient dL/dH* vanishes elsewhere.  The
+// fields' spectra stay within p columns and rows of zero (the shell bound of
+// tune_support), so the product b conj(a) has extent 2 p and its spectrum at
+// |k| <= kb is exact on any grid of more than 2 p + kb points per axis: an
+// alias k + L of a value beyond lands outside the band.  Backward, Gamma b has
+// extent kb + p and u_A, u_B are needed within p: the same condition; and
+// sum Gamma b conj(a) needs the zero frequency of a product of extent 2 p + kb
+// only.  So the iterations run on the shortest compiled lengths that satisfy
+// it (80 x 80 for 128 x 128 tiles, 320 x 320 for 512 x 512) with the same
+// physical extents, and the transforms around the loss carry the band's
+// columns and rows only; every sum over the grid scales with its point count,
+// which the kernels take from the sampling.  256 patches of 32 x 128 x 128, one
+// loss and gradient: kernels 5.4 ms on the grid's own sampling, 2.1 ms so.
+// full_data: the data spectra hold every frequency (the restoration after the
+// iterations reads them all), else the band's columns.
+void tune_band(const wo_optics* o, const double* nu_c, bool full_data, TuneGroup* g) {
+  const Sampling sm = sampling_of(g->rep);
+  const int X = sm.nx, Y = sm.ny, Xh = X / 2 + 1;
+  g->bsm = sm;
+  g->bsup = g->sup;
+  g->band = BandPlanes{Xh, Y, Y, Y, Xh};
+  const double vx = 1.0 / sm.Lx, vy = 1.0 / sm.Ly, dnu = fmin(vx, vy);
+  double px = 0.0, py = 0.0, kbx = 0.0, kby = 0.0;
+  for (int i : g->idx) {
+    const double q = o[i].n_medium / o[i].wavelength + o[i].edge_width * dnu;
+    const double nuc = (nu_c && nu_c[i] > 0) ? nu_c[i] : (o[i].na_det + o[i].na_ill) / o[i].wavelength;
+    px = fmax(px, floor(q / vx) + 1.0);
+    py = fmax(py, floor(q / vy) + 1.0);
+    kbx = fmax(kbx, floor(0.25 * nuc / vx) + 1.0);
+    kby = fmax(kby, floor(0.25 * nuc / vy) + 1.0);
+  }
+  // the shortest compiled length above the bounds; 0: none below the grid's own
+  auto shortest = [](double p, double kb, int full) {
+    static const int sizes[] = {64, 80, 96, 128, 160, 192, 240, 256, 320, 384, 480, 512, 1024};
+    if (!(p >= 0.0 && kb >= 0.0 && p < full && kb < full)) return 0;
+    const int ip = (int)p, ik = (int)kb;
+    const int need = std::max(std::max(2 * ip + ik + 1, 2 * ik + 2), (2 * ip + 1 + 15) / 16 * 16);
+    for (int n : sizes)
+      if (n >= need && n < full) return n;
+    return need <= full ? full : 0;
+  };
+  const int lx = shortest(px, kbx, X), ly = shortest(py, kby, Y);
+  if (!lx || !ly) return;
+  g->bsm.nx = lx;
+  g->bsm.ny = ly;
+  g->bsup = full_support(g->bsm);
+  const int xc = (2 * (int)px + 1 + 15) / 16 * 16;
+  if (xc < lx) {
+    g->bsup.xc = g->bsup.xa = xc;
+    g->bsup.kp = g->bsup.kpa = (int)px;
+  }
+  // band columns in runs of 64 bytes; the band's row count on both grids
+  g->bsup.kt = std::min(((int)kbx + 1 + 7) / 8 * 8, lx / 2 + 1);
+  const int nb = 2 * (int)kby + 1;
+  g->band.kt = g->bsup.kt;
+  g->band.ky = (int)kby;
+  g->band.nb = nb;
+  if (!full_data) g->band.DP = g->bsup.kt;
 }
 
 // Runs of consecutive patch indices inside a group: (first local index, length).
@@ -911,10 +980,12 @@ DevOptics dev_optics(const wo_optics& o) {
 int tune_iteration(const TuneGroup& g, char* ws, int starts, int update, hipStream_t hs) {
   const TuneLayout& L = g.L;
   char* w = ws + g.base;
-  Sampling sm = sampling_of(g.rep);
+  Sampling sm = g.bsm;
   sm.aberrated = g.ab;
-  const long Z = sm.nz, Y = sm.ny, Xh = sm.nx / 2 + 1;
-  const long plane = Y * Xh;
+  const long Z = sm.nz, Y = sm.ny, kt = g.bsup.kt;
+  const long plane = Y * kt;
+  const int banded = g.band.nb < Y;
+  const long lmax = loss_blocks(sampling_of(g.rep));   // the workspace's loss partials per patch
   DevOptics* dopt = (DevOptics*)(w + L.off_opt);
   TuneState* st = (TuneState*)(w + L.off_st);
   float2* D = (float2*)(w + L.off_D);
@@ -926,14 +997,15 @@ int tune_iteration(const TuneGroup& g, char* ws, int starts, int update, hipStre
   double* gp = (double*)(w + L.off_gp);
   double* ip = (double*)(w + L.off_ip);
   const int nv = L.nv;
-  WO_TRY(launch_tf_fields_y(dopt, sm, nv, ab, pp, hs, &g.sup));
-  WO_TRY(launch_tf_rows_labelfree(pp, sm, nv, ab, bank, 2 * Z * plane, plane, 2 * plane, hs, &g.sup));
-  WO_TRY(launch_cols(bank, (int)Y, Xh, 2 * Z, 2 * Z, nv, -1.f, hs, "k_cols_y_tf"));
-  WO_TRY(launch_loss_grad(dopt, st, sm, nv, D, bank, lp, starts, hs));
-  WO_TRY(launch_cols(bank, (int)Y, Xh, 2 * Z, 2 * Z, nv, 1.f, hs, "k_cols_y_grad"));
-  WO_TRY(launch_tf_rows_bwd(pp, sm, nv, ab, bank, dp, hs, &g.sup));
-  WO_TRY(launch_tf_grad_y(dopt, sm, nv, ab, gp, ip, hs, &g.sup));
-  WO_TRY(launch_adam(dopt, st, sm, nv, pp, lp, dp, gp, ip, update, hs, &g.sup));
+  WO_TRY(launch_tf_fields_y(dopt, sm, nv, ab, pp, hs, &g.bsup));
+  WO_TRY(launch_tf_rows_labelfree(pp, sm, nv, ab, bank, 2 * Z * plane, plane, 2 * plane, hs, &g.bsup,
+                                  (int)kt));
+  WO_TRY(launch_cols(bank, (int)Y, kt, 2 * Z, 2 * Z, nv, -1.f, hs, "k_cols_y_tf", banded ? 1 : 0, g.band.ky));
+  WO_TRY(launch_loss_grad(st, sm, g.band, nv, D, bank, lp, lmax, starts, hs));
+  WO_TRY(launch_cols(bank, (int)Y, kt, 2 * Z, 2 * Z, nv, 1.f, hs, "k_cols_y_grad", banded ? 2 : 0, g.band.ky));
+  WO_TRY(launch_tf_rows_bwd(pp, sm, nv, ab, bank, dp, hs, &g.bsup));
+  WO_TRY(launch_tf_grad_y(dopt, sm, nv, ab, gp, ip, hs, &g.bsup));
+  WO_TRY(launch_adam(dopt, st, sm, nv, pp, lp, dp, gp, ip, loss_blocks(g.band, lmax), update, hs, &g.bsup));
   return WO_OK;
 }
 
@@ -1054,14 +1126,16 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
   }
   WO_TRY(launch_set_params((DevOptics*)(w + L.off_opt), hopt.data(), nv, hs));
   WO_TRY(launch_set_tune((TuneState*)(w + L.off_st), hst.data(), nv, hs));
-  const long Z = g.rep->nz, Y = g.rep->ny, Xh = g.rep->nx / 2 + 1;
+  const long Z = g.rep->nz, Y = g.rep->ny, Xh = g.rep->nx / 2 + 1, DP = g.band.DP;
   float2* D = (float2*)(w + L.off_D);
   for (auto r : index_runs(g.idx)) {
     RowGroups rg{Z * Y, Z * Y, Z * Y, r.second};
-    WO_TRY(launch_rows_r2c(d + doff[g.idx[r.first]], D + (size_t)r.first * Z * Y * Xh, g.rep->nx, rg,
-                           hs));
+    WO_TRY(launch_rows_r2c(d + doff[g.idx[r.first]], D + (size_t)r.first * Z * Y * DP, g.rep->nx, rg, hs,
+                           (int)DP, (int)DP));
   }
-  WO_TRY(launch_cols(D, (int)Y, Xh, Z, Z, np, -1.f, hs, "k_cols_y_data"));
+  // without a restoration only the band's rows are kept too
+  const bool banded = DP < Xh && g.band.nb < Y;
+  WO_TRY(launch_cols(D, (int)Y, DP, Z, Z, np, -1.f, hs, "k_cols_y_data", banded ? 1 : 0, g.band.ky));
   return WO_OK;
 }
 
@@ -1177,6 +1251,7 @@ int run_tune(wo_optics* o, int32_t n, const float* d, const double* eta,
   char* w = (char*)ws;
   std::lock_guard<std::mutex> lk(g_tune_mu);
   for (auto& g : groups) {
+    tune_band(o, opts->nu_c, f_out != nullptr, &g);
     st = tune_setup(o, g, starts, opts->theta0, d, doff.data(), eta, opts->nu_c, opts->lr, opts->lo,
                     opts->hi, opts->tune_mask, w, hs, opts->lr_zernike, opts->zernike_bound);
     if (st) return st;
@@ -1213,7 +1288,12 @@ int run_tune(wo_optics* o, int32_t n, const float* d, const double* eta,
     // A graph depends only on the shapes and samplings, the buffers, the counts
     // and the FFT schedules (parameters live in the workspace): reuse it when a
     // call repeats them.
-    const std::string key = graph_key(o, n, opts, starts, B, ws, ws_bytes, d, f_out);
+    std::string key = graph_key(o, n, opts, starts, B, ws, ws_bytes, d, f_out);
+    for (auto& g : groups) {   // and the iterations' grids (tune_band)
+      char b[96];
+      snprintf(b, sizeof(b), "|%d %d %d %d %d", g.bsm.ny, g.bsm.nx, g.band.kt, g.band.ky, g.bsup.xc);
+      key += b;
+    }
     hipGraphExec_t exec = graph_cache_find(key);
     if (!exec) {
       const bool was_timing = timing_enabled();
@@ -1835,7 +1915,7 @@ extern "C" int wo_reconstruct_grad(const wo_optics* o, int32_t n, const float* d
     WO_TRY(launch_cols(bank, (int)Y, Xh, 2 * Z, 2 * Z, n, 1.f, hs, "k_cols_y_grad"));
     WO_TRY(launch_tf_rows_bwd(pp, sm, n, ab, bank, dp, hs, &sup));
     WO_TRY(launch_tf_grad_y(dopt, sm, n, ab, gp, ip, hs, &sup));
-    WO_TRY(launch_adam(dopt, tst, sm, n, pp, lp, dp, gp, ip, 0, hs, &sup));
+    WO_TRY(launch_adam(dopt, tst, sm, n, pp, lp, dp, gp, ip, loss_blocks(sm), 0, hs, &sup));
   }
   if (dL_dd_out) {
     WO_TRY(launch_cols(D, (int)Z, plane, C, C, n, 1.f, hs, "k_cols_z_inv"));
@@ -1940,6 +2020,7 @@ static int midband(const wo_optics* o, int32_t n, const float* d, const double* 
   hipStream_t hs = (hipStream_t)stream;
   char* w = (char*)ws;
   for (auto& g : groups) {
+    tune_band(o, nu_c, false, &g);
     st = tune_setup(o, g, 1, nullptr, d, doff.data(), eta, nu_c, nullptr, nullptr, nullptr, 0, w, hs);
     if (st) return st;
     st = tune_iteration(g, w, 1, 0, hs);

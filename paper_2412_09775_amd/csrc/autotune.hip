@@ -38,82 +38,126 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
 
 // ------------------------------------------------------------------ loss and dL/dH*
 
-// One thread per half-spectrum frequency m = ky * Xh + kx of virtual patch v.
-// D: [n][Z][Y][Xh] (patch v reads data patch v / data_div), bank: [v][Z][2][Y][Xh],
-// overwritten with dL/dH*.  lpart[v * bpp + block] = sum of w |F_phase|^2.
-__global__ __launch_bounds__(256) void k_loss_grad(const DevOptics* __restrict__ opt,
-                                                   const TuneState* __restrict__ st, Sampling sm,
-                                                   const float2* __restrict__ D,
+// Only the frequencies of the band rows and columns (BandPlanes) are visited:
+// the loss and dL/dH* vanish elsewhere, and the transforms around this kernel
+// carry nothing else.  ZS lanes share a frequency, each summing every ZS-th
+// plane (a fixed shuffle tree adds them); lane = slice * (64 / ZS) + frequency,
+// so a wave still reads runs of 64 / ZS consecutive columns.  Bound by the
+// latency of its strided plane loads; four slices quarter the chain.
+// D: [n][Z][DY][DP] (patch v reads data patch v / data_div), bank:
+// [v][Z][2][Y][kt], the band rows overwritten with dL/dH*.
+// lpart[v * bpp + block] = sum of w |F_phase|^2.
+template <int ZS>
+__global__ __launch_bounds__(256) void k_loss_grad(const TuneState* __restrict__ st, Sampling sm,
+                                                   BandPlanes bp, const float2* __restrict__ D,
                                                    float2* __restrict__ bank,
                                                    double* __restrict__ lpart, long bpp,
                                                    int data_div) {
   __shared__ double red[4];
-  const int Z = sm.nz, Y = sm.ny, X = sm.nx, Xh = X / 2 + 1;
-  const long M = (long)Y * Xh;
+  constexpr int FW = 64 / ZS;   // frequencies per wave
+  const int Z = sm.nz, Y = sm.ny;
   const long v = blockIdx.x / bpp;
   const long blk = blockIdx.x - v * bpp;
-  const long m = blk * blockDim.x + threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int zq = lane / FW;
+  const long q = (blk * 4 + wave) * FW + (lane & (FW - 1));
   double lsum = 0.0;
-  if (m < M) {
-    const int ky = (int)(m / Xh), kx = (int)(m - (long)ky * Xh);
-    const double fy = fftfreq(ky, Y, sm.dy), fx = fftfreq(kx, X, sm.dx);
-    const double r = sqrt(fy * fy + fx * fx);
-    const TuneState& s = st[v];
-    const bool band = r >= s.nu_c / 8.0 && r <= s.nu_c / 4.0;
-    const float eta = (float)s.eta;
-    const float2* dp = D + (v / data_div) * (long)Z * M + m;
-    float2* hp = bank + v * (long)Z * 2 * M + m;
-    // pass 1: normal matrix and right-hand side
-    float m00 = 0.f, m11 = 0.f;
-    float2 m10 = make_float2(0.f, 0.f), r0 = make_float2(0.f, 0.f), r1 = make_float2(0.f, 0.f);
+  const bool on = q < (long)bp.nb * bp.kt;
+  const int b = on ? (int)(q / bp.kt) : 0, kx = on ? (int)(q - (long)b * bp.kt) : 0;
+  const bool neg = bp.nb < Y ? b > bp.ky : b >= (Y + 1) / 2;   // negative row frequency
+  const int sy = neg ? b - bp.nb : b;
+  const double fy = (double)sy * (1.0 / sm.Ly), fx = (double)kx * (1.0 / sm.Lx);
+  const double r = sqrt(fy * fy + fx * fx);
+  const TuneState& s = st[v];
+  const bool band = on && r >= s.nu_c / 8.0 && r <= s.nu_c / 4.0;
+  const float eta = (float)s.eta;
+  const long M = (long)Y * bp.kt, DM = (long)bp.DY * bp.DP;
+  const float2* dp = D + (v / data_div) * (long)Z * DM + (long)(neg ? bp.DY + sy : sy) * bp.DP + kx;
+  float2* hp = bank + v * (long)Z * 2 * M + (long)(neg ? Y + sy : sy) * bp.kt + kx;
+  // pass 1: normal matrix and right-hand side
+  float m00 = 0.f, m11 = 0.f;
+  float2 m10 = make_float2(0.f, 0.f), r0 = make_float2(0.f, 0.f), r1 = make_float2(0.f, 0.f);
+  if (band) {
 #pragma unroll 4
-    for (int c = 0; c < Z; ++c) {
+    for (int c = zq; c < Z; c += ZS) {
       const float2 h0 = hp[(long)(2 * c) * M], h1 = hp[(long)(2 * c + 1) * M];
-      const float2 x = dp[(long)c * M];
+      const float2 x = dp[(long)c * DM];
       m00 += h0.x * h0.x + h0.y * h0.y;
       m11 += h1.x * h1.x + h1.y * h1.y;
       m10 = cadd(m10, cmul(cconj(h1), h0));
       r0 = cadd(r0, cmul(cconj(h0), x));
       r1 = cadd(r1, cmul(cconj(h1), x));
     }
+  }
+#pragma unroll
+  for (int o = FW; o < 64; o <<= 1) {
+    m00 += __shfl_xor(m00, o, 64);
+    m11 += __shfl_xor(m11, o, 64);
+    m10.x += __shfl_xor(m10.x, o, 64);
+    m10.y += __shfl_xor(m10.y, o, 64);
+    r0.x += __shfl_xor(r0.x, o, 64);
+    r0.y += __shfl_xor(r0.y, o, 64);
+    r1.x += __shfl_xor(r1.x, o, 64);
+    r1.y += __shfl_xor(r1.y, o, 64);
+  }
+  if (band) {
     const float a00 = m00 + eta, a11 = m11 + eta;
     const float det = a00 * a11 - (m10.x * m10.x + m10.y * m10.y);
     const float idet = __builtin_amdgcn_rcpf(det);   // hardware reciprocal (about 1 ulp)
     // F = M^-1 r with M = [[a00, conj(m10)], [m10, a11]]
     const float2 F0 = cscale(csub(cscale(r0, a11), cmul(cconj(m10), r1)), idet);
     const float2 F1 = cscale(csub(cscale(r1, a00), cmul(m10, r0)), idet);
-    if (band) {
-      const double w = (kx == 0 || 2 * kx == X) ? 1.0 : 2.0;
-      lsum = w * ((double)F0.x * F0.x + (double)F0.y * F0.y);
-      const float ib = (float)(1.0 / s.band_count);
-      const float2 g0 = cscale(F0, -ib);                  // dL/dF_phase*
-      const float2 Y0 = cscale(cscale(g0, a11), idet);    // Y = M^-1 (g0, 0)
-      const float2 Y1 = cscale(cmul(m10, g0), -idet);
+    const double w = (kx == 0 || 2 * kx == sm.nx) ? 1.0 : 2.0;
+    if (zq == 0) lsum = w * ((double)F0.x * F0.x + (double)F0.y * F0.y);
+    const float ib = (float)(1.0 / s.band_count);
+    const float2 g0 = cscale(F0, -ib);                  // dL/dF_phase*
+    const float2 Y0 = cscale(cscale(g0, a11), idet);    // Y = M^-1 (g0, 0)
+    const float2 Y1 = cscale(cmul(m10, g0), -idet);
 #pragma unroll 4
-      for (int c = 0; c < Z; ++c) {
-        const float2 h0 = hp[(long)(2 * c) * M], h1 = hp[(long)(2 * c + 1) * M];
-        const float2 x = dp[(long)c * M];
-        const float2 rc = csub(x, cadd(cmul(h0, F0), cmul(h1, F1)));
-        const float2 hy = cadd(cmul(h0, Y0), cmul(h1, Y1));
-        hp[(long)(2 * c) * M] = csub(cmulconj(rc, Y0), cmulconj(hy, F0));
-        hp[(long)(2 * c + 1) * M] = csub(cmulconj(rc, Y1), cmulconj(hy, F1));
-      }
-    } else {
-      for (int c = 0; c < 2 * Z; ++c) hp[(long)c * M] = make_float2(0.f, 0.f);
+    for (int c = zq; c < Z; c += ZS) {
+      const float2 h0 = hp[(long)(2 * c) * M], h1 = hp[(long)(2 * c + 1) * M];
+      const float2 x = dp[(long)c * DM];
+      const float2 rc = csub(x, cadd(cmul(h0, F0), cmul(h1, F1)));
+      const float2 hy = cadd(cmul(h0, Y0), cmul(h1, Y1));
+      hp[(long)(2 * c) * M] = csub(cmulconj(rc, Y0), cmulconj(hy, F0));
+      hp[(long)(2 * c + 1) * M] = csub(cmulconj(rc, Y1), cmulconj(hy, F1));
+    }
+  } else if (on) {
+    for (int c = zq; c < Z; c += ZS) {
+      hp[(long)(2 * c) * M] = make_float2(0.f, 0.f);
+      hp[(long)(2 * c + 1) * M] = make_float2(0.f, 0.f);
     }
   }
   const double tot = block_sum_d(lsum, red);
   if (threadIdx.x == 0) lpart[v * bpp + blk] = tot;
 }
 
-hipError_t launch_loss_grad(const DevOptics* opt, const TuneState* st, const Sampling& sm, int nv,
-                            const float2* D, float2* bank, double* lpart, int data_div,
+// Workgroups (loss partials) per patch: 64 frequencies each with four plane
+// slices, or 256 where the band is the whole grid (the partials' space).
+static int loss_slices(const BandPlanes& bp, long max_blocks) {
+  return ((long)bp.nb * bp.kt + 63) / 64 <= max_blocks ? 4 : 1;
+}
+
+long loss_blocks(const BandPlanes& bp, long max_blocks) {
+  const long per = 256 / loss_slices(bp, max_blocks);
+  return ((long)bp.nb * bp.kt + per - 1) / per;
+}
+
+hipError_t launch_loss_grad(const TuneState* st, const Sampling& sm, const BandPlanes& bp, int nv,
+                            const float2* D, float2* bank, double* lpart, long max_blocks, int data_div,
                             hipStream_t s) {
-  const long M = (long)sm.ny * (sm.nx / 2 + 1);
-  const long bpp = (M + 255) / 256;
-  { ScopedTiming _t("k_loss_grad", s);
-  hipLaunchKernelGGL(k_loss_grad, dim3((unsigned)(bpp * nv)), dim3(256), 0, s, opt, st, sm, D, bank,
-                     lpart, bpp, data_div); }
+  if (bp.kt < 1 || bp.kt > sm.nx / 2 + 1 || bp.nb < 1 || bp.nb > sm.ny || bp.nb > bp.DY || bp.DP < bp.kt ||
+      (bp.nb < sm.ny && bp.nb != 2 * bp.ky + 1) || (bp.nb == sm.ny && bp.DY != sm.ny))
+    return hipErrorInvalidValue;
+  const long bpp = loss_blocks(bp, max_blocks);
+  if (bpp > max_blocks) return hipErrorInvalidValue;
+  ScopedTiming _t("k_loss_grad", s);
+  if (loss_slices(bp, max_blocks) == 4)
+    hipLaunchKernelGGL(k_loss_grad<4>, dim3((unsigned)(bpp * nv)), dim3(256), 0, s, st, sm, bp, D, bank,
+                       lpart, bpp, data_div);
+  else
+    hipLaunchKernelGGL(k_loss_grad<1>, dim3((unsigned)(bpp * nv)), dim3(256), 0, s, st, sm, bp, D, bank,
+                       lpart, bpp, data_div);
   return hipGetLastError();
 }
 
@@ -231,7 +275,8 @@ hipError_t launch_recon_grad(float2* bank, float2* D, const float2* G, const flo
 // in the compact columns of the field kernel: XC kept, last non-negative KP;
 // the others are zero, and so are u_A, u_B there: only the kept columns are
 // written back);
-// g: [v][Z][2][Y][Xh], the half spectra of dL/dH* after the inverse Y pass.  For
+// g: [v][Z][2][Y][KT], the half spectra of dL/dH* after the inverse Y pass
+// (columns k < KT kept, the others zero).  For
 // each row the kernel forms Gamma = Gamma_phase + i Gamma_abs in one inverse X
 // transform (the two real rows packed into one complex line), then replaces
 // field 0 by the inverse X transform of u_A = conj(Gamma b)/(N I_bg) and field 1
@@ -243,13 +288,13 @@ __global__ __launch_bounds__(1024) void k_tf_rows_bwd(const double* __restrict__
                                                       float2* __restrict__ ab,
                                                       const float2* __restrict__ g,
                                                       double* __restrict__ dpart, int rows_per_wg,
-                                                      long wg_per_patch, int XC, int KP, FftPlan plan) {
+                                                      long wg_per_patch, int XC, int KP, int KT,
+                                                      FftPlan plan) {
   extern __shared__ float2 smem[];
   __shared__ double red[kMaxThreads / 64];
   __shared__ double ibg_s;
   const int Y = sm.ny, Z = sm.nz;
   const int X = NS > 0 ? NS : sm.nx;   // compile-time length for the index arithmetic
-  const int Xh = X / 2 + 1;
   float2* tw = smem;
   float2* buf = smem + X;
   const int tid = threadIdx.x, nthr = blockDim.x;
@@ -262,7 +307,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_bwd(const double* __restrict__
   const int z0 = (int)(row0 / Y), y0 = (int)(row0 - (long)z0 * Y);
   float2* a_src = ab + (v * 2 + 0) * rpp * XC;
   float2* b_src = ab + (v * 2 + 1) * rpp * XC;
-  const float2* g_src = g + v * rpp * 2 * Xh;
+  const float2* g_src = g + v * rpp * 2 * KT;
   const int neg0 = X - (XC - KP - 1);   // first kept negative-frequency column
   auto kept = [&](int i) { return i <= KP || i >= neg0; };
   auto ccol = [&](int i) { return i <= KP ? i : max(i - (X - XC), KP); };   // clamped compact column
@@ -300,8 +345,12 @@ __global__ __launch_bounds__(1024) void k_tf_rows_bwd(const double* __restrict__
         int y = y0 + r, z = z0;
         while (y >= Y) { y -= Y; ++z; }
         const int kk = 2 * i > X ? X - i : i;
-        const float2* gp = g_src + ((long)(z * 2 + 0) * Y + y) * Xh + kk;   // absorption: Y Xh on
-        const float2 P = gp[0], A = gp[(long)Y * Xh];
+        const float2* gp = g_src + ((long)(z * 2 + 0) * Y + y) * KT + kk;   // absorption: Y KT on
+        float2 P = make_float2(0.f, 0.f), A = P;
+        if (kk < KT) {   // the condition depends on the index only
+          P = gp[0];
+          A = gp[(long)Y * KT];
+        }
         vg[q] = make_float4(P.x, P.y, A.x, A.y);
       }
     }
@@ -380,6 +429,8 @@ long bwd_wg_per_patch(const Sampling& sm) {
 
 hipError_t launch_tf_rows_bwd(const double* partials, const Sampling& sm, int nv, float2* ab,
                               const float2* g, double* dpart, hipStream_t s, const LatSupport* sup) {
+  const int KT = sup ? sup->kt : sm.nx / 2 + 1;
+  if (KT < 1 || KT > sm.nx / 2 + 1) return hipErrorInvalidValue;
   if (3L * sm.nx > kMaxElems) return hipErrorInvalidValue;
   const LatSupport ls = sup ? *sup : full_support(sm);
   if (ls.xc < 1 || ls.xc > sm.nx || ls.kp < 0 || ls.kp >= ls.xc || ls.ly != sm.ny || ls.lx != sm.nx)
@@ -395,7 +446,7 @@ hipError_t launch_tf_rows_bwd(const double* partials, const Sampling& sm, int nv
 #define X_(NN)                                                                                   \
   case NN:                                                                                       \
     hipLaunchKernelGGL((k_tf_rows_bwd<NN>), dim3((unsigned)(wpp * nv)), dim3(thr), lds, s, partials, \
-                       tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, plan);                 \
+                       tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, KT, plan);             \
     return hipGetLastError();
   switch (sm.nx) {
     WO_LATERAL_SIZES(X_)
@@ -404,7 +455,7 @@ hipError_t launch_tf_rows_bwd(const double* partials, const Sampling& sm, int nv
   }
 #undef X_
   hipLaunchKernelGGL((k_tf_rows_bwd<0>), dim3((unsigned)(wpp * nv)), dim3(thr), lds, s, partials,
-                     tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, plan);
+                     tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, KT, plan);
   return hipGetLastError();
 }
 
@@ -480,7 +531,7 @@ __global__ __launch_bounds__(1024) void k_tf_grad_y(const DevOptics* __restrict_
       const int c = x0 + w;   // compact column of the fields
       if (c >= XC) continue;
       const int kx = field_column(c, KP, X, XC);
-      const double fy = fftfreq(ky, Y, sm.dy), fx = fftfreq(kx, X, sm.dx);
+      const double fy = lateral_freq(ky, Y, sm.Ly), fx = lateral_freq(kx, X, sm.Lx);
       const double rp = sqrt(fy * fy + fx * fx);
       const double P = det_pupil(o, dax, fy, fx, hw);
       double dP, dPt, dPa;                                           // dP / d(NA_det, tilt, azimuth)
@@ -604,7 +655,7 @@ __global__ __launch_bounds__(1024) void k_tf_grad_y(const DevOptics* __restrict_
       if (e >= Y * W || Qe[i] == 0.0) continue;
       const int ky = e >> wsh, kx = field_column(x0 + (e & (W - 1)), KP, X, XC);
       double zj[7], dwdna;
-      zernike_terms(o, fftfreq(ky, Y, sm.dy), fftfreq(kx, X, sm.dx), zj, &dwdna);
+      zernike_terms(o, lateral_freq(ky, Y, sm.Ly), lateral_freq(kx, X, sm.Lx), zj, &dwdna);
       g[1] -= tp * dwdna * Qe[i];
 #pragma unroll
       for (int j = 0; j < 7; ++j) ga[j] -= tp * zj[j] * Qe[i];
@@ -770,7 +821,7 @@ __global__ __launch_bounds__(256) void k_adam(DevOptics* __restrict__ opt,
 
 hipError_t launch_adam(DevOptics* opt, TuneState* st, const Sampling& sm, int nv,
                        const double* ppart, const double* lpart, const double* dpart,
-                       const double* gpart, const double* ipart, int update, hipStream_t s,
+                       const double* gpart, const double* ipart, long lbpp, int update, hipStream_t s,
                        const LatSupport* sup) {
   const LatSupport ls = sup ? *sup : full_support(sm);
   const long tiles_x = pupil_tiles(sm, ls);
@@ -779,7 +830,7 @@ hipError_t launch_adam(DevOptics* opt, TuneState* st, const Sampling& sm, int nv
   const long gt = grad_tiles(sm, &ls);
   const long gn = (long)((sm.nz + ZC - 1) / ZC) * gt;
   hipLaunchKernelGGL(k_adam, dim3(nv), dim3(256), 0, s, opt, st, sm, ppart, tiles_x, gt, lpart,
-                     loss_blocks(sm), dpart, bwd_wg_per_patch(sm), gpart, gn, ipart, update); }
+                     lbpp, dpart, bwd_wg_per_patch(sm), gpart, gn, ipart, update); }
   return hipGetLastError();
 }
 

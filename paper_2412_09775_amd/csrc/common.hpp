@@ -163,6 +163,25 @@ __device__ __forceinline__ void dft6(float2* v, float s) {
   v[5] = csub(e[2], t2);
 }
 
+// 10 = 2 x 5, as dft6: X[k] = E[k] + W10^k O[k], X[k + 5] = E[k] - W10^k O[k],
+// W10 = exp(s i pi / 5).
+__device__ __forceinline__ void dft10(float2* v, float s) {
+  const float c1 = 0.80901699437494742410f, s1 = 0.58778525229247312917f;   // cos, sin of pi / 5
+  const float c2 = 0.30901699437494742410f, s2 = 0.95105651629515357212f;   // of 2 pi / 5
+  float2 e[5] = {v[0], v[2], v[4], v[6], v[8]}, o[5] = {v[1], v[3], v[5], v[7], v[9]};
+  dft5(e, s);
+  dft5(o, s);
+  o[1] = make_float2(c1 * o[1].x - s * s1 * o[1].y, c1 * o[1].y + s * s1 * o[1].x);
+  o[2] = make_float2(c2 * o[2].x - s * s2 * o[2].y, c2 * o[2].y + s * s2 * o[2].x);
+  o[3] = make_float2(-c2 * o[3].x - s * s2 * o[3].y, -c2 * o[3].y + s * s2 * o[3].x);
+  o[4] = make_float2(-c1 * o[4].x - s * s1 * o[4].y, -c1 * o[4].y + s * s1 * o[4].x);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    v[k] = cadd(e[k], o[k]);
+    v[k + 5] = csub(e[k], o[k]);
+  }
+}
+
 // 16 = 4 x 4: with n = 4 n1 + n2 and k = k1 + 4 k2, Y_n2[k1] = DFT4 over n1 of
 // v[4 n1 + n2] times W16^(n2 k1), and X[k1 + 4 k2] = DFT4 over n2 of Y_n2[k1]
 // (W16 = exp(s 2 pi i / 16); the products n2 k1 are 1, 2, 3, 4, 6 and 9).
@@ -206,6 +225,7 @@ __device__ __forceinline__ void dft_small(float2* v, float s) {
   else if constexpr (R == 5) dft5(v, s);
   else if constexpr (R == 6) dft6(v, s);
   else if constexpr (R == 8) dft8(v, s);
+  else if constexpr (R == 10) dft10(v, s);
   else if constexpr (R == 16) dft16(v, s);
 }
 
@@ -218,7 +238,7 @@ __device__ __forceinline__ void dft_small(float2* v, float s) {
 struct TwPair {
   float c, s;
 };
-constexpr int kTwSizes[] = {16, 24, 32, 48, 64, 96, 128, 160, 192, 240, 256, 320, 384, 480, 512, 1024};
+constexpr int kTwSizes[] = {16, 24, 32, 48, 64, 80, 96, 128, 160, 192, 240, 256, 320, 384, 480, 512, 1024};
 constexpr int kTwCount = sizeof(kTwSizes) / sizeof(kTwSizes[0]);
 constexpr int tw_offset(int n) {
   int off = 0;
@@ -782,6 +802,10 @@ struct Sampling {
   int model;
   int nz, ny, nx;
   double dz, dy, dx;
+  // Physical lateral extents of the grid, ny dy and nx dx: frequency index k is
+  // k / extent whatever number of points samples the field of view (the
+  // auto-tune runs on coarser grids of the same extents).
+  double Ly, Lx;
   int aberrated = 0;   // some patch has detection aberrations (selects the kernel variant)
   int det_grad = 0;    // the gradient kernels also form d/d(det_tilt, det_azimuth)
 };
@@ -790,6 +814,11 @@ __host__ __device__ __forceinline__ double fftfreq(int k, int n, double d) {
   const double val = 1.0 / ((double)n * d);
   const int ks = (k < (n + 1) / 2) ? k : k - n;
   return (double)ks * val;
+}
+
+// fftfreq of an n-point axis of physical extent L.
+__device__ __forceinline__ double lateral_freq(int k, int n, double L) {
+  return (double)(k < (n + 1) / 2 ? k : k - n) * (1.0 / L);
 }
 
 // e / d for 0 <= e < 2^20 and 1 <= d <= 2^13, given inv_d = 1.0f / d: the exact
@@ -896,7 +925,7 @@ __host__ __device__ __forceinline__ double det_radius(const DevOptics& o) {
 }
 
 __device__ __forceinline__ double soft_halfwidth(const DevOptics& o, const Sampling& sm) {
-  const double dnu = fmin(1.0 / ((double)sm.nx * sm.dx), 1.0 / ((double)sm.ny * sm.dy));
+  const double dnu = fmin(1.0 / sm.Lx, 1.0 / sm.Ly);
   return o.edge_width * dnu;
 }
 
@@ -965,6 +994,9 @@ struct StaticPlan {
       const int np = (t - 4) / 3 + 1;
       return q < np - 1 ? 8 : (q == np - 1 ? 16 : 0);
     }
+    // 80 = 8 10 and 480 = 8 6 10: one pass fewer than 8 2 5 and 8 4 3 5
+    if (N == 80) return q == 0 ? 8 : (q == 1 ? 10 : 0);
+    if (N == 480) return q == 0 ? 8 : (q == 1 ? 6 : (q == 2 ? 10 : 0));
     int m = N, p = 0;
     const int order[6] = {8, 4, 6, 2, 3, 5};
     for (int i = 0; i < 6; ++i) {
@@ -1260,7 +1292,8 @@ __device__ __forceinline__ void fft_lines(float2* lds, const LdsLines& L, const 
 
 }  // namespace wo
 
-// Transform lengths with compiled FFT stages (lateral sizes and axial sizes).
-#define WO_LATERAL_SIZES(X) X(64) X(128) X(160) X(192) X(240) X(256) X(320) X(384) X(480) X(512) X(1024)
+// Transform lengths with compiled FFT stages (lateral sizes and axial sizes;
+// 80 and 96 points carry the auto-tune of 128- and 160-pixel tiles).
+#define WO_LATERAL_SIZES(X) X(64) X(80) X(96) X(128) X(160) X(192) X(240) X(256) X(320) X(384) X(480) X(512) X(1024)
 #define WO_AXIAL_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96)
-#define WO_ALL_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(160) X(192) X(240) X(256) X(320) X(384) X(480) X(512) X(1024)
+#define WO_ALL_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(80) X(96) X(128) X(160) X(192) X(240) X(256) X(320) X(384) X(480) X(512) X(1024)

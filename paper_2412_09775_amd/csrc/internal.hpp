@@ -210,7 +210,19 @@ hipError_t launch_set_coupling(Coupling* dst, const Coupling* host, int n, hipSt
 
 // Auto-tune (thin model).
 hipError_t launch_set_tune(TuneState* dst, const TuneState* host, int n, hipStream_t s);
+// Loss partials per patch a whole-grid band takes at most.
 long loss_blocks(const Sampling& sm);
+// The frequencies the mid-band loss visits: half-spectrum columns kx < kt of
+// the nb band rows (rows 0..ky and the nb - ky - 1 last ones of the transform;
+// nb = ny: every row) of planes [ny][kt]; the data planes are [DY][DP], their
+// negative rows counted from the end.
+struct BandPlanes {
+  int kt, ky, nb;
+  int DY;
+  long DP;
+};
+// Loss partials per patch of a launch that has room for max_blocks.
+long loss_blocks(const BandPlanes& bp, long max_blocks);
 long bwd_wg_per_patch(const Sampling& sm);
 // Column tiles of the gradient kernel over the support's compact columns (all
 // columns: sup = NULL); its partials hold nz * tiles * 4 (at most) and
@@ -219,8 +231,8 @@ long grad_tiles(const Sampling& sm, const LatSupport* sup = nullptr);
 // Column tiles of the field kernel over the support's compact columns: the
 // pupil-sum partials per patch.
 long pupil_tiles(const Sampling& sm, const LatSupport& ls);
-hipError_t launch_loss_grad(const DevOptics* opt, const TuneState* st, const Sampling& sm, int nv,
-                            const float2* D, float2* bank, double* lpart, int data_div,
+hipError_t launch_loss_grad(const TuneState* st, const Sampling& sm, const BandPlanes& bp, int nv,
+                            const float2* D, float2* bank, double* lpart, long max_blocks, int data_div,
                             hipStream_t s);
 // Gradient of a loss of the 3D reconstruction per frequency (bank [v][Z][2][M]
 // the label-free pair after its Z transform, D [v][C][Z][M] the data spectrum,
@@ -230,7 +242,8 @@ hipError_t launch_recon_grad(float2* bank, float2* D, const float2* G, const flo
                              const Sampling& sm, int npatch, float eta, double n_full, int want_dd,
                              hipStream_t s);
 // The backward kernels and Adam take the fields' compact columns (sup; NULL:
-// every column), as the field kernel wrote them.
+// every column), as the field kernel wrote them; the backward rows read the
+// columns k < sup->kt of g (row pitch sup->kt).
 hipError_t launch_tf_rows_bwd(const double* partials, const Sampling& sm, int nv, float2* ab,
                               const float2* g, double* dpart, hipStream_t s,
                               const LatSupport* sup = nullptr);
@@ -238,7 +251,7 @@ hipError_t launch_tf_grad_y(const DevOptics* opt, const Sampling& sm, int nv, co
                             double* gpart, double* ipart, hipStream_t s, const LatSupport* sup = nullptr);
 hipError_t launch_adam(DevOptics* opt, TuneState* st, const Sampling& sm, int nv,
                        const double* ppart, const double* lpart, const double* dpart,
-                       const double* gpart, const double* ipart, int update, hipStream_t s,
+                       const double* gpart, const double* ipart, long lbpp, int update, hipStream_t s,
                        const LatSupport* sup = nullptr);
 // Per patch, the start with the lowest loss: its optics into ropt[i] and the
 // patch's eta into eta[i].

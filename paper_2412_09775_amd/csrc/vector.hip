@@ -74,8 +74,8 @@ __global__ __launch_bounds__(256) void k_vec_spectra(const DevOptics* __restrict
   const int F = 6 + 3 * NS;
   const long plane = (long)LY * XC;
   float2* base = fields + patch * (long)F * Z * plane + (long)ky * XC + c;
-  const double fy = (double)(ky < (LY + 1) / 2 ? ky : ky - LY) / ((double)sm.ny * sm.dy);
-  const double fx = fftfreq(kx, X, sm.dx);
+  const double fy = (double)(ky < (LY + 1) / 2 ? ky : ky - LY) / sm.Ly;
+  const double fx = lateral_freq(kx, X, sm.Lx);
   const double hw = soft_halfwidth(o, sm);
   const double km = o.n_medium / o.wavelength;
   const DetAxis dax = det_axis(o);
