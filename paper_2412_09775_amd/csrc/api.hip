@@ -1079,7 +1079,10 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
   char* w = ws + g.base;
   const int np = L.np, nv = L.nv;
   std::vector<DevOptics> hopt(nv);
-  std::vector<TuneState> hst(nv);
+  std::vector<TuneInit> hst(np);
+  // the box of theta: shared but for the cap on NA_det (clamp_box)
+  TuneShared shared;
+  memset(&shared, 0, sizeof(shared));
   for (int j = 0; j < np; ++j) {
     const int i = g.idx[j];
     double blo[4], bhi[4];
@@ -1091,6 +1094,17 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
     const double nuc = (nu_c && nu_c[i] > 0) ? nu_c[i] : (o[i].na_det + o[i].na_ill) / o[i].wavelength;
     const double bc = band_count(&o[i], nuc);
     if (bc < 1) return WO_EINVAL;
+    hst[j] = TuneInit{eta[i], nuc, bc, bhi[1]};
+    if (j == 0) {
+      for (int k = 0; k < 4; ++k) {
+        shared.lr[k] = lr ? lr[k] : 0.0;
+        shared.lo[k] = blo[k];
+        shared.hi[k] = bhi[k];
+      }
+      shared.lr_ab = lr_ab;
+      shared.bound_ab = bound_ab > 0.0 ? bound_ab : 1.0;
+      shared.mask = mask;
+    }
     for (int s = 0; s < starts; ++s) {
       const int v = j * starts + s;
       const long gv = (long)i * starts + s;
@@ -1101,19 +1115,6 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
         hopt[v].tilt_zenith = theta0[4 * gv + 2];
         hopt[v].tilt_azimuth = theta0[4 * gv + 3];
       }
-      TuneState& t = hst[v];
-      memset(&t, 0, sizeof(t));
-      for (int k = 0; k < 4; ++k) {
-        t.lr[k] = lr ? lr[k] : 0.0;
-        t.lo[k] = blo[k];
-        t.hi[k] = bhi[k];
-      }
-      t.lr_ab = lr_ab;
-      t.bound_ab = bound_ab > 0.0 ? bound_ab : 1.0;
-      t.eta = eta[i];
-      t.nu_c = nuc;
-      t.band_count = bc;
-      t.mask = mask;
       // every virtual patch must describe valid optics at its start
       wo_optics ov = o[i];
       ov.defocus = hopt[v].defocus;
@@ -1125,7 +1126,7 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
     }
   }
   WO_TRY(launch_set_params((DevOptics*)(w + L.off_opt), hopt.data(), nv, hs));
-  WO_TRY(launch_set_tune((TuneState*)(w + L.off_st), hst.data(), nv, hs));
+  WO_TRY(launch_set_tune((TuneState*)(w + L.off_st), hst.data(), shared, np, starts, hs));
   const long Z = g.rep->nz, Y = g.rep->ny, Xh = g.rep->nx / 2 + 1, DP = g.band.DP;
   float2* D = (float2*)(w + L.off_D);
   for (auto r : index_runs(g.idx)) {
@@ -1874,17 +1875,17 @@ extern "C" int wo_reconstruct_grad(const wo_optics* o, int32_t n, const float* d
   Coupling* cpl = is_pol5(s) ? (Coupling*)(w + L.cpl) : nullptr;
   {
     std::vector<DevOptics> h(n);
-    std::vector<TuneState> t(n);
+    std::vector<TuneInit> t(n);
+    TuneShared shared;
+    memset(&shared, 0, sizeof(shared));
     std::vector<Coupling> hc(n);
     for (int i = 0; i < n; ++i) {
       h[i] = dev_optics(o[i]);
-      memset(&t[i], 0, sizeof(TuneState));
-      t[i].band_count = 1.0;   // no loss of its own: the loss partials are zero
-      t[i].eta = eta;
+      t[i] = TuneInit{eta, 0.0, 1.0, 0.0};   // no loss of its own: the loss partials are zero
       if (cpl) hc[i] = coupling_of(o[i].swing);
     }
     WO_TRY(launch_set_params(dopt, h.data(), n, hs));
-    WO_TRY(launch_set_tune(tst, t.data(), n, hs));
+    WO_TRY(launch_set_tune(tst, t.data(), shared, n, 1, hs));
     if (cpl) WO_TRY(launch_set_coupling(cpl, hc.data(), n, hs));
   }
   Sampling sm = sampling_of(o);

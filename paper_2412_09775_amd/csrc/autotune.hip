@@ -741,8 +741,34 @@ hipError_t launch_tf_grad_y(const DevOptics* opt, const Sampling& sm, int nv, co
 // ------------------------------------------------------------------ reduction + Adam
 
 // One workgroup per virtual patch: total loss and gradient from the partials,
-// then (if update) one Adam step with bias correction, mask and box.
-__global__ __launch_bounds__(256) void k_adam(DevOptics* __restrict__ opt,
+// then (if update) one Adam step with bias correction, mask and box.  A chain
+// of short reductions at the end of every iteration, bound by latency: all
+// waves share the longest (the backward rows' partials), then each wave takes
+// whole sums of the others with no barrier between them, and one lane per
+// parameter does its Adam step.  (One reduction after the other with a
+// barrier pair each, the steps on one thread: 13-16 us a launch, 5 us so.)
+__device__ __forceinline__ double wave_sum_d(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+// Sum of p[(i0 + i) * stride], i = t, t + step, ... < n: four running sums, so
+// that the loads are in flight together.
+__device__ __forceinline__ double strided_sum(const double* __restrict__ p, long n, long stride, int t,
+                                              int step) {
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  long i = t;
+  for (; i + 3 * step < n; i += 4 * step) {
+    a0 += p[i * stride];
+    a1 += p[(i + step) * stride];
+    a2 += p[(i + 2 * step) * stride];
+    a3 += p[(i + 3 * step) * stride];
+  }
+  for (; i < n; i += step) a0 += p[i * stride];
+  return (a0 + a1) + (a2 + a3);
+}
+
+constexpr int kAdamThreads = 512;
+__global__ __launch_bounds__(kAdamThreads) void k_adam(DevOptics* __restrict__ opt,
                                               TuneState* __restrict__ st, Sampling sm,
                                               const double* __restrict__ ppart, long tiles_x,
                                               long gtiles,
@@ -750,73 +776,77 @@ __global__ __launch_bounds__(256) void k_adam(DevOptics* __restrict__ opt,
                                               const double* __restrict__ dpart, long dwpp,
                                               const double* __restrict__ gpart, long gn,
                                               const double* __restrict__ ipart, int update) {
-  __shared__ double red[4];
+  constexpr int NW = kAdamThreads / 64;
+  __shared__ double dred[NW], tot[2 + kGradAll + kThetaAll];
   const long v = blockIdx.x;
-  const int tid = threadIdx.x;
-  double acc;
-  acc = 0.0;
-  for (long i = tid; i < lbpp; i += blockDim.x) acc += lpart[v * lbpp + i];
-  const double lsum = block_sum_d(acc, red);
-  acc = 0.0;
-  for (long i = tid; i < dwpp; i += blockDim.x) acc += dpart[v * dwpp + i];
-  const double dsum = block_sum_d(acc, red);
-  acc = 0.0;
-  for (long i = tid; i < tiles_x; i += blockDim.x) acc += ppart[v * tiles_x + i];
-  const double ibg = block_sum_d(acc, red);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int TH = sm.det_grad ? kThetaAll : 4;
   const int KG = TH + (sm.aberrated ? 7 : 0);
-  double gj[kGradAll], dij[kThetaAll];
-  for (int j = 0; j < KG; ++j) {
-    acc = 0.0;
-    for (long i = tid; i < gn; i += blockDim.x) acc += gpart[(v * gn + i) * KG + j];
-    gj[j] = block_sum_d(acc, red);
+  const double dw = wave_sum_d(strided_sum(dpart + v * dwpp, dwpp, 1, tid, kAdamThreads));
+  if (lane == 0) dred[wave] = dw;
+  // sum q: 0 the loss, 1 I_bg, then the KG gradient sums, then dI_bg/dtheta
+  for (int q = wave; q < 2 + KG + TH; q += NW) {
+    const double* p;
+    long n, stride = 1;
+    if (q == 0) {
+      p = lpart + v * lbpp;
+      n = lbpp;
+    } else if (q == 1) {
+      p = ppart + v * tiles_x;
+      n = tiles_x;
+    } else if (q < 2 + KG) {
+      p = gpart + v * gn * KG + (q - 2);
+      n = gn;
+      stride = KG;
+    } else {
+      p = ipart + v * gtiles * TH + (q - 2 - KG);
+      n = gtiles;
+      stride = TH;
+    }
+    const double t = wave_sum_d(strided_sum(p, n, stride, lane, 64));
+    if (lane == 0) tot[q] = t;
   }
-  for (int j = 0; j < TH; ++j) {
-    acc = 0.0;
-    for (long i = tid; i < gtiles; i += blockDim.x) acc += ipart[(v * gtiles + i) * TH + j];
-    dij[j] = block_sum_d(acc, red);
-  }
-  if (tid != 0) return;
-  TuneState s = st[v];
+  __syncthreads();
+  if (tid >= kThetaAll + 7) return;   // lanes 0..5 theta, 6..12 the aberration coefficients
+  double dsum = 0.0;
+  for (int w = 0; w < NW; ++w) dsum += dred[w];
+  const double ibg = tot[1];
   const double N = (double)sm.ny * sm.nx;
-  const double loss = -lsum / s.band_count;
-  double grad[kThetaAll] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int j = 0; j < TH; ++j) grad[j] = gj[j] - 4.0 * dsum / (N * ibg * ibg) * dij[j];
-  s.loss = loss;
-  for (int j = 0; j < kThetaAll; ++j) s.grad[j] = grad[j];
+  TuneState& s = st[v];
+  const int step = s.t + 1;   // every lane reads it before lane 0 stores it (one wave)
+  const int mask = s.mask;
+  const bool theta = tid < kThetaAll;
+  const int j = theta ? tid : tid - kThetaAll;
+  double grad = 0.0;
   // I_bg = sum S |P|^2 does not depend on the aberration
-  for (int j = 0; j < 7; ++j) s.gab[j] = KG > TH ? gj[TH + j] : 0.0;
-  if (update) {
-    DevOptics o = opt[v];
-    double th[4] = {o.defocus, o.na_det, o.tilt_zenith, o.tilt_azimuth};
-    s.t += 1;
-    const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
-    const double c1 = 1.0 - pow(b1, (double)s.t), c2 = 1.0 - pow(b2, (double)s.t);
-    for (int j = 0; j < 4; ++j) {
-      const double gm = ((s.mask >> j) & 1) ? grad[j] : 0.0;
-      s.m[j] = b1 * s.m[j] + (1.0 - b1) * gm;
-      s.v[j] = b2 * s.v[j] + (1.0 - b2) * gm * gm;
-      const double mh = s.m[j] / c1, vh = s.v[j] / c2;
-      double t = th[j] - s.lr[j] * mh / (sqrt(vh) + eps);
-      t = t < s.lo[j] ? s.lo[j] : (t > s.hi[j] ? s.hi[j] : t);
-      th[j] = t;
-    }
-    opt[v].defocus = th[0];
-    opt[v].na_det = th[1];
-    opt[v].tilt_zenith = th[2];
-    opt[v].tilt_azimuth = th[3];
-    for (int j = 0; j < 7; ++j) {
-      if (!((s.mask >> (4 + j)) & 1)) continue;
-      const double gm = s.gab[j];
-      s.mab[j] = b1 * s.mab[j] + (1.0 - b1) * gm;
-      s.vab[j] = b2 * s.vab[j] + (1.0 - b2) * gm * gm;
-      const double mh = s.mab[j] / c1, vh = s.vab[j] / c2;
-      double t = (double)o.zern[j] - s.lr_ab * mh / (sqrt(vh) + eps);
-      t = t < -s.bound_ab ? -s.bound_ab : (t > s.bound_ab ? s.bound_ab : t);
-      opt[v].zern[j] = (float)t;
-    }
+  if (theta && j < TH) grad = tot[2 + j] - 4.0 * dsum / (N * ibg * ibg) * tot[2 + KG + j];
+  if (!theta && KG > TH) grad = tot[2 + TH + j];
+  if (theta) s.grad[j] = grad; else s.gab[j] = grad;
+  if (tid == 0) s.loss = -tot[0] / s.band_count;
+  if (!update) return;
+  const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
+  const double c1 = 1.0 - pow(b1, (double)step), c2 = 1.0 - pow(b2, (double)step);
+  if (tid == 0) s.t = step;
+  DevOptics& o = opt[v];
+  if (theta && j < 4) {
+    const double gm = ((mask >> j) & 1) ? grad : 0.0;
+    const double m = b1 * s.m[j] + (1.0 - b1) * gm;
+    const double vv = b2 * s.v[j] + (1.0 - b2) * gm * gm;
+    s.m[j] = m;
+    s.v[j] = vv;
+    double* th = j == 0 ? &o.defocus : (j == 1 ? &o.na_det : (j == 2 ? &o.tilt_zenith : &o.tilt_azimuth));
+    double t = *th - s.lr[j] * (m / c1) / (sqrt(vv / c2) + eps);
+    t = t < s.lo[j] ? s.lo[j] : (t > s.hi[j] ? s.hi[j] : t);
+    *th = t;
+  } else if (!theta && ((mask >> (4 + j)) & 1)) {
+    const double m = b1 * s.mab[j] + (1.0 - b1) * grad;
+    const double vv = b2 * s.vab[j] + (1.0 - b2) * grad * grad;
+    s.mab[j] = m;
+    s.vab[j] = vv;
+    double t = (double)o.zern[j] - s.lr_ab * (m / c1) / (sqrt(vv / c2) + eps);
+    t = t < -s.bound_ab ? -s.bound_ab : (t > s.bound_ab ? s.bound_ab : t);
+    o.zern[j] = (float)t;
   }
-  st[v] = s;
 }
 
 hipError_t launch_adam(DevOptics* opt, TuneState* st, const Sampling& sm, int nv,
@@ -829,7 +859,7 @@ hipError_t launch_adam(DevOptics* opt, TuneState* st, const Sampling& sm, int nv
   const int ZC = grad_z_chunk(sm, nv);
   const long gt = grad_tiles(sm, &ls);
   const long gn = (long)((sm.nz + ZC - 1) / ZC) * gt;
-  hipLaunchKernelGGL(k_adam, dim3(nv), dim3(256), 0, s, opt, st, sm, ppart, tiles_x, gt, lpart,
+  hipLaunchKernelGGL(k_adam, dim3(nv), dim3(kAdamThreads), 0, s, opt, st, sm, ppart, tiles_x, gt, lpart,
                      lbpp, dpart, bwd_wg_per_patch(sm), gpart, gn, ipart, update); }
   return hipGetLastError();
 }

@@ -790,6 +790,18 @@ struct TuneState {
   int pad[2];
 };
 
+// What a virtual patch's starting TuneState takes from its patch, and what the
+// call's patches share.
+struct TuneInit {
+  double eta, nu_c, band_count;
+  double hi_na;   // upper bound of NA_det (capped inside the patch's shell)
+};
+struct TuneShared {
+  double lr[4], lo[4], hi[4];
+  double lr_ab, bound_ab;
+  int mask;
+};
+
 // Gradient components per partial: theta (4), then the 7 aberration coefficients
 // when the gradient kernels run aberration-aware.
 constexpr int kGradAll = 13;

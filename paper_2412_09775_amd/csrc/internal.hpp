@@ -209,7 +209,9 @@ hipError_t launch_tf_rows_fluor(const double* partials, const Sampling& sm, int 
 hipError_t launch_set_coupling(Coupling* dst, const Coupling* host, int n, hipStream_t s);
 
 // Auto-tune (thin model).
-hipError_t launch_set_tune(TuneState* dst, const TuneState* host, int n, hipStream_t s);
+// States of np patches x `starts` virtual patches (moments and step count zero).
+hipError_t launch_set_tune(TuneState* dst, const TuneInit* host, const TuneShared& shared, int np,
+                           int starts, hipStream_t s);
 // Loss partials per patch a whole-grid band takes at most.
 long loss_blocks(const Sampling& sm);
 // The frequencies the mid-band loss visits: half-spectrum columns kx < kt of

@@ -15,29 +15,38 @@ namespace wo {
 
 // ------------------------------------------------------------------ parameters
 
-// Per-patch optics travel as kernel arguments (a batch of up to 8 records per
-// launch), so setting them needs no host staging buffer and stays
-// asynchronous on the stream.
+// Per-patch optics travel as kernel arguments, so setting them needs no host
+// staging buffer and stays asynchronous on the stream: 29 records of 120 bytes
+// fill a launch's 4 KiB (256 patches of a tune: 9 launches of about 2 us, 32
+// with the 8 records of before); a short argument block serves one or two.
+template <int NB>
 struct OpticsBatch {
-  DevOptics o[8];
+  DevOptics o[NB];
 };
-static_assert(sizeof(OpticsBatch) <= 3584, "kernel arguments are limited to 4 KiB");
+constexpr int kOpticsBatch = 29;
+static_assert(sizeof(OpticsBatch<kOpticsBatch>) <= 3584, "kernel arguments are limited to 4 KiB");
 
-__global__ void k_set_params(DevOptics* dst, OpticsBatch b, int count) {
+template <int NB>
+__global__ void k_set_params(DevOptics* dst, OpticsBatch<NB> b, int count) {
   const int i = threadIdx.x;
   if (i < count) dst[i] = b.o[i];
 }
 
-hipError_t launch_set_params(DevOptics* dst, const DevOptics* host, int n, hipStream_t s) {
-  for (int i0 = 0; i0 < n; i0 += 8) {
-    OpticsBatch b;
-    const int cnt = n - i0 < 8 ? n - i0 : 8;
+template <int NB>
+static hipError_t set_params(DevOptics* dst, const DevOptics* host, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += NB) {
+    OpticsBatch<NB> b;
+    const int cnt = n - i0 < NB ? n - i0 : NB;
     for (int j = 0; j < cnt; ++j) b.o[j] = host[i0 + j];
-    hipLaunchKernelGGL(k_set_params, dim3(1), dim3(64), 0, s, dst + i0, b, cnt);
+    hipLaunchKernelGGL(k_set_params<NB>, dim3(1), dim3(64), 0, s, dst + i0, b, cnt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_set_params(DevOptics* dst, const DevOptics* host, int n, hipStream_t s) {
+  return n <= 2 ? set_params<2>(dst, host, n, s) : set_params<kOpticsBatch>(dst, host, n, s);
 }
 
 struct CouplingBatch {
@@ -62,22 +71,48 @@ hipError_t launch_set_coupling(Coupling* dst, const Coupling* host, int n, hipSt
   return hipSuccess;
 }
 
+// The starting state of each virtual patch from what differs between patches
+// (32 bytes, 96 patches a launch) and what they share.
+constexpr int kTuneBatch = 96;
 struct TuneBatch {
-  TuneState t[8];
+  TuneInit t[kTuneBatch];
 };
-static_assert(sizeof(TuneBatch) <= 3584, "kernel arguments are limited to 4 KiB");
+static_assert(sizeof(TuneBatch) + sizeof(TuneShared) <= 3584, "kernel arguments are limited to 4 KiB");
 
-__global__ void k_set_tune(TuneState* dst, TuneBatch b, int count) {
-  const int i = threadIdx.x;
-  if (i < count) dst[i] = b.t[i];
+__global__ __launch_bounds__(256) void k_set_tune(TuneState* dst, TuneBatch b, TuneShared c, int count,
+                                                  int starts) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count * starts) return;
+  const TuneInit t = b.t[i / starts];
+  TuneState& d = dst[i];
+  for (int k = 0; k < 4; ++k) {
+    d.m[k] = d.v[k] = 0.0;
+    d.lr[k] = c.lr[k];
+    d.lo[k] = c.lo[k];
+    d.hi[k] = k == 1 ? t.hi_na : c.hi[k];
+  }
+  d.eta = t.eta;
+  d.nu_c = t.nu_c;
+  d.band_count = t.band_count;
+  d.loss = 0.0;
+  for (int k = 0; k < 6; ++k) d.grad[k] = 0.0;
+  for (int k = 0; k < 7; ++k) d.gab[k] = d.mab[k] = d.vab[k] = 0.0;
+  d.lr_ab = c.lr_ab;
+  d.bound_ab = c.bound_ab;
+  d.t = 0;
+  d.mask = c.mask;
+  d.pad[0] = d.pad[1] = 0;
 }
 
-hipError_t launch_set_tune(TuneState* dst, const TuneState* host, int n, hipStream_t s) {
-  for (int i0 = 0; i0 < n; i0 += 8) {
+hipError_t launch_set_tune(TuneState* dst, const TuneInit* host, const TuneShared& shared, int np,
+                           int starts, hipStream_t s) {
+  for (int i0 = 0; i0 < np; i0 += kTuneBatch) {
     TuneBatch b;
-    const int cnt = n - i0 < 8 ? n - i0 : 8;
+    const int cnt = np - i0 < kTuneBatch ? np - i0 : kTuneBatch;
     for (int j = 0; j < cnt; ++j) b.t[j] = host[i0 + j];
-    hipLaunchKernelGGL(k_set_tune, dim3(1), dim3(64), 0, s, dst + i0, b, cnt);
+    const long n = (long)cnt * starts;
+    hipLaunchKernelGGL(k_set_tune, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                       dst + (long)i0 * starts, b, shared, cnt, starts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
