@@ -621,7 +621,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ 
         float2 va[R0], vb[R0];
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
-          const int sl = row_slot(k + i * NB, PS);
+          const int sl = RowPassSlots<NS, R0, 1>::load(k, i);
           va[i] = buf[2 * r * LS + sl];
           vb[i] = buf[(2 * r + 1) * LS + sl];
           if constexpr (NP > 1) {
@@ -645,7 +645,8 @@ __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ 
     for (int b = 0; b < BPF; ++b) {
       if (cr[b] >= 0) {
 #pragma unroll
-        for (int i = 0; i < R0; ++i) buf[2 * cr[b] * LS + row_slot(ck[b] * R0 + i, PS)] = cv[b][i];
+        for (int i = 0; i < R0; ++i) 
+          buf[2 * cr[b] * LS + RowPassSlots<NS, R0, 1>::store(ck[b] * R0, i)] = cv[b][i];
       }
     }
     __syncthreads();
