@@ -606,20 +606,27 @@ VecLengths vec_lengths(const Shape& s, const LatSupport& sup) {
   return VecLengths{false, (int)s.Y, (int)s.X};
 }
 
+// Fields the workspace has room for (the model needs vec_fields of them).
+long vec_space_fields(const wo_optics* o) { return 6 + 3 * (o->vec_channels == 0 ? 1 : 5); }
+size_t vec_full_fields_bytes(const wo_optics* o, int32_t n, size_t vox) {
+  return align_up((size_t)n * vec_space_fields(o) * vox * sizeof(float2));
+}
+
 size_t vec_compact_elems(const wo_optics* o, int32_t n, const Shape& s, const LatSupport& sup, int LY) {
-  const long F = 6 + 3 * (o->vec_channels == 0 ? 1 : 5);
+  const long F = vec_space_fields(o);
   return (size_t)n * s.Z * LY * std::max(F * sup.xc, (long)s.C * s.P * sup.kt);
 }
 
 size_t vec_ws(const wo_optics* o, int32_t n, const Shape& s) {
-  const int F = 6 + 3 * (o->vec_channels == 0 ? 1 : 5);
   const LatSupport sup = lateral_support(o, n);
   const VecLengths L = vec_lengths(s, sup);
   const size_t vox = (size_t)s.Z * L.LY * L.LX;
-  const size_t full_fields = L.fused ? 0 : align_up((size_t)n * F * vox * sizeof(float2));
+  const size_t full_fields = L.fused ? 0 : vec_full_fields_bytes(o, n, vox);
+  // the responses as reals or, fused, as their kt complex columns (kt <= LX / 2 + 1)
+  const size_t resp = std::max(vox * sizeof(float), L.fused ? (size_t)s.Z * L.LY * sup.kt * sizeof(float2) : 0);
   return params_bytes(n) + align_up((size_t)n * sizeof(VecRec)) +
          align_up(vec_compact_elems(o, n, s, sup, L.LY) * sizeof(float2)) + full_fields +
-         align_up((size_t)n * s.C * s.P * vox * sizeof(float));
+         align_up((size_t)n * s.C * s.P * resp);
 }
 
 size_t tf_ws(const wo_optics* o, int32_t n, const Shape& s) {
@@ -1517,7 +1524,7 @@ int wo_lateral_support(const wo_optics* o, int32_t n, wo_support* out) {
 static int run_vector_tf(const wo_optics* o, int32_t n, const Shape& s, float2* tf, void* ws, hipStream_t hs,
                          bool band_out) {
   const int NS = o->vec_channels == 0 ? 1 : 5;
-  const int F = 6 + 3 * NS;
+  const int F = vec_fields(NS);
   const LatSupport sup = lateral_support(o, n);   // the detection pupils' columns: sup.xc, sup.kp
   const VecLengths L = vec_lengths(s, sup);
   std::vector<DevOptics> h(n);
@@ -1535,28 +1542,30 @@ static int run_vector_tf(const wo_optics* o, int32_t n, const Shape& s, float2* 
   float2* spec = (float2*)w;
   w += align_up(vec_compact_elems(o, n, s, sup, L.LY) * sizeof(float2));
   float2* fields = (float2*)w;
-  if (!L.fused) w += align_up((size_t)n * F * vox * sizeof(float2));
-  float* resp = (float*)w;
+  if (!L.fused) w += vec_full_fields_bytes(o, n, vox);
+  float* resp = (float*)w;   // the responses, or (fused) their half-spectrum columns
   WO_TRY(launch_set_params(dopt, h.data(), n, hs));
   WO_TRY(launch_set_vec(drec, vr.data(), n, hs));
   const Sampling sm = sampling_of(o);
   WO_TRY(launch_vec_spectra(dopt, drec, sm, n, NS, spec, sup.xc, sup.kp, L.LY, hs));
   WO_TRY(launch_cols(spec, L.LY, sup.xc, (long)F * s.Z, (long)F * s.Z, n, 1.f, hs, "k_cols_vec"));
+  // the bank vanishes outside the columns k < kt and the band rows: the X and
+  // Y transforms keep those, the Z pass writes the full bank with zeros
+  // elsewhere, or the band layout (band_out)
+  float2* cols = spec;   // the responses' columns k < kt
   if (L.fused) {
-    WO_TRY(launch_vec_rows_resp(drec, spec, resp, L.LX, sup.xc, sup.kp, s.Z * (long)L.LY, NS, n, hs));
+    cols = (float2*)resp;
+    WO_TRY(launch_vec_rows(drec, spec, cols, L.LX, sup.xc, sup.kp, sup.kt, s.Z * (long)L.LY, NS, s.P, n, hs));
   } else {
     WO_TRY(launch_rows_c2c(spec, fields, L.LX, sup.xc, sup.kp, (long)n * F * s.Z * L.LY, 1.f, hs));
-    WO_TRY(launch_vec_products(drec, fields, resp, vox, F, n, hs));
+    WO_TRY(launch_vec_products(drec, fields, resp, vox, NS, n, hs));
+    const long rows = (long)s.C * s.P * s.Z * L.LY;
+    const RowGroups g{rows, rows, rows, n};
+    WO_TRY(launch_rows_r2c(resp, spec, L.LX, g, hs, sup.kt, sup.kt, "k_rows_r2c_tf"));
   }
-  // the bank vanishes outside the columns k < kt and the band rows: the X and
-  // Y transforms keep those (in the spectra's buffer), the Z pass writes the
-  // full bank with zeros elsewhere, or the band layout (band_out)
-  const long rows = (long)s.C * s.P * s.Z * L.LY;
-  const RowGroups g{rows, rows, rows, n};
-  WO_TRY(launch_rows_r2c(resp, spec, L.LX, g, hs, sup.kt, sup.kt, "k_rows_r2c_tf"));
   const long planes = (long)s.C * s.P * s.Z;
-  WO_TRY(launch_cols(spec, L.LY, sup.kt, planes, planes, n, -1.f, hs, "k_cols_y_tf", 1, sup.ky));
-  WO_TRY(launch_cols_expand(spec, tf, (int)s.Z, L.LY, (int)s.Y, (int)s.Xh, sup.kt, sup.ky,
+  WO_TRY(launch_cols(cols, L.LY, sup.kt, planes, planes, n, -1.f, hs, "k_cols_y_tf", 1, sup.ky));
+  WO_TRY(launch_cols_expand(cols, tf, (int)s.Z, L.LY, (int)s.Y, (int)s.Xh, sup.kt, sup.ky,
                             (long)n * s.C * s.P, -1.f, hs, band_out));
   return WO_OK;
 }

@@ -276,11 +276,13 @@ struct VecRec {
   int C, P, NS;
 };
 hipError_t launch_set_vec(VecRec* dst, const VecRec* host, int n, hipStream_t s);
+// Fields of the vector model with NS illumination states (1 or 5).
+int vec_fields(int NS);
 // Field spectra fields [patch][f][z][y][c] on the XC kept columns c (column kx
 // = field_column(c, KP, X, XC)) and LY rows (row i the grid's frequency (i or
-// i - LY) / (ny dy)): f < 6 the detected scattered field of a unit
-// dipole, u_i'n (f = 3 i' + n), then for each illumination state s the direct
-// arm S P E conj(e_k) (f = 6 + 3 s + k), each times the propagator of plane z.
+// i - LY) / (ny dy)): f < 5 the detected scattered fields U_a, then the three
+// w_k of a single state or the five W_a of several, each times the propagator
+// of plane z.
 hipError_t launch_vec_spectra(const DevOptics* opt, const VecRec* rec, const Sampling& sm, int npatch, int NS,
                               float2* fields, int XC, int KP, int LY, hipStream_t s);
 // Unnormalised complex FFT along X (sign -1 forward, +1 inverse) of nrows rows:
@@ -289,14 +291,14 @@ hipError_t launch_rows_c2c(const float2* src, float2* dst, int X, int XC, int KP
                            hipStream_t s);
 // The real channel responses out [patch][C][P][vox] = 2 Re R_cp from the
 // transformed fields [patch][F][vox].
-hipError_t launch_vec_products(const VecRec* rec, const float2* fields, float* out, long vox, int F, int npatch,
+hipError_t launch_vec_products(const VecRec* rec, const float2* fields, float* out, long vox, int NS, int npatch,
                                hipStream_t s);
-// Whether the row length has the fused X pass + responses kernel (compiled lengths).
+// Whether the row length has the fused X pass (compiled lengths).
 bool vec_rows_fused(int X);
-// The same responses straight from the Y-transformed spectra [patch][F][zy][XC]
-// (zy = Z * Y rows of the kept columns): X inverse transforms and products
-// fused per row and channel.
-hipError_t launch_vec_rows_resp(const VecRec* rec, const float2* spec, float* out, int X, int XC, int KP, long zy,
-                                int NS, int npatch, hipStream_t s);
+// The responses' X transforms straight from the Y-transformed spectra
+// [patch][F][zy][XC] (zy = Z * Y rows of the kept columns): out [patch][C][P][zy][KT]
+// the half-spectrum columns k < KT of every response (P <= 8).
+hipError_t launch_vec_rows(const VecRec* rec, const float2* spec, float2* out, int X, int XC, int KP, int KT,
+                           long zy, int NS, int P, int npatch, hipStream_t s);
 
 }  // namespace wo

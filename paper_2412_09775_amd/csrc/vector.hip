@@ -8,19 +8,24 @@
 // source point q is e = Q J, the detection tensor is P E Q^T, and its
 // columns are transverse to the wave, so P E Q^T (I - k^ k^T) g = P E g Q^T.
 // The direct light reaches the detector as P E J, so v_ik = J_i w_k with
-// w_k = IFFT2[S P E conj(e_k) prop]: six u fields and three w fields per
-// illumination state.  A channel c (state s, analyser M_c) then responds to
+// w_k = IFFT2[S P E conj(e_k) prop].  Q is real with five distinct entries q_a
+// (Q_xy = Q_yx), so every field is one of, or a constant mix of, ten transforms:
+//   U_a = IFFT2[i P E g q_a prop]     (u_i'n = U_a(n, i')),
+//   W_a = IFFT2[S P E q_a prop]       (w_k = conj(J_x) W_a(k, 0) + conj(J_y) W_a(k, 1)),
+// whatever the number of illumination states (a single state takes its three
+// w_k instead of the five W_a).  A channel c (state s, analyser M_c) then responds to
 // property p (tensor T_p) with
 //   R_cp = 1 / (Y X I_bg) sum_n,k beta_n T_p^{nk} conj(w_k),
 //   beta_n = sum_i' alpha_c,i' u_i'n,  alpha_c = J_s^H M_c,
 // and H_cp = FFT3(2 Re R_cp).  The spectra vanish outside the detection
 // pupil's columns: they are written on those columns only and inverse-
-// transformed along Y there (column passes).  With a compiled row length the
-// X transform and the products are fused per row (k_vec_rows_all or
-// k_vec_rows_resp) on the support's shortened transforms; otherwise a complex
-// row pass writes the fields on the grid and k_vec_products multiplies them
-// per voxel.  The real responses are transformed forward by the row and
-// column passes of the linear model, on the bank's support.
+// transformed along Y there (column passes).  With a compiled row length one kernel per row
+// (k_vec_rows) inverse-transforms the fields along X, forms every channel's real
+// responses and transforms those forward, on the support's shortened lengths;
+// otherwise a complex row pass writes the fields on the grid, k_vec_products
+// multiplies them per voxel, and the row pass of the linear model transforms
+// the responses.  The column passes of the linear model do the rest, on the
+// bank's support.
 #include <algorithm>
 
 #include "internal.hpp"
@@ -49,29 +54,55 @@ hipError_t launch_set_vec(VecRec* dst, const VecRec* host, int n, hipStream_t s)
   return hipSuccess;
 }
 
-// One thread per lateral frequency (ky, kx) of one patch: the pupil values
-// and the map Q in FP64, then every plane's propagator phase.  Q is written
-// without angles: with w = 1 / (k_m (k_m + kz)),
+// Entry a of the map Q read as Q_n,i' (n = x, y, z; i' = x, y).
+constexpr int kQ[3][2] = {{0, 1}, {1, 2}, {3, 4}};
+// Fields of a model with NS illumination states: five U, then the three w of a
+// single state or the five W that every state mixes.
+template <int NS>
+struct VecFields {
+  static constexpr int kW = NS == 1 ? 3 : 5;
+  static constexpr int kF = 5 + kW;
+};
+int vec_fields(int NS) { return NS == 1 ? VecFields<1>::kF : VecFields<5>::kF; }
+
+// w_k of channel state s at one point from the model's W fields there (W(a)).
+template <int NS, typename WF>
+__device__ __forceinline__ void vec_w(const VecRec& r, int s, WF W, float2 (&w)[3]) {
+  if constexpr (NS == 1) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = W(k);
+  } else {
+    const float2 jx = make_float2(r.J[s][0][0], -r.J[s][0][1]), jy = make_float2(r.J[s][1][0], -r.J[s][1][1]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = cadd(cmul(jx, W(kQ[k][0])), cmul(jy, W(kQ[k][1])));
+  }
+}
+
+// One thread per lateral frequency (ky, kx) of one patch and chunk of planes:
+// the pupil values and the map Q in FP64, then each plane's propagator phase.
+// Q is written without angles: with w = 1 / (k_m (k_m + kz)),
 //   Q = [[1 - px^2 w, -px py w], [-px py w, 1 - py^2 w], [-px / k_m, -py / k_m]].
-// NS (1 or 5 illumination states) is a template parameter so that the
-// per-state arrays stay in registers (a runtime bound indexed them from
-// scratch memory).
 // LY rows: row i of the LY-point transform stands for the grid's frequency
 // (i or i - LY) / (ny dy); LY = ny is the grid's own transform, a shorter one
 // (longer than twice the band) samples the same band-limited fields more
-// coarsely along y.
+// coarsely along y.  Bound by its writes; one wave per 64 columns and 16 planes
+// keeps the chip busy where a row's columns fill half of a 256-thread
+// workgroup (5 states, 64 x 512 x 512: 21 fields in 65 us, 10 in 37).
+constexpr int kVecPlanes = 16;
 template <int NS>
-__global__ __launch_bounds__(256) void k_vec_spectra(const DevOptics* __restrict__ opt,
+__global__ __launch_bounds__(64) void k_vec_spectra(const DevOptics* __restrict__ opt,
                                                      const VecRec* __restrict__ rec, Sampling sm,
                                                      float2* __restrict__ fields, int XC, int KP, int LY) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int F = VecFields<NS>::kF;
+  const int X = sm.nx, Z = sm.nz;
+  const int nzc = (Z + kVecPlanes - 1) / kVecPlanes;
+  const int zc = blockIdx.x % nzc;
+  const int c = (blockIdx.x / nzc) * 64 + threadIdx.x;
   const int ky = blockIdx.y;
   const long patch = blockIdx.z;
-  const int X = sm.nx, Z = sm.nz;
   if (c >= XC) return;
   const int kx = field_column(c, KP, X, XC);
   const DevOptics o = opt[patch];
-  const int F = 6 + 3 * NS;
   const long plane = (long)LY * XC;
   float2* base = fields + patch * (long)F * Z * plane + (long)ky * XC + c;
   const double fy = (double)(ky < (LY + 1) / 2 ? ky : ky - LY) / sm.Ly;
@@ -84,31 +115,23 @@ __global__ __launch_bounds__(256) void k_vec_spectra(const DevOptics* __restrict
   source_centre(o, &cy, &cx);
   const double S = disc(fy - cy, fx - cx, o.na_ill / o.wavelength, hw);
   const double kz = sqrt(fmax(km * km - (fy * fy + fx * fx), 0.0));
-  // u_i'n spectrum: i (P k_m / kz) Q_n,i' e^{i phi}; w_k: S P conj(e_k) e^{i phi}
-  float q[3][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+  float q[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
   float gp = 0.f, sp = 0.f;
-  float2 ce[NS][3];
   if (P != 0.0 && kz > 0.0) {
     const double w = 1.0 / (km * (km + kz));
-    q[0][0] = (float)(1.0 - fx * fx * w);
-    q[0][1] = (float)(-fx * fy * w);
-    q[1][0] = q[0][1];
-    q[1][1] = (float)(1.0 - fy * fy * w);
-    q[2][0] = (float)(-fx / km);
-    q[2][1] = (float)(-fy / km);
+    q[0] = (float)(1.0 - fx * fx * w);
+    q[1] = (float)(-fx * fy * w);
+    q[2] = (float)(1.0 - fy * fy * w);
+    q[3] = (float)(-fx / km);
+    q[4] = (float)(-fy / km);
     gp = (float)(P * km / kz);
     sp = (float)(S * P);
   }
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const float2 jx = make_float2(rec[patch].J[s][0][0], rec[patch].J[s][0][1]);
-    const float2 jy = make_float2(rec[patch].J[s][1][0], rec[patch].J[s][1][1]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k)   // conj(e_k) = conj(Q_k0 Jx + Q_k1 Jy)
-      ce[s][k] = make_float2(q[k][0] * jx.x + q[k][1] * jy.x, -(q[k][0] * jx.y + q[k][1] * jy.y));
-  }
+  float2 ce[3];   // a single state: conj(e_k) = conj(Q_k0 Jx + Q_k1 Jy)
+  if constexpr (NS == 1) vec_w<5>(rec[patch], 0, [&](int a) { return make_float2(q[a], 0.f); }, ce);   // J mixes the q_a
   const double ab2 = (gp != 0.f) ? 2.0 * aberration_waves(o, fy, fx) : 0.0;
-  for (int z = 0; z < Z; ++z) {
+  const int z1 = min(Z, (zc + 1) * kVecPlanes);
+  for (int z = zc * kVecPlanes; z < z1; ++z) {
     float sn = 0.f, cs = 0.f;
     if (gp != 0.f) {
       const double arg = 2.0 * kz * (plane_z(z, sm) - o.defocus) + ab2;   // phase / pi
@@ -116,35 +139,32 @@ __global__ __launch_bounds__(256) void k_vec_spectra(const DevOptics* __restrict
     }
     float2* pz = base + (long)z * plane;
 #pragma unroll
-    for (int ip = 0; ip < 2; ++ip)
+    for (int a = 0; a < 5; ++a) {
+      const float g = gp * q[a];
+      pz[(long)a * Z * plane] = make_float2(-g * sn, g * cs);   // i g e^{i phi}
+    }
+    const float2 e = make_float2(sp * cs, sp * sn);
 #pragma unroll
-      for (int n = 0; n < 3; ++n) {
-        const float a = gp * q[n][ip];
-        pz[(long)(3 * ip + n) * Z * plane] = make_float2(-a * sn, a * cs);   // i a e^{i phi}
-      }
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const float2 c = ce[s][k];
-        const float2 e = make_float2(sp * cs, sp * sn);
-        pz[(long)(6 + 3 * s + k) * Z * plane] = make_float2(e.x * c.x - e.y * c.y, e.x * c.y + e.y * c.x);
-      }
+    for (int a = 0; a < VecFields<NS>::kW; ++a) {
+      float2 v;
+      if constexpr (NS == 1) v = cmul(e, ce[a]);
+      else v = cscale(e, q[a]);
+      pz[(long)(5 + a) * Z * plane] = v;
+    }
   }
 }
 
 hipError_t launch_vec_spectra(const DevOptics* opt, const VecRec* rec, const Sampling& sm, int npatch, int NS,
                               float2* fields, int XC, int KP, int LY, hipStream_t s) {
-  if (NS < 1 || NS > 5 || npatch < 1 || npatch > 65535 || LY < 2 || LY > sm.ny) return hipErrorInvalidValue;
+  if ((NS != 1 && NS != 5) || npatch < 1 || npatch > 65535 || LY < 2 || LY > sm.ny) return hipErrorInvalidValue;
   if (XC < 1 || XC > sm.nx || KP < 0 || KP >= XC) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((XC + 255) / 256), (unsigned)LY, (unsigned)npatch);
+  const int nzc = (sm.nz + kVecPlanes - 1) / kVecPlanes;
+  const dim3 grid((unsigned)(((XC + 63) / 64) * nzc), (unsigned)LY, (unsigned)npatch);
   ScopedTiming _t("k_vec_spectra", s);
   if (NS == 1)
-    hipLaunchKernelGGL(k_vec_spectra<1>, grid, dim3(256), 0, s, opt, rec, sm, fields, XC, KP, LY);
-  else if (NS == 5)
-    hipLaunchKernelGGL(k_vec_spectra<5>, grid, dim3(256), 0, s, opt, rec, sm, fields, XC, KP, LY);
+    hipLaunchKernelGGL(k_vec_spectra<1>, grid, dim3(64), 0, s, opt, rec, sm, fields, XC, KP, LY);
   else
-    return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_vec_spectra<5>, grid, dim3(64), 0, s, opt, rec, sm, fields, XC, KP, LY);
   return hipGetLastError();
 }
 
@@ -229,225 +249,149 @@ hipError_t launch_rows_c2c(const float2* src, float2* dst, int X, int XC, int KP
   return hipGetLastError();
 }
 
-// One thread per voxel of one patch: beta_n = sum_i' alpha_c,i' u_i'n for
-// every channel, then 2 Re(sum_n,k T_p^{nk} beta_n conj(w_k)) / (Y X I_bg)
-// for every property.  NS illumination states: one (the four Stokes channels
-// share it) or five (channel c uses state c); compile-time, so that every
-// array index is static and the fields stay in registers.
+// The P responses of channel c (state s of w) at one point from the fields
+// there: beta_n = sum_i' alpha_c,i' u_i'n, then sc Re(sum_n,k T_p^{nk} beta_n
+// conj(w_k)) for every property p: put(p, value), p < P <= kVecProps.
+constexpr int kVecProps = 8;
+template <int NS, typename UF, typename WF, typename PUT>
+__device__ __forceinline__ void vec_channel(const VecRec& r, int c, int P, float sc, UF U, WF W, PUT put) {
+  const float2 a0 = make_float2(r.alpha[c][0][0], r.alpha[c][0][1]);
+  const float2 a1 = make_float2(r.alpha[c][1][0], r.alpha[c][1][1]);
+  float2 w[3], qm[3][3];
+  vec_w<NS>(r, NS == 1 ? 0 : c, W, w);
+#pragma unroll
+  for (int n = 0; n < 3; ++n) {
+    const float2 b = cadd(cmul(a0, U(kQ[n][0])), cmul(a1, U(kQ[n][1])));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) qm[n][k] = cmulconj(b, w[k]);
+  }
+#pragma unroll
+  for (int p = 0; p < kVecProps; ++p) {
+    if (p >= P) break;
+    float acc = 0.f;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) acc += r.T[p][e][0] * qm[e / 3][e % 3].x - r.T[p][e][1] * qm[e / 3][e % 3].y;
+    put(p, sc * acc);
+  }
+}
+
+// Row lengths without compiled stages: one thread per voxel of one patch, from
+// the fields on the grid.  NS is a template parameter so that the per-field
+// arrays stay in registers.
 template <int NS>
 __global__ __launch_bounds__(256) void k_vec_products(const VecRec* __restrict__ rec,
                                                       const float2* __restrict__ fields,
                                                       float* __restrict__ out, long vox) {
-  constexpr int C = NS == 1 ? 4 : 5, F = 6 + 3 * NS;
+  constexpr int C = NS == 1 ? 4 : 5, F = VecFields<NS>::kF;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const long patch = blockIdx.y;
   if (i >= vox) return;
   const VecRec& r = rec[patch];
   const int P = r.P;
   const float2* fp = fields + patch * (long)F * vox + i;
-  float2 u[6], w[NS][3];
+  float2 f[F];
 #pragma unroll
-  for (int f = 0; f < 6; ++f) u[f] = fp[(long)f * vox];
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) w[s][k] = fp[(long)(6 + 3 * s + k) * vox];
+  for (int a = 0; a < F; ++a) f[a] = fp[(long)a * vox];
   const float sc = 2.f * r.scale;
   float* op = out + patch * (long)C * P * vox + i;
 #pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const int s = NS == 1 ? 0 : c;
-    const float2 a0 = make_float2(r.alpha[c][0][0], r.alpha[c][0][1]);
-    const float2 a1 = make_float2(r.alpha[c][1][0], r.alpha[c][1][1]);
-    float2 qm[3][3];
-#pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      const float2 b = cadd(cmul(a0, u[n]), cmul(a1, u[3 + n]));
-#pragma unroll
-      for (int k = 0; k < 3; ++k) qm[n][k] = cmul(b, make_float2(w[s][k].x, -w[s][k].y));
-    }
-    for (int p = 0; p < P; ++p) {
-      float acc = 0.f;
-#pragma unroll
-      for (int e = 0; e < 9; ++e) {
-        const float2 t = make_float2(r.T[p][e][0], r.T[p][e][1]);
-        acc += t.x * qm[e / 3][e % 3].x - t.y * qm[e / 3][e % 3].y;
-      }
-      op[(long)(c * P + p) * vox] = sc * acc;
-    }
-  }
+  for (int c = 0; c < C; ++c)
+    vec_channel<NS>(r, c, P, sc, [&](int a) { return f[a]; }, [&](int a) { return f[5 + a]; },
+                    [&](int p, float v) { op[(long)(c * P + p) * vox] = v; });
 }
 
-hipError_t launch_vec_products(const VecRec* rec, const float2* fields, float* out, long vox, int F, int npatch,
+hipError_t launch_vec_products(const VecRec* rec, const float2* fields, float* out, long vox, int NS, int npatch,
                                hipStream_t s) {
   if (vox < 1 || npatch < 1 || npatch > 65535) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((vox + 255) / 256), (unsigned)npatch);
   ScopedTiming _t("k_vec_products", s);
-  if (F == 9)
+  if (NS == 1)
     hipLaunchKernelGGL(k_vec_products<1>, grid, dim3(256), 0, s, rec, fields, out, vox);
-  else if (F == 21)
+  else if (NS == 5)
     hipLaunchKernelGGL(k_vec_products<5>, grid, dim3(256), 0, s, rec, fields, out, vox);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-// Channel responses straight from the Y-transformed spectra (compiled row
-// lengths N, the grid's X or a shorter length holding the responses'
-// band without wrap-around): one workgroup per row (patch, z, y) and channel c.  beta_n =
-// sum_i' alpha_c,i' u_i'n is linear in the fields, so its three lines are
-// formed from the u spectra as they are loaded; with the three w lines of
-// the channel's state they are inverse-transformed along X in LDS (six
-// lines), and each x then gets the channel's P responses.  This replaces the
-// full-grid fields' round trip through HBM (the X pass writing them, the
-// products reading them) by a re-read of the compact spectra per channel.
+// Compiled row lengths N (the grid's X or a shorter length that holds the
+// responses' band without wrap-around): one workgroup per row (patch, z, y).
+// The row's F fields are inverse-transformed along X from their XC kept columns
+// in LDS, each x gets its C P responses, these
+// replace the fields in LDS as real rows, two per complex line, and are
+// transformed forward; the columns k < KT of each leave for the Y pass.  So
+// neither the fields on the grid nor the responses visit HBM.  Bound by VALU
+// issue (about 20 transforms and C N contractions of 160 instructions a row).
+// 5 states x 4 properties, 64 x 512 x 512 (rows of 256): 21 fields, responses
+// through HBM and a row pass 328 + 111 us, 308 us so.
+// More lines than a workgroup owns at once go in batches.
 template <int NS, int N>
-__global__ __launch_bounds__(1024) void k_vec_rows_resp(const VecRec* __restrict__ rec,
-                                                        const float2* __restrict__ spec,
-                                                        float* __restrict__ out, int XC, int KP, long zy) {
-  constexpr int C = NS == 1 ? 4 : 5, F = 6 + 3 * NS, NL = 6;
+__global__ __launch_bounds__(1024) void k_vec_rows(const VecRec* __restrict__ rec,
+                                                   const float2* __restrict__ spec,
+                                                   float2* __restrict__ out, int XC, int KP, int KT, long zy) {
+  constexpr int C = NS == 1 ? 4 : 5, F = VecFields<NS>::kF;
+  constexpr bool SPLIT = F * N > kMaxElems;             // the fields in two batches
+  constexpr int NB = SPLIT ? 5 : F;                      // lines of the first batch
   extern __shared__ float2 smem[];
   float2* tw = smem;
   float2* buf = smem + N;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const long rowid = blockIdx.x / C;
-  const int c = (int)(blockIdx.x - rowid * C);
-  const long patch = rowid / zy, r = rowid - patch * zy;
-  const VecRec& rv = rec[patch];
-  const int s = NS == 1 ? 0 : c;
-  const float2 a0 = make_float2(rv.alpha[c][0][0], rv.alpha[c][0][1]);
-  const float2 a1 = make_float2(rv.alpha[c][1][0], rv.alpha[c][1][1]);
-  const float2* sp = spec + patch * (long)F * zy * XC + r * XC;
-  const int PS = pad_shift(N), LS = row_stride(N);
-  fill_twiddles(tw, N, tid, nthr);
-  // line l < 3: beta_l = alpha_0 u_0l + alpha_1 u_1l; l >= 3: w_{l-3} of state s
-  auto load = [&](int l, int k) {
-    const int cc = compact_column(k, KP, N, XC);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (cc >= 0) {
-      if (l < 3) {
-        const float2 u0 = sp[(long)l * zy * XC + cc], u1 = sp[(long)(3 + l) * zy * XC + cc];
-        v = make_float4(u0.x, u0.y, u1.x, u1.y);
-      } else {
-        const float2 w = sp[(long)(6 + 3 * s + l - 3) * zy * XC + cc];
-        v = make_float4(w.x, w.y, 0.f, 0.f);
-      }
-    }
-    return v;
-  };
-  auto finish = [&](int l, int, float4 v) {
-    if (l >= 3) return make_float2(v.x, v.y);
-    return cadd(cmul(a0, make_float2(v.x, v.y)), cmul(a1, make_float2(v.z, v.w)));
-  };
-  constexpr int NP = StaticPlan<N>::passes();
-  first_pass_in2<N, 0, false, kEmax, true, false>(buf, NL, 1, LS, -1, 1.f, tid, nthr, load, finish, [] {});
-  static_passes<N, 0, false, kEmax, true, false, 1, NP>(buf, NL, 1, LS, -1, tw, 1.f, tid, nthr);
-  __syncthreads();
-  const int P = rv.P;
-  const float sc = 2.f * rv.scale_short;
-  const long vox = zy * N;
-  float* op = out + (patch * (long)C + c) * P * vox + r * N;
-  for (int x = tid; x < N; x += nthr) {
-    const int sl = row_slot(x, PS);
-    float2 qm[3][3];
-#pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      const float2 b = buf[n * LS + sl];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const float2 w = buf[(3 + k) * LS + sl];
-        qm[n][k] = cmul(b, make_float2(w.x, -w.y));
-      }
-    }
-    for (int p = 0; p < P; ++p) {
-      float acc = 0.f;
-#pragma unroll
-      for (int e = 0; e < 9; ++e) {
-        const float2 t = make_float2(rv.T[p][e][0], rv.T[p][e][1]);
-        acc += t.x * qm[e / 3][e % 3].x - t.y * qm[e / 3][e % 3].y;
-      }
-      op[(long)p * vox + x] = sc * acc;
-    }
-  }
-}
-
-// The same for every channel of a row in one workgroup, where the row's six u
-// lines and 3 NS w lines fit LDS (each set transformed in one batch): the
-// spectra are read once per row instead of once per channel, and beta is
-// formed per x from the transformed u lines.
-template <int NS, int N>
-__global__ __launch_bounds__(1024) void k_vec_rows_all(const VecRec* __restrict__ rec,
-                                                       const float2* __restrict__ spec,
-                                                       float* __restrict__ out, int XC, int KP, long zy) {
-  constexpr int C = NS == 1 ? 4 : 5, F = 6 + 3 * NS, NW = 3 * NS;
-  extern __shared__ float2 smem[];
-  float2* tw = smem;
   const int LS = row_stride(N), PS = pad_shift(N);
-  float2* bu = smem + N;            // 6 u lines
-  float2* bw = bu + 6 * LS;         // 3 NS w lines
   const int tid = threadIdx.x, nthr = blockDim.x;
   const long rowid = blockIdx.x;
   const long patch = rowid / zy, r = rowid - patch * zy;
   const VecRec& rv = rec[patch];
   const float2* sp = spec + patch * (long)F * zy * XC + r * XC;
-  fill_twiddles(tw, N, tid, nthr);
-  auto finish = [](int, int, float2 v) { return v; };
+  TwFetch twf;   // as in the row passes of the linear model
+  tw_begin(twf, tw, N, tid, nthr);
   constexpr int NP = StaticPlan<N>::passes();
-  auto load_u = [&](int l, int k) {
-    const int cc = compact_column(k, KP, N, XC);
-    return cc >= 0 ? sp[(long)l * zy * XC + cc] : make_float2(0.f, 0.f);
-  };
-  auto load_w = [&](int l, int k) {
-    const int cc = compact_column(k, KP, N, XC);
-    return cc >= 0 ? sp[(long)(6 + l) * zy * XC + cc] : make_float2(0.f, 0.f);
-  };
-  first_pass_in2<N, 0, false, kEmax, true, false>(bu, 6, 1, LS, -1, 1.f, tid, nthr, load_u, finish, [] {});
-  static_passes<N, 0, false, kEmax, true, false, 1, NP>(bu, 6, 1, LS, -1, tw, 1.f, tid, nthr);
-  first_pass_in2<N, 0, false, kEmax, true, false>(bw, NW, 1, LS, -1, 1.f, tid, nthr, load_w, finish, [] {});
-  static_passes<N, 0, false, kEmax, true, false, 1, NP>(bw, NW, 1, LS, -1, tw, 1.f, tid, nthr);
-  __syncthreads();
+#pragma unroll
+  for (int l0 = 0; l0 < F; l0 += NB) {
+    const int nl = F - l0 < NB ? F - l0 : NB;
+    first_pass_in<N, 0, false, kEmax, true, false>(
+        buf + l0 * LS, nl, 1, LS, -1, 1.f, tid, nthr,
+        [&](int l, int k) {
+          const int cc = compact_column(k, KP, N, XC);
+          return cc >= 0 ? sp[(long)(l0 + l) * zy * XC + cc] : make_float2(0.f, 0.f);
+        },
+        [&] { if (l0 == 0) tw_end(twf, tw, N, tid, nthr); });
+    static_passes<N, 0, false, kEmax, true, false, 1, NP>(buf + l0 * LS, nl, 1, LS, -1, tw, 1.f, tid, nthr);
+  }
+  // Response q = c P + p is the real (q even) or imaginary part of line q / 2.
+  // One thread owns point x of every line, so it may replace the fields there as
+  // soon as it has read them; the channel index is uniform, so the constants of
+  // a channel stay in scalar registers.
   const int P = rv.P;
   const float sc = 2.f * rv.scale_short;
-  const long vox = zy * N;
-  float* op = out + patch * (long)C * P * vox + r * N;
-  // one (channel, x) pair per thread and step: every thread busy, x contiguous
-  // across a wave for the stores
-  for (int e = tid; e < C * N; e += nthr) {
-    const int c = e / N, x = e - c * N;
+  const int nq = C * P, nlo = (nq + 1) / 2;
+  for (int x = tid; x < N; x += nthr) {
     const int sl = row_slot(x, PS);
-    const int s = NS == 1 ? 0 : c;
-    const float2 a0 = make_float2(rv.alpha[c][0][0], rv.alpha[c][0][1]);
-    const float2 a1 = make_float2(rv.alpha[c][1][0], rv.alpha[c][1][1]);
-    float2 cw[3];
+    float2 f[F];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float2 w = bw[(3 * s + k) * LS + sl];
-      cw[k] = make_float2(w.x, -w.y);
-    }
-    float2 qm[3][3];
+    for (int a = 0; a < F; ++a) f[a] = buf[a * LS + sl];
 #pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      const float2 b = cadd(cmul(a0, bu[n * LS + sl]), cmul(a1, bu[(3 + n) * LS + sl]));
-#pragma unroll
-      for (int k = 0; k < 3; ++k) qm[n][k] = cmul(b, cw[k]);
-    }
-    for (int p = 0; p < P; ++p) {
-      float acc = 0.f;
-#pragma unroll
-      for (int q = 0; q < 9; ++q) {
-        const float2 t = make_float2(rv.T[p][q][0], rv.T[p][q][1]);
-        acc += t.x * qm[q / 3][q % 3].x - t.y * qm[q / 3][q % 3].y;
-      }
-      op[(long)(c * P + p) * vox + x] = sc * acc;
-    }
+    for (int c = 0; c < C; ++c)
+      vec_channel<NS>(rv, c, P, sc, [&](int a) { return f[a]; }, [&](int a) { return f[5 + a]; },
+                      [&](int p, float v) {
+                        const int q = c * P + p;
+                        ((float*)(buf + (q >> 1) * LS + sl))[q & 1] = v;
+                      });
+    if (nq & 1) ((float*)(buf + (nlo - 1) * LS + sl))[1] = 0.f;
   }
-}
-
-// Whether every channel of a row fits one workgroup of k_vec_rows_all.
-static bool vec_rows_all_fits(int X, int NS) {
-  const long nw = 3L * NS * X;
-  return 6L * X <= kMaxElems && nw <= kMaxElems &&
-         (long)(X + (6L + 3L * NS) * row_stride(X)) * (long)sizeof(float2) <= lds_limit_bytes();
+  __syncthreads();
+  const int LB = nthr * kEmax / N;   // lines a workgroup owns at once
+  for (int l0 = 0; l0 < nlo; l0 += LB)
+    static_passes<N, 0, false, kEmax, true, false, 0, NP>(buf + l0 * LS, min(LB, nlo - l0), 1, LS, -1, tw, -1.f,
+                                                          tid, nthr);
+  float2* op = out + (patch * (long)nq * zy + r) * KT;
+  const float inv_kt = 1.0f / (float)KT;
+  for (int e = tid; e < nlo * KT; e += nthr) {
+    const int l = div_small(e, inv_kt), k = e - l * KT;
+    const float2 zk = buf[l * LS + row_slot(k, PS)];
+    const float2 zm = buf[l * LS + row_slot(k == 0 ? 0 : N - k, PS)];
+    op[(long)(2 * l) * zy * KT + k] = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
+    if (2 * l + 1 < nq)
+      op[(long)(2 * l + 1) * zy * KT + k] = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
+  }
 }
 
 bool vec_rows_fused(int X) {
@@ -461,49 +405,27 @@ bool vec_rows_fused(int X) {
   }
 }
 
-hipError_t launch_vec_rows_resp(const VecRec* rec, const float2* spec, float* out, int X, int XC, int KP, long zy,
-                                int NS, int npatch, hipStream_t s) {
+hipError_t launch_vec_rows(const VecRec* rec, const float2* spec, float2* out, int X, int XC, int KP, int KT,
+                           long zy, int NS, int P, int npatch, hipStream_t s) {
   if (!vec_rows_fused(X) || (NS != 1 && NS != 5) || zy < 1 || npatch < 1 || XC < 1 || XC > X || KP < 0 ||
-      KP >= XC)
+      KP >= XC || KT < 1 || KT > X / 2 + 1 || P < 1 || P > kVecProps)
     return hipErrorInvalidValue;
-  const int C = NS == 1 ? 4 : 5;
-  if (vec_rows_all_fits(X, NS)) {
-    const long nwg = (long)npatch * zy;
-    if (nwg > 0x7fffffffL) return hipErrorInvalidValue;
-    const int thr = threads_for(std::max(6L, 3L * NS) * X);
-    const size_t lds = (size_t)(X + (6L + 3L * NS) * row_stride(X)) * sizeof(float2);
-    ScopedTiming _t("k_vec_rows_resp", s);
-#define X_(NN)                                                                                       \
-  case NN:                                                                                           \
-    if (NS == 1)                                                                                     \
-      hipLaunchKernelGGL((k_vec_rows_all<1, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, \
-                         KP, zy);                                                                    \
-    else                                                                                             \
-      hipLaunchKernelGGL((k_vec_rows_all<5, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, \
-                         KP, zy);                                                                    \
-    return hipGetLastError();
-    switch (X) {
-      WO_LATERAL_SIZES(X_)
-      default:
-        break;
-    }
-#undef X_
-    return hipErrorInvalidValue;
-  }
-  const long nwg = (long)npatch * zy * C;
+  const int F = vec_fields(NS), C = NS == 1 ? 4 : 5;
+  const long nwg = (long)npatch * zy;
   if (nwg > 0x7fffffffL) return hipErrorInvalidValue;
-  const int thr = threads_for(6L * X);
-  const size_t lds = (size_t)(X + 6L * row_stride(X)) * sizeof(float2);
+  const int thr = threads_for((long)((long)F * X > kMaxElems ? 5 : F) * X);
+  const long lines = std::max(F, (C * P + 1) / 2);
+  const size_t lds = (size_t)(X + lines * row_stride(X)) * sizeof(float2);
   if ((long)lds > lds_limit_bytes()) return hipErrorInvalidValue;
-  ScopedTiming _t("k_vec_rows_resp", s);
+  ScopedTiming _t("k_vec_rows", s);
 #define X_(NN)                                                                                       \
   case NN:                                                                                           \
     if (NS == 1)                                                                                     \
-      hipLaunchKernelGGL((k_vec_rows_resp<1, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, \
-                         KP, zy);                                                                    \
+      hipLaunchKernelGGL((k_vec_rows<1, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, KP, \
+                         KT, zy);                                                                    \
     else                                                                                             \
-      hipLaunchKernelGGL((k_vec_rows_resp<5, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, \
-                         KP, zy);                                                                    \
+      hipLaunchKernelGGL((k_vec_rows<5, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, KP, \
+                         KT, zy);                                                                    \
     return hipGetLastError();
   switch (X) {
     WO_LATERAL_SIZES(X_)

@@ -102,3 +102,29 @@ def test_tuned_schedules_keep_the_vector_bank_and_reconstruction(gpu_lib):
     e_rec = np.linalg.norm(rec - ref) / np.linalg.norm(ref)
     print(f"  tf {e_tf:.2e}  reconstruct {e_rec:.2e}", flush=True)
     assert e_tf < 1e-5 and e_rec < 1e-4
+
+
+@pytest.mark.parametrize("name,channels,props,shape", [
+    ("odd_responses", 1, (0, 16, 8), (6, 64, 96)),          # 15 responses: half a line
+    ("eight_properties", 0, (0, 1, 2, 5, 8, 11, 14, 17), (4, 96, 64)),   # more lines than fields
+    ("two_batches", 1, (0, 16, 8, 1), (3, 48, 1280)),        # rows of 1024: fields in two batches
+    ("one_response_set", 0, (1,), (5, 64, 160)),
+])
+def test_row_kernel_edges(gpu_lib, name, channels, props, shape):
+    """The bank where the fused row kernel splits its lines differently: an odd
+    number of responses, more response than field lines, rows longer than a
+    workgroup owns at once; element-wise <= 1e-5 of the largest entry, as for
+    every vector bank."""
+    nz, ny, nx = shape
+    o = op.Optics(model=op.VECTOR_3D, nz=nz, ny=ny, nx=nx, dz=0.25, dy=0.1, dx=0.1, wavelength=0.532, na_ill=0.5,
+                  na_det=1.1, n_medium=1.33, tilt_zenith=0.1, defocus=0.2, swing=0.1, vec_channels=channels,
+                  vec_props=props)
+    print(f"[case] vector rows {name} {shape}", flush=True)
+    from paper_2412_09775_amd import api
+    ref = tfm.transfer_function(o)[..., : nx // 2 + 1]
+    got = gpu_lib.transfer_function([api.Optics(**{f: getattr(o, f) for f in (
+        "model", "nz", "ny", "nx", "dz", "dy", "dx", "wavelength", "na_ill", "na_det", "n_medium", "defocus",
+        "tilt_zenith", "swing", "vec_channels", "vec_props")})], device="cuda:0").cpu().numpy()[0]
+    err = np.max(np.abs(got - ref)) / np.max(np.abs(ref))
+    print(f"  max abs / max {err:.2e}", flush=True)
+    assert err <= 1e-5
