@@ -1577,12 +1577,26 @@ static int run_tf(const wo_optics* o, int32_t n, const Shape& s, void* tf_out, v
   if (o->model == WO_MODEL_VECTOR_3D) return run_vector_tf(o, n, s, (float2*)tf_out, ws, hs, band_out);
   const int fs = field_sets(o);
   const int nv = n * fs;          // field sets: patch i, aperture c at i * fs + c
+  bool compact_out = false;
+  LatSupport sup = tf_support(o, n, s, &compact_out);
+  // the nine apertures through their shared scattered arm: direct arms of the
+  // sectors first (patch i, sector c at 8 i + c), then B of every patch
+  const bool shared_arm = fs == 9 && tf_rows_sectors_fits(sup.lx);
   std::vector<DevOptics> h(nv);
   for (int i = 0; i < n; ++i)
     for (int c = 0; c < fs; ++c) {
       DevOptics& d = h[i * fs + c];
       d = dev_optics(o[i]);
       if (fs == 9) d.sector = c < 8 ? c : -1;
+    }
+  if (shared_arm)
+    for (int i = 0; i < n; ++i) {
+      for (int c = 0; c < 8; ++c) {
+        h[8 * i + c] = dev_optics(o[i]);
+        h[8 * i + c].sector = c;
+      }
+      h[8 * n + i] = dev_optics(o[i]);
+      h[8 * n + i].sector = kScatteredArm;
     }
   char* w = (char*)ws;
   DevOptics* dopt = (DevOptics*)w;
@@ -1600,14 +1614,25 @@ static int run_tf(const wo_optics* o, int32_t n, const Shape& s, void* tf_out, v
   // in its support (columns kx < kt, band rows) until the Z pass, which
   // writes the full bank (zeros outside), when that compact copy fits the
   // field buffer behind the compact fields.
-  bool compact_out = false;
-  LatSupport sup = tf_support(o, n, s, &compact_out);
   float2* tf = (float2*)tf_out;
   const long M = s.Y * s.Xh;
   const long plane = s.Y * s.Xh;
   const long cplane = (long)sup.ly * sup.kt;   // a compact plane: ly rows of kt columns
   float2* cb = ab + compact_fields_elems(nv, nf, s, sup);
-  WO_TRY(launch_tf_fields_y(dopt, sm, nv, ab, partials, hs, &sup));
+  float2* arm_b = nullptr;
+  if (shared_arm) {
+    LatSupport as = sup;
+    as.xc = as.xa;
+    as.kp = as.kpa;
+    arm_b = ab + 8L * n * s.Z * sup.ly * sup.xa;
+    WO_TRY(launch_tf_fields_y(dopt, sm, 8 * n, ab, partials, hs, &as, true));
+    // B's workgroups write pupil sums (zeros) too: behind the sectors'
+    const int W1 = tf_tile_width(sm, sup.ly, 1);
+    WO_TRY(launch_tf_fields_y(dopt + 8 * n, sm, n, arm_b, partials + 8L * n * ((sup.xa + W1 - 1) / W1), hs, &sup,
+                              true));
+  } else {
+    WO_TRY(launch_tf_fields_y(dopt, sm, nv, ab, partials, hs, &sup));
+  }
   LatSupport full_out = sup;
   full_out.kt = (int)s.Xh;
   switch (o->model) {
@@ -1638,13 +1663,20 @@ static int run_tf(const wo_optics* o, int32_t n, const Shape& s, void* tf_out, v
     case WO_MODEL_SECTORS9_3D:
       // phase TF of every aperture: [patch][aperture][1][Z][Y][Xh]
       if (compact_out) {
-        WO_TRY(launch_tf_rows_labelfree(partials, sm, nv, ab, cb, s.Z * cplane, -1, cplane, hs, &sup,
-                                        sup.kt));
+        if (shared_arm)
+          WO_TRY(launch_tf_rows_sectors(partials, sm, n, ab, arm_b, cb, s.Z * cplane, cplane, sup.kt, sup, hs));
+        else
+          WO_TRY(launch_tf_rows_labelfree(partials, sm, nv, ab, cb, s.Z * cplane, -1, cplane, hs, &sup,
+                                          sup.kt));
         WO_TRY(launch_cols(cb, sup.ly, sup.kt, s.Z, s.Z, nv, -1.f, hs, "k_cols_y_tf", 1, sup.ky));
         WO_TRY(launch_cols_expand(cb, tf, (int)s.Z, sup.ly, (int)s.Y, (int)s.Xh, sup.kt, sup.ky, nv, -1.f,
                                   hs, band_out));
       } else {
-        WO_TRY(launch_tf_rows_labelfree(partials, sm, nv, ab, tf, s.Z * plane, -1, plane, hs, &full_out));
+        if (shared_arm)
+          WO_TRY(launch_tf_rows_sectors(partials, sm, n, ab, arm_b, tf, s.Z * plane, plane, (int)s.Xh, full_out,
+                                        hs));
+        else
+          WO_TRY(launch_tf_rows_labelfree(partials, sm, nv, ab, tf, s.Z * plane, -1, plane, hs, &full_out));
         WO_TRY(launch_cols(tf, (int)s.Y, s.Xh, s.Z, s.Z, nv, -1.f, hs, "k_cols_y_tf"));
         WO_TRY(launch_cols(tf, (int)s.Z, M, 1, 1, nv, -1.f, hs, "k_cols_z_tf"));
       }

@@ -657,12 +657,14 @@ enum Model { kFluor3D = 0, kLabelFree3D = 1, kLabelFreeThin = 2, kPol5 = 3, kSec
 
 // Per-patch optical parameters on the device (float64).  ``ibg`` is written
 // by the pupil-sum kernel: sum S P^2 (label-free) or sum P^2 (fluorescence).
+constexpr int kScatteredArm = 8;
 struct DevOptics {
   double wavelength, na_ill, na_det, n_medium;
   double defocus, tilt_zenith, tilt_azimuth;
   double edge_width;       // half-width of the soft edge, in frequency pixels
   double ibg;
   int sector;              // illumination aperture: -1 the full disc, 0..7 an azimuthal sector
+                           // (kScatteredArm: the field kernel's B alone)
   float zern[7];           // detection aberration, waves, Noll j = 5..11
   double det_tilt, det_azimuth;   // oblique detection: zenith and azimuth of the detection axis
 };

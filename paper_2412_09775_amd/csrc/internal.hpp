@@ -193,11 +193,23 @@ inline LatSupport full_support(const Sampling& sm) {
 }
 // Column tile width of the field kernel for a transform of ly points (0: ny);
 // the pupil-sum partials hold ceil(xc / width) doubles per patch.
-int tf_tile_width(const Sampling& sm, int ly = 0);
+// fields: 1 or 2 per tile column (0: by the model).
+int tf_tile_width(const Sampling& sm, int ly = 0, int fields = 0);
 // Planes per workgroup of the z-chunked field and gradient kernels.
 int tf_z_chunk(const Sampling& sm, long tiles_x, long npatch, long target);
 hipError_t launch_tf_fields_y(const DevOptics* opt, const Sampling& sm, int npatch, float2* ab,
-                              double* partials, hipStream_t s, const LatSupport* sup = nullptr);
+                              double* partials, hipStream_t s, const LatSupport* sup = nullptr,
+                              bool one_arm = false);
+// The nine apertures' phase responses from the sectors' direct arms a
+// [patch][8][z][y][xa], the shared scattered arm b [patch][z][y][xc] (field
+// kernel, one_arm) and the sectors' pupil-sum partials: columns k < kt of
+// out[(patch 9 + c) set_stride + z zstride + y pitch + k]; rows up to
+// tf_rows_sectors_fits.
+bool tf_rows_sectors_fits(int X);
+hipError_t launch_tf_rows_sectors(const double* partials, const Sampling& sm, int npatch, const float2* a,
+                                  const float2* b, float2* out, long set_stride, long zstride, int pitch,
+                                  const LatSupport& ls, hipStream_t s);
+// one_arm: one field per patch, [z][y][xc] (opt.sector kScatteredArm: B, else A).
 // out[patch * patch_stride + p * pstride + z * zstride + y * pitch + k], k < sup->kt
 // (pitch: Xh, or sup->kt when the caller keeps the compact columns).
 hipError_t launch_tf_rows_labelfree(const double* partials, const Sampling& sm, int npatch,

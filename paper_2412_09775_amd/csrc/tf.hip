@@ -9,6 +9,8 @@
 // -2 Im c (absorption).  The remaining Y (and, for 3D models, Z) transforms
 // reuse the generic column passes.  Fluorescence does the same with the single
 // field P e^{i 2 pi kz (z - dz0)} and the real PSF |h|^2 normalised to unit sum.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace wo {
@@ -148,7 +150,9 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // are evaluated once into registers; each plane then only needs its phase.
 // The workgroup of the first chunk also writes the tile's share of the pupil
 // sum (sum S P^2 for label-free, sum P^2 for fluorescence) to
-// partials[patch * tiles_x + tile].
+// partials[patch * tiles_x + tile].  NF = 1 also serves one arm of the label-free
+// pair alone (the nine-aperture model, whose apertures share B): B for
+// opt.sector = kScatteredArm, else A.
 template <int NS, int NF, bool AB, bool CS>
 __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restrict__ opt,
                                                       Sampling sm, float2* __restrict__ ab,
@@ -183,7 +187,9 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
   int zbeg, zend;
   z_chunk_range(Z, zsplit, ZC, zc, &zbeg, &zend);
   const DevOptics o = opt[patch];
-  constexpr bool fluor = NF == 1;   // one field (fluorescence) or A and B (label-free)
+  // one field (fluorescence, or one label-free arm) or A and B
+  const bool fluor = NF == 1 && sm.model == kFluor3D;
+  const bool arm_b = NF == 1 && o.sector == kScatteredArm;
   constexpr int nf = NF;
   constexpr int EPT = kEmax / NF;   // elements of a thread: Y * W * NF <= threads * kEmax
   const int x0 = (int)(tile * W);
@@ -234,15 +240,13 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
               if (fluor) {
                 fac[b][r] = (float)P;
                 psum += P * P;
-              } else {
+              } else if (NF == 2 ? f == 0 : !arm_b) {
                 double S = disc(fy - cy, fx - cx, ri, hw);
                 if (o.sector >= 0 && octant(fy - cy, fx - cx) != o.sector) S = 0.0;
-                if (f == 0) {
-                  fac[b][r] = (float)(S * P);
-                  psum += S * P * P;
-                } else if (kz > 0.0) {
-                  fac[b][r] = (float)(P * km / kz);   // P * (i k_m / kz)
-                }
+                fac[b][r] = (float)(S * P);
+                psum += S * P * P;
+              } else if (kz > 0.0) {
+                fac[b][r] = (float)(P * km / kz);   // P * (i k_m / kz)
               }
             }
           }
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
 #pragma unroll
       for (int b = 0; b < B0; ++b) {
         const int j = tid + b * nthr;
-        const bool fa = ((j & (nl - 1)) >> wsh) == 0;   // A (or the fluorescence field), else B
+        const bool fa = !arm_b && ((j & (nl - 1)) >> wsh) == 0;   // A (or the fluorescence field), else B
 #pragma unroll
         for (int r = 0; r < R0; ++r) {
           ph[b][r] = st[b][r] = make_float2(0.f, 0.f);
@@ -349,7 +353,7 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
     }
   } else {
     // z-independent factors of this thread's elements e = tid + i * nthr
-    double tkz[EPT], sp[EPT], gg[fluor ? 1 : EPT];
+    double tkz[EPT], sp[EPT], gg[NF == 1 ? 1 : EPT];
     float ab2[AB ? EPT : 1];   // 2 W(p): the aberration phase in units of pi
     {
       const double hw = soft_halfwidth(o, sm);
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
         tkz[i] = 0.0;
         sp[i] = 0.0;
         if constexpr (AB) ab2[i] = 0.f;
-        if (!fluor) gg[i] = 0.0;
+        if (NF == 2) gg[i] = 0.0;
         const int e = tid + i * nthr;
         if (e < Y * W) {
           const int ky = e >> wsh, w = e & (W - 1);
@@ -380,12 +384,14 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
               if (fluor) {
                 sp[i] = P;
                 psum += P * P;
+              } else if (arm_b) {
+                if (kz > 0.0) sp[i] = P * km / kz;
               } else {
                 double S = disc(fy - cy, fx - cx, ri, hw);
                 if (o.sector >= 0 && octant(fy - cy, fx - cx) != o.sector) S = 0.0;
                 psum += S * P * P;
                 sp[i] = S * P;
-                if (kz > 0.0) gg[i] = P * km / kz;   // P * (i k_m / kz)
+                if (NF == 2 && kz > 0.0) gg[i] = P * km / kz;   // P * (i k_m / kz)
               }
             }
           }
@@ -404,7 +410,7 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
         if (e < Y * W) {
           const int ky = e >> wsh, w = e & (W - 1);
           float2 A = make_float2(0.f, 0.f), B = make_float2(0.f, 0.f);
-          if (sp[i] != 0.0 || (!fluor && gg[i] != 0.0)) {
+          if (sp[i] != 0.0 || (NF == 2 && gg[i] != 0.0)) {
             // phase 2 pi kz (z - dz0): reduce the argument (in units of pi) in FP64
             // to [-1, 1], then evaluate sin/cos in FP32
             double arg = tkz[i] * dzr;
@@ -413,11 +419,12 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
             float snf, csf;
             sincospif(rr, &snf, &csf);
             const double sn = snf, cs = csf;
-            A = make_float2((float)(sp[i] * cs), (float)(sp[i] * sn));
-            if (!fluor) B = make_float2((float)(-gg[i] * sn), (float)(gg[i] * cs));   // e^{i phi} (i g)
+            A = arm_b ? make_float2((float)(-sp[i] * sn), (float)(sp[i] * cs))
+                      : make_float2((float)(sp[i] * cs), (float)(sp[i] * sn));
+            if (NF == 2) B = make_float2((float)(-gg[i] * sn), (float)(gg[i] * cs));   // e^{i phi} (i g)
           }
           buf[ky * nf * W + w] = A;
-          if (!fluor) buf[ky * nf * W + W + w] = B;
+          if (NF == 2) buf[ky * nf * W + W + w] = B;
         }
       }
       __syncthreads();
@@ -476,8 +483,8 @@ FftChoice tf_fields_default(int Z, long tiles, long npatch) {
 // plane, so several smaller workgroups per CU hide those waits better than
 // one large one (measured: 96x512x512, 8 columns x 2 fields 169 us, 4 columns
 // 135 us).
-int tf_tile_width(const Sampling& sm, int ly) {
-  const int nf = sm.model == kFluor3D ? 1 : 2;
+int tf_tile_width(const Sampling& sm, int ly, int fields) {
+  const int nf = fields > 0 ? fields : (sm.model == kFluor3D ? 1 : 2);
   const long n = ly > 0 ? ly : sm.ny;
   const long lim = lds_limit_bytes() / (long)sizeof(float2);
   int W = 16;
@@ -486,23 +493,23 @@ int tf_tile_width(const Sampling& sm, int ly) {
 }
 
 hipError_t launch_tf_fields_y(const DevOptics* opt, const Sampling& sm, int npatch, float2* ab,
-                              double* partials, hipStream_t s, const LatSupport* sup) {
+                              double* partials, hipStream_t s, const LatSupport* sup, bool one_arm) {
   const LatSupport ls = sup ? *sup : full_support(sm);
   if (ls.xc < 1 || ls.xc > sm.nx || ls.kp < 0 || ls.kp >= ls.xc || ls.ly < 2 || ls.ly > sm.ny ||
       ls.xa < 1 || ls.xa > ls.xc || ls.kpa < 0 || ls.kpa > ls.kp ||
       ls.xa - ls.kpa > ls.xc - ls.kp)   // A's columns among B's
     return hipErrorInvalidValue;
   const int LY = ls.ly;
-  const bool one_field = sm.model == kFluor3D;
+  const bool one_field = sm.model == kFluor3D || one_arm;
   const int xa = one_field ? ls.xc : ls.xa, kpa = one_field ? ls.kp : ls.kpa;
   FftPlan plan;
   if (!make_plan(LY, &plan)) return hipErrorInvalidValue;
-  const int nf = sm.model == kFluor3D ? 1 : 2;
-  const int W = tf_tile_width(sm, LY);
+  const int nf = one_field ? 1 : 2;
+  const int W = tf_tile_width(sm, LY, nf);
   const long tiles = (ls.xc + W - 1) / W;
   const FftKey key{kFftTfFields, LY, tiles, (long)npatch, sm.nz * 10 + nf};
   if (fft_recording())
-    fft_record(key, [=] { return launch_tf_fields_y(opt, sm, npatch, ab, partials, s, &ls); });
+    fft_record(key, [=] { return launch_tf_fields_y(opt, sm, npatch, ab, partials, s, &ls, one_arm); });
   FftChoice fc;
   if (!fft_lookup(key, &fc) || !tf_fields_choice_ok(sm.nz, fc)) fc = tf_fields_default(sm.nz, tiles, npatch);
   const int ZC = fc.w;
@@ -748,6 +755,186 @@ hipError_t launch_tf_rows_labelfree(const double* partials, const Sampling& sm, 
   hipLaunchKernelGGL((k_tf_rows_lf<0>), dim3((unsigned)nwg), dim3(thr), lds, s, partials, tiles_x, sm,
                      ab, out, patch_stride, pstride, zstride, R, wpp, ls.xc, ls.kp, ls.kt, OP, LY, LX,
                      ls.xa, ls.kpa, plan);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ rows: nine apertures
+
+// The phase responses of the eight sectors and the full disc, which share the
+// scattered arm B and whose direct arms add up (A_8 = sum of the sectors').  a:
+// [patch][8][z][y][XA], b: [patch][z][y][XC] (compact columns, last
+// non-negative KPA, KP), partials: [patch][8][tiles_x].  Per row: the inverse X
+// transforms of b and the eight a; at each x the nine responses 2 Re(b conj a_c)
+// / (X Y I_c) (I_8 the sum of the sectors' I_c), which are real and go forward
+// two to a complex line; out + (patch 9 + c) set_stride + z zstride + y OP + k,
+// k < KT.  Nine inverse and five forward transforms a row, where the pairwise
+// pass takes eighteen and nine and the fields' Y pass eighteen columns instead
+// of nine: 48 x 512 x 512 (rows of 384) fields and rows 240 + 379 us, 76 + 339 us so;
+// bound by VALU issue.  LDS line j nr + r: b (j = 0) or a_{j-1} of row r, then
+// the packed responses 2j and 2j + 1.
+template <int NS>
+__global__ __launch_bounds__(1024) void k_tf_rows_sectors(const double* __restrict__ partials, long tiles_x,
+                                                          Sampling sm, const float2* __restrict__ a,
+                                                          const float2* __restrict__ b,
+                                                          float2* __restrict__ out, long set_stride,
+                                                          long zstride, int rows_per_wg, long wg_per_patch,
+                                                          LatSupport sup, int OP, FftPlan plan) {
+  __shared__ double ibg_s[8];
+  extern __shared__ float2 smem[];
+  const int Y = sup.ly, Z = sm.nz;
+  const int X = NS > 0 ? NS : sup.lx;
+  float2* tw = smem;
+  float2* buf = smem + X;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  TwFetch twf;   // as in the row passes of the linear model
+  tw_begin(twf, tw, X, tid, nthr);
+  const long patch = blockIdx.x / wg_per_patch;
+  const long rpp = (long)Z * Y;
+  const long row0 = (blockIdx.x - patch * wg_per_patch) * (long)rows_per_wg;
+  const int nr = (int)min((long)rows_per_wg, rpp - row0);
+  const float2* ap = a + patch * 8 * rpp * sup.xa;
+  const float2* bp = b + patch * rpp * sup.xc;
+  const int PS = pad_shift(X), LS = row_stride(X);
+  const int z0 = (int)(row0 / Y), y0 = (int)(row0 - (long)z0 * Y);
+  const float inv_nr = 1.0f / (float)nr;
+  // as in k_tf_rows_lf: a column that is not stored loads a valid address and
+  // is zeroed after the loads
+  auto load = [&](int t, int i) {
+    const int j = div_small(t, inv_nr), r = t - j * nr;
+    const int xc = j == 0 ? sup.xc : sup.xa, kp = j == 0 ? sup.kp : sup.kpa;
+    const float2* src = (j == 0 ? bp : ap + (long)(j - 1) * rpp * sup.xa) + (row0 + r) * xc;
+    return src[i <= kp ? i : max(i - (X - xc), kp)];
+  };
+  auto kept = [&](int t, int i, float2 v) {
+    const bool isb = t < nr;
+    const int xc = isb ? sup.xc : sup.xa, kp = isb ? sup.kp : sup.kpa;
+    return (i <= kp || i >= X - (xc - kp - 1)) ? v : make_float2(0.f, 0.f);
+  };
+  // forward and inverse transforms in batches of the lines a workgroup owns
+  const int LB = nthr * kEmax / X;
+  for (int l0 = 0; l0 < 9 * nr; l0 += LB) {
+    const int nl = min(LB, 9 * nr - l0);
+    float2* lb = buf + l0 * LS;
+    if constexpr (NS > 0) {
+      first_pass_in2<NS, 0, false, kEmax, true, false>(
+          lb, nl, 1, LS, -1, 1.f, tid, nthr, [&](int l, int i) { return load(l0 + l, i); },
+          [&](int l, int i, float2 v) { return kept(l0 + l, i, v); },
+          [&] { if (l0 == 0) tw_end(twf, tw, X, tid, nthr); });
+      static_passes<NS, 0, false, kEmax, true, false, 1, StaticPlan<NS>::passes()>(lb, nl, 1, LS, -1, tw, 1.f,
+                                                                                   tid, nthr);
+    } else {
+      gather2_to_lds(lb, nl * X, tid, nthr, [&](int e) { const int l = e / X; return load(l0 + l, e - l * X); },
+                     [&](int e, float2 v) { const int l = e / X; return kept(l0 + l, e - l * X, v); },
+                     [&](int e) { const int l = e / X; return l * LS + row_slot(e - l * X, PS); },
+                     [&] { if (l0 == 0) tw_end(twf, tw, X, tid, nthr); });
+      __syncthreads();
+      fft_lines<0, 0, false, kEmax, true>(lb, LdsLines{nl, 1, LS, false, -1, true}, plan, tw, 1.f, tid, nthr);
+    }
+  }
+  {
+    const int wave = tid >> 6, nw = nthr >> 6;
+    for (int c = wave; c < 8; c += nw) {
+      const double* p = partials + (patch * 8 + c) * tiles_x;
+      double v = 0.0;
+      for (long i = tid & 63; i < tiles_x; i += 64) v += p[i];
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+      if ((tid & 63) == 0) ibg_s[c] = v;
+    }
+  }
+  __syncthreads();
+  float cs[9];
+  {
+    const double n2 = 2.0 / ((double)X * (double)Y);
+    double tot = 0.0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      tot += ibg_s[c];
+      cs[c] = (float)(n2 / ibg_s[c]);
+    }
+    cs[8] = (float)(n2 / tot);
+  }
+  for (int e = tid; e < nr * X; e += nthr) {
+    const int r = e / X, sl = row_slot(e - r * X, PS);
+    float2* p = buf + r * LS + sl;
+    const float2 vb = p[0];
+    float2 sum = make_float2(0.f, 0.f);
+    float v[10];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float2 va = p[(long)(c + 1) * nr * LS];
+      sum = cadd(sum, va);
+      v[c] = cs[c] * (vb.x * va.x + vb.y * va.y);
+    }
+    v[8] = cs[8] * (vb.x * sum.x + vb.y * sum.y);
+    v[9] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) p[(long)j * nr * LS] = make_float2(v[2 * j], v[2 * j + 1]);
+  }
+  __syncthreads();
+  for (int l0 = 0; l0 < 5 * nr; l0 += LB) {
+    const int nl = min(LB, 5 * nr - l0);
+    float2* lb = buf + l0 * LS;
+    if constexpr (NS > 0)
+      static_passes<NS, 0, false, kEmax, true, false, 0, StaticPlan<NS>::passes()>(lb, nl, 1, LS, -1, tw, -1.f,
+                                                                                   tid, nthr);
+    else
+      fft_lines<0, 0, false, kEmax, true>(lb, LdsLines{nl, 1, LS, false, -1, true}, plan, tw, -1.f, tid, nthr);
+  }
+  const int KT = sup.kt;
+  const float inv_kt = 1.0f / (float)KT;
+  for (int e = tid; e < 5 * nr * KT; e += nthr) {
+    const int l = div_small(e, inv_kt), k = e - l * KT;
+    const int j = div_small(l, inv_nr), r = l - j * nr;
+    const float2 zk = buf[l * LS + row_slot(k, PS)];
+    const float2 zm = buf[l * LS + row_slot(k == 0 ? 0 : X - k, PS)];
+    int y = y0 + r, z = z0;
+    while (y >= Y) { y -= Y; ++z; }
+    float2* op = out + (patch * 9 + 2 * j) * set_stride + (long)z * zstride + (long)y * OP + k;
+    *op = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
+    if (j < 4) op[set_stride] = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
+  }
+}
+
+// Rows per workgroup: about 2048 elements, and every line in LDS at once (rows up
+// to some 1700 points on 160 KB); 0: longer rows, for the pairwise pass.
+static int sectors_rows(int X) {
+  int R = std::max(1, 2048 / (9 * X));
+  return (long)(X + 9L * R * row_stride(X)) * (long)sizeof(float2) + 128 <= lds_limit_bytes() ? R : 0;
+}
+bool tf_rows_sectors_fits(int X) { return sectors_rows(X) > 0; }
+
+hipError_t launch_tf_rows_sectors(const double* partials, const Sampling& sm, int npatch, const float2* a,
+                                  const float2* b, float2* out, long set_stride, long zstride, int pitch,
+                                  const LatSupport& ls, hipStream_t s) {
+  const int LX = ls.lx, LY = ls.ly;
+  const int R = sectors_rows(LX);
+  if (R < 1 || ls.xc < 1 || ls.xc > LX || ls.kp < 0 || ls.kp >= ls.xc || ls.kt < 1 || 2 * (ls.kt - 1) > LX ||
+      LX > sm.nx || LY < 2 || LY > sm.ny || ls.xa < 1 || ls.xa > ls.xc || ls.kpa < 0 || ls.kpa >= ls.xa ||
+      pitch < ls.kt || npatch < 1)
+    return hipErrorInvalidValue;
+  FftPlan plan;
+  if (!make_plan(LX, &plan)) return hipErrorInvalidValue;
+  const long wpp = ((long)sm.nz * LY + R - 1) / R;
+  const int W = tf_tile_width(sm, LY, 1);
+  const long tiles = (ls.xa + W - 1) / W;
+  // at most kMaxElems at once: five lines of longer rows, then the other four
+  const long own = 9L * R * LX <= kMaxElems ? 9L * R * LX : std::min<long>(5L * LX, kMaxElems);
+  const int thr = threads_for(own);
+  const size_t lds = (size_t)(LX + 9L * R * row_stride(LX)) * sizeof(float2);
+  ScopedTiming _t("k_tf_rows_sectors", s);
+#define X_(NN)                                                                                      \
+  case NN:                                                                                          \
+    hipLaunchKernelGGL((k_tf_rows_sectors<NN>), dim3((unsigned)(wpp * npatch)), dim3(thr), lds, s,   \
+                       partials, tiles, sm, a, b, out, set_stride, zstride, R, wpp, ls, pitch, plan); \
+    return hipGetLastError();
+  switch (LX) {
+    WO_LATERAL_SIZES(X_)
+    default:
+      break;
+  }
+#undef X_
+  hipLaunchKernelGGL((k_tf_rows_sectors<0>), dim3((unsigned)(wpp * npatch)), dim3(thr), lds, s, partials, tiles,
+                     sm, a, b, out, set_stride, zstride, R, wpp, ls, pitch, plan);
   return hipGetLastError();
 }
 
