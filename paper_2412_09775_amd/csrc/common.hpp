@@ -163,6 +163,64 @@ __device__ __forceinline__ void dft6(float2* v, float s) {
   v[5] = csub(e[2], t2);
 }
 
+// 9 = 3 x 3: with n = 3 n1 + n2 and k = k1 + 3 k2, Y_n2[k1] = DFT3 over n1 of
+// v[3 n1 + n2] times W9^(n2 k1), and X[k1 + 3 k2] = DFT3 over n2 of Y_n2[k1].
+__device__ __forceinline__ void dft9(float2* v, float s) {
+  const float c1 = 0.76604444311897803520f, s1 = 0.64278760968653932632f;    // cos, sin of 2 pi / 9
+  const float c2 = 0.17364817766693034885f, s2 = 0.98480775301220805937f;    // of 4 pi / 9
+  const float c4 = -0.93969262078590838405f, s4 = 0.34202014332566873304f;   // of 8 pi / 9
+  auto rot = [s](float2 x, float c, float sn) {   // x (c + i s sn)
+    return make_float2(c * x.x - s * sn * x.y, c * x.y + s * sn * x.x);
+  };
+  float2 y[3][3];
+#pragma unroll
+  for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < 3; ++n1) y[n2][n1] = v[3 * n1 + n2];
+    dft3(y[n2], s);
+  }
+  y[1][1] = rot(y[1][1], c1, s1);
+  y[1][2] = rot(y[1][2], c2, s2);
+  y[2][1] = rot(y[2][1], c2, s2);
+  y[2][2] = rot(y[2][2], c4, s4);
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    float2 z[3] = {y[0][k1], y[1][k1], y[2][k1]};
+    dft3(z, s);
+#pragma unroll
+    for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = z[k2];
+  }
+}
+
+// 12 = 3 x 4: with n = 4 n1 + n2 and k = k1 + 3 k2, Y_n2[k1] = DFT3 over n1 of
+// v[4 n1 + n2] times W12^(n2 k1), and X[k1 + 3 k2] = DFT4 over n2 of Y_n2[k1].
+__device__ __forceinline__ void dft12(float2* v, float s) {
+  const float h = 0.86602540378443864676f;   // sin(pi / 3)
+  auto rot = [s](float2 x, float c, float sn) {
+    return make_float2(c * x.x - s * sn * x.y, c * x.y + s * sn * x.x);
+  };
+  float2 y[4][3];
+#pragma unroll
+  for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < 3; ++n1) y[n2][n1] = v[4 * n1 + n2];
+    dft3(y[n2], s);
+  }
+  y[1][1] = rot(y[1][1], h, 0.5f);       // W^1
+  y[1][2] = rot(y[1][2], 0.5f, h);       // W^2
+  y[2][1] = rot(y[2][1], 0.5f, h);       // W^2
+  y[2][2] = rot(y[2][2], -0.5f, h);      // W^4
+  y[3][1] = ctimes_i(y[3][1], s);        // W^3
+  y[3][2] = make_float2(-y[3][2].x, -y[3][2].y);   // W^6
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    float2 z[4] = {y[0][k1], y[1][k1], y[2][k1], y[3][k1]};
+    dft4(z, s);
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) v[k1 + 3 * k2] = z[k2];
+  }
+}
+
 // 10 = 2 x 5, as dft6: X[k] = E[k] + W10^k O[k], X[k + 5] = E[k] - W10^k O[k],
 // W10 = exp(s i pi / 5).
 __device__ __forceinline__ void dft10(float2* v, float s) {
@@ -225,34 +283,20 @@ __device__ __forceinline__ void dft_small(float2* v, float s) {
   else if constexpr (R == 5) dft5(v, s);
   else if constexpr (R == 6) dft6(v, s);
   else if constexpr (R == 8) dft8(v, s);
+  else if constexpr (R == 9) dft9(v, s);
   else if constexpr (R == 10) dft10(v, s);
+  else if constexpr (R == 12) dft12(v, s);
   else if constexpr (R == 16) dft16(v, s);
 }
 
-// Twiddle tables of the compiled transform lengths, evaluated by the compiler:
-// tw_n[m] = exp(-2 pi i m / n) rounded to FP32 from FP64 Taylor sums of sin
-// and cos on [0, pi/4] (error below 1e-16 there), the other octants by the
-// symmetries of compute_twiddles below.  A workgroup copies its table from
-// memory (it stays in the caches) instead of evaluating n/8 + 1 FP64 sines
-// and cosines.
+// Twiddle table of a compiled transform length, evaluated by the compiler:
+// tw[m] = exp(-2 pi i m / N) rounded to FP32 from FP64 Taylor sums of sin and cos
+// on [0, pi/4] (error below 1e-16 there), the rest of the turn by its symmetries.
+// A workgroup copies its table from memory (it stays in the caches) instead of
+// evaluating sines and cosines.  One table per length that a source file uses.
 struct TwPair {
   float c, s;
 };
-constexpr int kTwSizes[] = {16, 24, 32, 48, 64, 80, 96, 128, 160, 192, 240, 256, 320, 384, 480, 512, 1024};
-constexpr int kTwCount = sizeof(kTwSizes) / sizeof(kTwSizes[0]);
-constexpr int tw_offset(int n) {
-  int off = 0;
-  for (int i = 0; i < kTwCount; ++i) {
-    if (kTwSizes[i] == n) return off;
-    off += kTwSizes[i];
-  }
-  return -1;
-}
-constexpr int kTwTotal = [] {
-  int t = 0;
-  for (int i = 0; i < kTwCount; ++i) t += kTwSizes[i];
-  return t;
-}();
 constexpr double cx_sin(double x) {   // |x| <= pi/4: terms to x^29
   double x2 = x * x, term = x, sum = x;
   for (int k = 1; k < 15; ++k) {
@@ -269,34 +313,42 @@ constexpr double cx_cos(double x) {
   }
   return sum;
 }
-struct TwTables {
-  TwPair v[kTwTotal];
+template <int N>
+struct TwTable {
+  TwPair v[N];
 };
-constexpr TwTables make_tw_tables() {
-  TwTables t{};
-  int off = 0;
-  for (int i = 0; i < kTwCount; ++i) {
-    const int n = kTwSizes[i], e = n >> 3, qn = n >> 2;
-    TwPair* tw = t.v + off;
-    for (int r = 0; r <= e; ++r) {
-      const double a = 2.0 * 3.14159265358979323846 * (double)r / (double)n;
-      const float c = (float)cx_cos(a), s = (float)cx_sin(a);
-      tw[r] = TwPair{c, -s};
-      tw[qn + r] = TwPair{-s, -c};
-      tw[2 * qn + r] = TwPair{-c, s};
-      tw[3 * qn + r] = TwPair{s, c};
-      if (r > 0 && r < e) {
-        tw[qn - r] = TwPair{s, -c};
-        tw[2 * qn - r] = TwPair{-c, -s};
-        tw[3 * qn - r] = TwPair{-s, c};
-        tw[n - r] = TwPair{c, s};
-      }
-    }
-    off += n;
+template <int N>
+constexpr TwTable<N> make_tw_table() {
+  TwTable<N> t{};
+  for (int m = 0; m < N; ++m) {
+    // the angle in units of 2 pi / (8 N), folded into [0, N] (an eighth turn)
+    int u = 8 * m;
+    const bool low = u > 4 * N;      // below the real axis
+    if (low) u = 8 * N - u;
+    const bool left = u > 2 * N;     // left of the imaginary axis
+    if (left) u = 4 * N - u;
+    const bool swap = u > N;         // nearer the imaginary axis
+    if (swap) u = 2 * N - u;
+    const double a = 2.0 * 3.14159265358979323846 * (double)u / (8.0 * (double)N);
+    const float c = (float)(swap ? cx_sin(a) : cx_cos(a)), sn = (float)(swap ? cx_cos(a) : cx_sin(a));
+    t.v[m] = TwPair{left ? -c : c, low ? sn : -sn};
   }
   return t;
 }
-static __device__ const TwTables kTwTables = make_tw_tables();
+template <int N>
+static __device__ const TwTable<N> kTwTable = make_tw_table<N>();
+
+// cos and sin of (pi / 4) t, 0 <= t <= 1, in FP64 to 1e-11 (Taylor sums about 0:
+// the next terms are x^14 / 14! and x^13 / 13! at x = pi / 4), for entries rounded
+// to FP32.  About 20 instructions, where a full FP64 sine-cosine pair takes more
+// than a hundred.
+__device__ __forceinline__ void eighth_sincos(double t, double* sn, double* cs) {
+  const double x = 0.78539816339744830962 * t, x2 = x * x;
+  *cs = 1.0 + x2 * (-1.0 / 2 + x2 * (1.0 / 24 + x2 * (-1.0 / 720 + x2 * (1.0 / 40320 + x2 * (-1.0 / 3628800 +
+        x2 * (1.0 / 479001600))))));
+  *sn = x * (1.0 + x2 * (-1.0 / 6 + x2 * (1.0 / 120 + x2 * (-1.0 / 5040 + x2 * (1.0 / 362880 +
+        x2 * (-1.0 / 39916800))))));
+}
 
 // Twiddles tw[m] = exp(-2 pi i m / n), m < n, from FP64 sines and cosines.
 // When 8 divides n only the angles a = 2 pi r / n in [0, pi/4] (r <= n/8) are
@@ -305,18 +357,28 @@ static __device__ const TwTables kTwTables = make_tw_tables();
 // and signs, so each evaluation fills up to eight entries exactly, and a
 // workgroup computes n/8 + 1 sine-cosine pairs instead of n.
 __device__ __forceinline__ void compute_twiddles(float2* tw, int n, int tid, int nthr) {
+  const double inv = 1.0 / (double)n;
   if ((n & 7) != 0) {
+    // the angle in units of 2 pi / (8 n), folded into [0, n] (an eighth turn)
     for (int m = tid; m < n; m += nthr) {
-      double sn, cs;
-      sincospi(-2.0 * (double)m / (double)n, &sn, &cs);
-      tw[m] = make_float2((float)cs, (float)sn);
+      int u = 8 * m;
+      const bool low = u > 4 * n;      // below the real axis
+      if (low) u = 8 * n - u;
+      const bool left = u > 2 * n;     // left of the imaginary axis
+      if (left) u = 4 * n - u;
+      const bool swap = u > n;         // nearer the imaginary axis
+      if (swap) u = 2 * n - u;
+      double sd, cd;
+      eighth_sincos((double)u * inv, &sd, &cd);
+      const float c = (float)(swap ? sd : cd), s = (float)(swap ? cd : sd);
+      tw[m] = make_float2(left ? -c : c, low ? s : -s);
     }
     return;
   }
   const int e = n >> 3, qn = n >> 2;
   for (int r = tid; r <= e; r += nthr) {
     double sd, cd;
-    sincospi(2.0 * (double)r / (double)n, &sd, &cd);
+    eighth_sincos(8.0 * (double)r * inv, &sd, &cd);
     const float c = (float)cd, s = (float)sd;
     // exp(-i t) = (cos t, -sin t) for t = q pi/2 + a
     tw[r] = make_float2(c, -s);
@@ -334,27 +396,29 @@ __device__ __forceinline__ void compute_twiddles(float2* tw, int n, int tid, int
 
 // The table copy in two steps, so that a kernel can issue its data loads in
 // between and the two wait on memory together: tw_begin issues this thread's
-// loads of the table of length n (at most kTwFetch entries a thread), or
-// evaluates the twiddles when n has no table or the workgroup is too small;
+// loads of the table of length NS (at most kTwFetch entries a thread), or
+// evaluates the n twiddles when NS = 0 (no table) or the workgroup is too small;
 // tw_end writes the fetched entries to LDS.
 constexpr int kTwFetch = 4;
 struct TwFetch {
   float2 v[kTwFetch];
   bool fetched;
 };
+template <int NS>
 __device__ __forceinline__ void tw_begin(TwFetch& f, float2* tw, int n, int tid, int nthr) {
-  const int off = tw_offset(n);
-  f.fetched = off >= 0 && n <= kTwFetch * nthr;
+  f.fetched = NS > 0 && n <= kTwFetch * nthr;
   if (!f.fetched) {
     compute_twiddles(tw, n, tid, nthr);
     return;
   }
+  if constexpr (NS > 0) {
 #pragma unroll
-  for (int i = 0; i < kTwFetch; ++i) {
-    const int m = tid + i * nthr;
-    if (m < n) {
-      const TwPair p = kTwTables.v[off + m];
-      f.v[i] = make_float2(p.c, p.s);
+    for (int i = 0; i < kTwFetch; ++i) {
+      const int m = tid + i * nthr;
+      if (m < NS) {
+        const TwPair p = kTwTable<NS>.v[m];
+        f.v[i] = make_float2(p.c, p.s);
+      }
     }
   }
 }
@@ -510,8 +574,21 @@ struct LdsLines {
 // with 16, the 128-point backward rows of the auto-tune 7 % faster with 8).
 // row_stride(n) is the line pitch that holds n padded elements.
 __host__ __device__ constexpr int pad_shift(int n) { return n <= 128 ? 3 : 4; }
-__host__ __device__ __forceinline__ int row_slot(int i, int ps) { return i + (i >> ps); }
+constexpr int kNoPad = 31;
+__host__ __device__ __forceinline__ int row_slot(int i, int ps) { return ps == kNoPad ? i : i + (i >> ps); }
 __host__ __device__ __forceinline__ int row_stride(int n) { return n + (n >> pad_shift(n)) + 1; }
+
+// Lengths whose radix orders were measured one by one, and rows are padded.
+constexpr bool listed_length(int n) {
+  constexpr int sizes[] = {16, 24, 32, 48, 64, 80, 96, 128, 160, 192, 240, 256, 320, 384, 480, 512, 1024};
+  for (int v : sizes)
+    if (v == n) return true;
+  return false;
+}
+
+// Row padding of a compiled length: none but for those.
+template <int N>
+constexpr int kStaticPad = listed_length(N) ? pad_shift(N) : kNoPad;
 
 // Slots of a pass's elements relative to its first one.  The pass of radix R and
 // span NS of a padded row of length N reads elements k + r NB (NB = N / R) and
@@ -524,14 +601,14 @@ __host__ __device__ __forceinline__ int row_stride(int n) { return n + (n >> pad
 // 488 VALU instructions and 52 -> 36 LDS instructions per wave).
 template <int N, int R, int NS>
 struct RowPassSlots {
-  static constexpr int PS = pad_shift(N), B = 1 << PS, NB = N / R;
+  static constexpr int PS = kStaticPad<N>, B = PS == kNoPad ? 1 : 1 << PS, NB = N / R;
   static constexpr bool kLoad = NB % B == 0;
   static constexpr bool kStore = NS % B == 0 || (B % NS == 0 && (NS * R) % B == 0) || B % (NS * R) == 0;
   __device__ static __forceinline__ int load(int k, int r) {
-    return kLoad ? row_slot(k, PS) + r * (NB + (NB >> PS)) : row_slot(k + r * NB, PS);
+    return kLoad ? row_slot(k, PS) + r * row_slot(NB, PS) : row_slot(k + r * NB, PS);
   }
   __device__ static __forceinline__ int store(int d0, int r) {
-    return kStore ? row_slot(d0, PS) + r * NS + ((r * NS) >> PS) : row_slot(d0 + r * NS, PS);
+    return kStore ? row_slot(d0, PS) + row_slot(r * NS, PS) : row_slot(d0 + r * NS, PS);
   }
 };
 
@@ -1010,6 +1087,52 @@ namespace wo {
 // and shifts.  Used for the transform lengths of the workloads; other lengths
 // take the runtime plan above.
 
+// Radices of the other compiled lengths: the fewest passes (each is an LDS round
+// trip and two barriers) from radices up to 12, the most even split among equals;
+// odd radices first, then those with the fewest factors of two.  The first pass
+// writes its outputs with a stride of its radix: an odd stride spreads over the
+// LDS banks, so rows of these lengths are not padded and every element of a pass
+// is a constant offset from its first.
+struct Radices {
+  int r[8];
+  int n;
+};
+constexpr Radices few_passes_descending(int n, int most) {
+  Radices best{{}, 99};
+  if (n == 1) return Radices{{}, 0};
+  int least = 0;
+  for (int f = most; f >= 2; --f) {
+    if (f == 11 || f == 7 || n % f != 0) continue;
+    const Radices sub = few_passes_descending(n / f, f);
+    if (sub.n > 6 || sub.n + 1 > best.n) continue;
+    const int low = sub.n > 0 ? sub.r[sub.n - 1] : f;
+    if (sub.n + 1 == best.n && low <= least) continue;
+    best.n = sub.n + 1;
+    best.r[0] = f;
+    for (int q = 0; q < 7; ++q) best.r[q + 1] = q < sub.n ? sub.r[q] : 0;   // zero behind the last
+    least = low;
+  }
+  return best;
+}
+constexpr Radices few_passes(int n) {
+  Radices p = few_passes_descending(n, 12);
+  auto twos = [](int f) {
+    int t = 0;
+    while (f % 2 == 0) {
+      f /= 2;
+      ++t;
+    }
+    return t;
+  };
+  for (int a = 1; a < p.n && p.n <= 8; ++a)   // stable insertion sort
+    for (int b = a; b > 0 && twos(p.r[b]) < twos(p.r[b - 1]); --b) {
+      const int t = p.r[b];
+      p.r[b] = p.r[b - 1];
+      p.r[b - 1] = t;
+    }
+  return p;
+}
+
 template <int N, bool W16 = false>
 struct StaticPlan {
   // radices in the order 8, 4, 6, 2, 3, 5: a radix-6 butterfly (two radix-3
@@ -1033,6 +1156,7 @@ struct StaticPlan {
     // 80 = 8 10 and 480 = 8 6 10: one pass fewer than 8 2 5 and 8 4 3 5
     if (N == 80) return q == 0 ? 8 : (q == 1 ? 10 : 0);
     if (N == 480) return q == 0 ? 8 : (q == 1 ? 6 : (q == 2 ? 10 : 0));
+    if (!listed_length(N)) return few_passes(N).r[q];
     int m = N, p = 0;
     const int order[6] = {8, 4, 6, 2, 3, 5};
     for (int i = 0; i < 6; ++i) {
@@ -1327,8 +1451,20 @@ __device__ __forceinline__ void fft_lines(float2* lds, const LdsLines& L, const 
 
 }  // namespace wo
 
-// Transform lengths with compiled FFT stages (lateral sizes and axial sizes;
-// 80 and 96 points carry the auto-tune of 128- and 160-pixel tiles).
+// Transform lengths with compiled FFT stages: WO_LATERAL_SIZES in every kernel
+// along a lateral axis (80 and 96 points carry the auto-tune of 128- and
+// 160-pixel tiles); the linear model's passes take every even length of the
+// factors 2, 3 and 5 from 32 to 1024 (WO_EVEN_SIZES: the others of that range) and,
+// along Z, every such length from 16 to 128 (WO_Z_SIZES).
 #define WO_LATERAL_SIZES(X) X(64) X(80) X(96) X(128) X(160) X(192) X(240) X(256) X(320) X(384) X(480) X(512) X(1024)
-#define WO_AXIAL_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96)
 #define WO_ALL_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(80) X(96) X(128) X(160) X(192) X(240) X(256) X(320) X(384) X(480) X(512) X(1024)
+#define WO_EVEN_SIZES(X) X(36) X(40) X(50) X(54) X(60) X(72) X(90) X(100) X(108) X(120) X(144) X(150) \
+   X(162) X(180) X(200) X(216) X(250) X(270) X(288) X(300) X(324) X(360) X(400) X(432) X(450) X(486) \
+   X(500) X(540) X(576) X(600) X(640) X(648) X(720) X(750) X(768) X(800) X(810) X(864) X(900) X(960) \
+   X(972) X(1000)
+#define WO_Z_SIZES(X) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(50) X(54) \
+   X(60) X(64) X(72) X(75) X(80) X(81) X(90) X(96) X(100) X(108) X(120) X(125) X(128)
+// (75 x 270 x 450, label-free: Y passes 30 + 60 -> 12 + 20 us, Z pass 49 -> 25, the
+// bank's Z pass 30 -> 19; the whole step 386 -> 204 us.)
+// Z lengths that are neither in WO_ALL_SIZES nor in WO_EVEN_SIZES.
+#define WO_Z_ONLY_SIZES(X) X(18) X(20) X(25) X(27) X(30) X(45) X(75) X(81) X(125)

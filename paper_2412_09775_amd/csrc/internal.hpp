@@ -92,6 +92,13 @@ inline bool threads_ok(int thr, long elems) {
   return thr >= 64 && thr <= kMaxThreads && thr % 64 == 0 && (long)thr * kEmax >= elems;
 }
 std::vector<FftChoice> fft_candidates(const FftKey& k);
+// Default schedules of the passes and whether the device runs a given one.
+bool rows_choice_ok(int X, const FftChoice& c);
+FftChoice rows_default(int X);
+bool zop_choice_ok(int Z, int CH, const FftChoice& c);
+FftChoice zop_default(int Z, int CH);
+// Widest column tile (a power of two, at most 16) of `ch` channels of n points.
+int tile_width(int n, int ch);
 // While a tuning run records, each tunable launch registers its key and a
 // closure that repeats it.
 bool fft_recording();
@@ -114,6 +121,15 @@ hipError_t launch_rows_r2c(const float* in, float2* out, int X, const RowGroups&
 // pitch `pitch` hold the columns k < kt, the others are taken as zero.
 hipError_t launch_rows_c2r(const float2* in, float* out, int X, const RowGroups& g, float scale,
                            hipStream_t s, int kt = 0, int pitch = 0);
+// Band rows of a compact plane: index b of the nb = 2 ky + 1 band rows is row b
+// (b <= ky) or row Y - nb + b; nb = Y (ky >= Y) is every row.
+__device__ __forceinline__ int band_row(int b, int ky, int nb, int Y) {
+  return b <= ky ? b : b + (Y - nb);
+}
+__device__ __forceinline__ bool in_band(int y, int ky, int nb, int Y) {
+  return nb == Y || y <= ky || y >= Y - (nb - ky - 1);
+}
+
 // In-place FFT along the middle axis of planes [N][M]; plane p of group g
 // starts at data + (g * group_stride + p) * N * M.
 // band: 0 every row; 1 stores only the band rows n <= ky or n >= N - ky of

@@ -787,7 +787,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_sectors(const double* __restri
   float2* buf = smem + X;
   const int tid = threadIdx.x, nthr = blockDim.x;
   TwFetch twf;   // as in the row passes of the linear model
-  tw_begin(twf, tw, X, tid, nthr);
+  tw_begin<NS>(twf, tw, X, tid, nthr);
   const long patch = blockIdx.x / wg_per_patch;
   const long rpp = (long)Z * Y;
   const long row0 = (blockIdx.x - patch * wg_per_patch) * (long)rows_per_wg;

@@ -342,7 +342,7 @@ __global__ __launch_bounds__(1024) void k_vec_rows(const VecRec* __restrict__ re
   const VecRec& rv = rec[patch];
   const float2* sp = spec + patch * (long)F * zy * XC + r * XC;
   TwFetch twf;   // as in the row passes of the linear model
-  tw_begin(twf, tw, N, tid, nthr);
+  tw_begin<N>(twf, tw, N, tid, nthr);
   constexpr int NP = StaticPlan<N>::passes();
 #pragma unroll
   for (int l0 = 0; l0 < F; l0 += NB) {
