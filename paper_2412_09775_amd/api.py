@@ -14,7 +14,9 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import operator
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libwaveorder.so")
@@ -205,40 +207,72 @@ def _get(o, name):
     return o[name] if isinstance(o, dict) else getattr(o, name)
 
 
+# One record of wo_optics: the integers, the doubles, the aberration, the detection
+# axis, the vector model's integers and Jones vector.
+_RECORD = struct.Struct("@4i12d7d2d2i8i4d")
+assert _RECORD.size == ctypes.sizeof(WoOptics)
+_RECORD_FIELDS = operator.attrgetter(*_FIELDS, "zernike", "det_tilt", "det_azimuth", "vec_channels", "vec_props",
+                                     "ill_jones")
+
+
+def _fill_record(buf, offset, o) -> bool:
+    """Writes one optics object that has every attribute as plain numbers; False
+    where it has not (the general path converts it, or says what is wrong)."""
+    try:
+        v = _RECORD_FIELDS(o)
+        z, props, (jx, jy) = v[16], v[20], v[21]
+        nz, np_ = len(z), len(props)
+        if nz > N_ZERNIKE or np_ > 8:
+            return False
+        jx, jy = complex(jx), complex(jy)
+        _RECORD.pack_into(buf, offset, *v[:16], *z, *(0.0,) * (N_ZERNIKE - nz), v[17], v[18], v[19], np_,
+                          *props, *(0,) * (8 - np_), jx.real, jx.imag, jy.real, jy.imag)
+    except (AttributeError, TypeError, ValueError, struct.error):
+        return False
+    return True
+
+
 def optics_array(optics) -> ctypes.Array:
     """ctypes array of wo_optics from one optics object or a sequence of them."""
     if not isinstance(optics, (list, tuple)):
         optics = [optics]
     arr = (WoOptics * len(optics))()
     for i, o in enumerate(optics):
-        for f in _FIELDS:
-            setattr(arr[i], f, int(_get(o, f)) if f in ("model", "nz", "ny", "nx") else float(_get(o, f)))
-        z = getattr(o, "zernike", None)
-        if z is None and isinstance(o, dict):
-            z = o.get("zernike")
-        z = tuple(z) if z is not None else ()
-        if len(z) > N_ZERNIKE:
-            raise ValueError(f"at most {N_ZERNIKE} Zernike coefficients (Noll 5..11)")
-        for j in range(N_ZERNIKE):
-            arr[i].zernike[j] = float(z[j]) if j < len(z) else 0.0
-        for f in ("det_tilt", "det_azimuth"):
-            v = o.get(f, 0.0) if isinstance(o, dict) else getattr(o, f, 0.0)
-            setattr(arr[i], f, float(v))
-
-        def opt(f, default):
-            return o.get(f, default) if isinstance(o, dict) else getattr(o, f, default)
-
-        arr[i].vec_channels = int(opt("vec_channels", 0))
-        props = tuple(int(p) for p in opt("vec_props", (0, 16, 8, 1)))
-        if len(props) > 8:
-            raise ValueError("at most 8 vector-model properties")
-        arr[i].vec_nprops = len(props)
-        for k in range(8):
-            arr[i].vec_props[k] = props[k] if k < len(props) else 0
-        jx, jy = (complex(v) for v in opt("ill_jones", (2 ** -0.5, 1j * 2 ** -0.5)))
-        for k, v in enumerate((jx.real, jx.imag, jy.real, jy.imag)):
-            arr[i].ill_jones[k] = v
+        # a record at once (1.6 us each, 11.7 field by field): a batch's optics cost more
+        # than its launches otherwise
+        if not _fill_record(arr, i * _RECORD.size, o):
+            _fill_fields(arr, i, o)
     return arr
+
+
+def _fill_fields(arr, i, o):
+    for f in _FIELDS:
+        setattr(arr[i], f, int(_get(o, f)) if f in ("model", "nz", "ny", "nx") else float(_get(o, f)))
+    z = getattr(o, "zernike", None)
+    if z is None and isinstance(o, dict):
+        z = o.get("zernike")
+    z = tuple(z) if z is not None else ()
+    if len(z) > N_ZERNIKE:
+        raise ValueError(f"at most {N_ZERNIKE} Zernike coefficients (Noll 5..11)")
+    for j in range(N_ZERNIKE):
+        arr[i].zernike[j] = float(z[j]) if j < len(z) else 0.0
+    for f in ("det_tilt", "det_azimuth"):
+        v = o.get(f, 0.0) if isinstance(o, dict) else getattr(o, f, 0.0)
+        setattr(arr[i], f, float(v))
+
+    def opt(f, default):
+        return o.get(f, default) if isinstance(o, dict) else getattr(o, f, default)
+
+    arr[i].vec_channels = int(opt("vec_channels", 0))
+    props = tuple(int(p) for p in opt("vec_props", (0, 16, 8, 1)))
+    if len(props) > 8:
+        raise ValueError("at most 8 vector-model properties")
+    arr[i].vec_nprops = len(props)
+    for k in range(8):
+        arr[i].vec_props[k] = props[k] if k < len(props) else 0
+    jx, jy = (complex(v) for v in opt("ill_jones", (2 ** -0.5, 1j * 2 ** -0.5)))
+    for k, v in enumerate((jx.real, jx.imag, jy.real, jy.imag)):
+        arr[i].ill_jones[k] = v
 
 
 def _check(status: int, where: str):
@@ -248,8 +282,11 @@ def _check(status: int, where: str):
 
 def bank_shape(optics):
     """(C, P, dims, complex elements per patch) of the model's bank."""
+    return _bank_shape(optics_array(optics))
+
+
+def _bank_shape(arr):
     lib = load()
-    arr = optics_array(optics)
     C, P, dims = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     n = ctypes.c_int64()
     _check(lib.wo_bank_shape(arr, ctypes.byref(C), ctypes.byref(P), ctypes.byref(dims), ctypes.byref(n)),
@@ -260,8 +297,11 @@ def bank_shape(optics):
 def lateral_support(optics):
     """Lateral support of the model for these patches (wo_lateral_support) as a dict:
     field_cols (A, B), tf_cols, band_rows, tf_lengths (y, x)."""
+    return _lateral_support(optics_array(optics))
+
+
+def _lateral_support(arr):
     lib = load()
-    arr = optics_array(optics)
     out = WoSupport()
     _check(lib.wo_lateral_support(arr, len(arr), ctypes.byref(out)), "wo_lateral_support")
     return {"field_cols": tuple(out.field_cols), "tf_cols": out.tf_cols, "band_rows": out.band_rows,
@@ -269,9 +309,8 @@ def lateral_support(optics):
 
 
 def workspace_size(optics, op: int) -> int:
-    lib = load()
     arr = optics_array(optics)
-    return int(lib.wo_workspace_size(arr, len(arr), op))
+    return int(load().wo_workspace_size(arr, len(arr), op))
 
 
 def _stream(stream):
@@ -284,9 +323,9 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
-def _workspace(optics, op, device, ws=None):
+def _workspace(arr, op, device, ws=None):
     import torch
-    need = workspace_size(optics, op)
+    need = int(load().wo_workspace_size(arr, len(arr), op))
     if ws is not None and ws.numel() >= need:
         return ws, need
     return torch.empty(max(need, 1), dtype=torch.uint8, device=device), need
@@ -294,9 +333,12 @@ def _workspace(optics, op, device, ws=None):
 
 def bank_dims(optics):
     """Tensor shape of one call's bank: (n, C, P, [Z,] Y, X/2+1)."""
-    arr = optics_array(optics)
+    return _bank_dims(optics_array(optics))
+
+
+def _bank_dims(arr):
     o = arr[0]
-    C, P, dims, _ = bank_shape(optics)
+    C, P, dims, _ = _bank_shape(arr)
     xh = o.nx // 2 + 1
     if dims == 3:
         return (len(arr), C, P, o.nz, o.ny, xh)
@@ -308,48 +350,45 @@ def transfer_function(optics, device="cuda", out=None, ws=None, stream=None):
     import torch
     lib = load()
     arr = optics_array(optics)
-    shape = bank_dims(optics)
     if out is None:
-        out = torch.empty(shape, dtype=torch.complex64, device=device)
-    ws, need = _workspace(optics, OP_TRANSFER_FUNCTION, out.device, ws)
+        out = torch.empty(_bank_dims(arr), dtype=torch.complex64, device=device)
+    ws, need = _workspace(arr, OP_TRANSFER_FUNCTION, out.device, ws)
     _check(lib.wo_transfer_function(arr, len(arr), _ptr(out), _ptr(ws), ws.numel(), _stream(stream)),
            "wo_transfer_function")
     return out
 
 
-def _linear(fn, name, optics, tf, x, out_shape, extra, ws, stream, op):
+def _linear(fn, name, arr, tf, x, out_shape, extra, ws, stream, op):
     import torch
-    lib = load()
-    arr = optics_array(optics)
     out = torch.empty(out_shape, dtype=torch.float32, device=x.device)
-    ws, _ = _workspace(optics, op, x.device, ws)
+    ws, _ = _workspace(arr, op, x.device, ws)
     _check(fn(arr, len(arr), _ptr(tf), _ptr(x), *extra(out), _ptr(ws), ws.numel(), _stream(stream)), name)
     return out
 
 
-def _vol(optics):
-    o = optics_array(optics)[0]
+def _vol(arr):
+    o = arr[0]
     return (o.ny, o.nx) if o.model == MODEL_LABELFREE_THIN else (o.nz, o.ny, o.nx)
 
 
 def forward(optics, tf, f, b=None, ws=None, stream=None):
     """d = H f + b; f: (n, P, *vol) float32 -> d: (n, C, *dvol)."""
     arr = optics_array(optics)
-    C, P, dims, _ = bank_shape(optics)
+    C, P, dims, _ = _bank_shape(arr)
     o = arr[0]
     dshape = (len(arr), C, o.ny, o.nx) if dims == 2 else (len(arr), C, o.nz, o.ny, o.nx)
     lib = load()
-    return _linear(lib.wo_forward, "wo_forward", optics, tf, f.contiguous(), dshape,
+    return _linear(lib.wo_forward, "wo_forward", arr, tf, f.contiguous(), dshape,
                    lambda out: (_ptr(b), _ptr(out)), ws, stream, OP_FORWARD)
 
 
 def reconstruct(optics, tf, d, eta, b=None, ws=None, stream=None):
     """Tikhonov reconstruction; d: (n, C, *dvol) -> f: (n, P, *vol)."""
     arr = optics_array(optics)
-    C, P, dims, _ = bank_shape(optics)
-    fshape = (len(arr), P) + _vol(optics)
+    C, P, dims, _ = _bank_shape(arr)
+    fshape = (len(arr), P) + _vol(arr)
     lib = load()
-    return _linear(lib.wo_reconstruct, "wo_reconstruct", optics, tf, d.contiguous(), fshape,
+    return _linear(lib.wo_reconstruct, "wo_reconstruct", arr, tf, d.contiguous(), fshape,
                    lambda out: (_ptr(b), ctypes.c_double(eta), _ptr(out)), ws, stream, OP_RECONSTRUCT)
 
 
@@ -363,8 +402,8 @@ def reconstruct_noalloc(optics, tf, d, eta, b=None, out=None, stream=None):
     import torch
     lib = load()
     arr = optics_array(optics)
-    C, P, dims, _ = bank_shape(optics)
-    fshape = (len(arr), P) + _vol(optics)
+    C, P, dims, _ = _bank_shape(arr)
+    fshape = (len(arr), P) + _vol(arr)
     if out is None:
         out = torch.empty(fshape, dtype=torch.float32, device=d.device)
     _check(lib.wo_reconstruct_noalloc(arr, len(arr), _ptr(tf), _ptr(d.contiguous()), _ptr(b),
@@ -399,11 +438,14 @@ def reconstruct_grad(optics, d, eta, dL_df, b=None, want_theta=True, want_data=T
 def band_dims(optics):
     """Tensor shape of one call's bank in the band layout: (n, C, P, Z, band rows, columns);
     the polarisation model's reduced form is the label-free pair, (n, 1, 2, ...)."""
-    arr = optics_array(optics)
-    C, P, dims, _ = bank_shape(optics)
+    return _band_dims(optics_array(optics))
+
+
+def _band_dims(arr):
+    C, P, dims, _ = _bank_shape(arr)
     if arr[0].model == MODEL_POL5_3D:
         C, P = 1, 2
-    sup = lateral_support(optics)
+    sup = _lateral_support(arr)
     return (len(arr), C, P, arr[0].nz, sup["band_rows"], sup["tf_cols"])
 
 
@@ -422,8 +464,8 @@ def transfer_function_band(optics, device="cuda", out=None, ws=None, stream=None
     lib = load()
     arr = optics_array(optics)
     if out is None:
-        out = torch.empty(band_dims(optics), dtype=torch.complex64, device=device)
-    ws, _ = _workspace(optics, OP_TRANSFER_FUNCTION, out.device, ws)
+        out = torch.empty(_band_dims(arr), dtype=torch.complex64, device=device)
+    ws, _ = _workspace(arr, OP_TRANSFER_FUNCTION, out.device, ws)
     _check(lib.wo_transfer_function_band(arr, len(arr), _ptr(out), _ptr(ws), ws.numel(), _stream(stream)),
            "wo_transfer_function_band")
     return out
@@ -435,10 +477,10 @@ def linear_band(op, optics, tf_band, x, eta=0.0, b=None, ws=None, stream=None):
     import torch
     lib = load()
     arr = optics_array(optics)
-    C, P, dims, _ = bank_shape(optics)
+    C, P, dims, _ = _bank_shape(arr)
     nout = C if op == OP_FORWARD else P
-    out = torch.empty((len(arr), nout) + _vol(optics), dtype=torch.float32, device=x.device)
-    ws, _ = _workspace(optics, op, x.device, ws)
+    out = torch.empty((len(arr), nout) + _vol(arr), dtype=torch.float32, device=x.device)
+    ws, _ = _workspace(arr, op, x.device, ws)
     _check(lib.wo_linear_band(op, arr, len(arr), _ptr(tf_band), _ptr(x.contiguous()), _ptr(b),
                               ctypes.c_double(eta), _ptr(out), _ptr(ws), ws.numel(), _stream(stream)),
            "wo_linear_band")
@@ -448,10 +490,10 @@ def linear_band(op, optics, tf_band, x, eta=0.0, b=None, ws=None, stream=None):
 def adjoint(optics, tf, r, ws=None, stream=None):
     """g = H^H r; r: (n, C, *dvol) -> g: (n, P, *vol)."""
     arr = optics_array(optics)
-    C, P, dims, _ = bank_shape(optics)
-    gshape = (len(arr), P) + _vol(optics)
+    C, P, dims, _ = _bank_shape(arr)
+    gshape = (len(arr), P) + _vol(arr)
     lib = load()
-    return _linear(lib.wo_adjoint, "wo_adjoint", optics, tf, r.contiguous(), gshape,
+    return _linear(lib.wo_adjoint, "wo_adjoint", arr, tf, r.contiguous(), gshape,
                    lambda out: (_ptr(out),), ws, stream, OP_ADJOINT)
 
 
@@ -513,7 +555,7 @@ def midband_loss_grad(optics, d, eta, nu_c=None, ws=None, stream=None, aberratio
     arr = optics_array(optics)
     n = len(arr)
     d = pack_stacks(d)
-    need = tune_workspace_size(optics, 1)
+    need = int(lib.wo_tune_workspace_size(arr, n, 1))
     if ws is None or ws.numel() < need:
         ws = torch.empty(need, dtype=torch.uint8, device=d.device)
     eta_a, eta_p = _dbl(np.broadcast_to(eta, (n,)))
@@ -537,7 +579,7 @@ def _tune_call(fn, name, optics, d, eta, iters, lr, lo, hi, mask, multistart, th
     n = len(arr)
     M = int(multistart)
     d = pack_stacks(d)
-    need = tune_workspace_size(optics, M)
+    need = int(load().wo_tune_workspace_size(arr, n, M))
     if ws is None or ws.numel() < need:
         ws = torch.empty(need, dtype=torch.uint8, device=d.device)
     opts = WoAutotuneOpts()
@@ -855,7 +897,7 @@ def fft_tune(op, optics, tf=None, x=None, out=None, eta=0.0, reps=3, ws=None, st
     lib = load()
     arr = optics_array(optics)
     dev = out.device
-    ws, _ = _workspace(optics, op, dev, ws)
+    ws, _ = _workspace(arr, op, dev, ws)
     _check(lib.wo_fft_tune(int(op) | (FFT_TUNE_BAND if band else 0), arr, len(arr), _ptr(tf), _ptr(x),
                            _ptr(out), float(eta), int(reps), _ptr(ws), ws.numel(), _stream(stream)),
            "wo_fft_tune")

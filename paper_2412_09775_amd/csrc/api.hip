@@ -1087,6 +1087,7 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
   const int np = L.np, nv = L.nv;
   std::vector<DevOptics> hopt(nv);
   std::vector<TuneInit> hst(np);
+  double last_nuc = NAN, last_count = 0.0;
   // the box of theta: shared but for the cap on NA_det (clamp_box)
   TuneShared shared;
   memset(&shared, 0, sizeof(shared));
@@ -1099,7 +1100,10 @@ int tune_setup(const wo_optics* o, const TuneGroup& g, int starts, const double*
     }
     if (lo && hi) clamp_box(&o[i], blo, bhi);
     const double nuc = (nu_c && nu_c[i] > 0) ? nu_c[i] : (o[i].na_det + o[i].na_ill) / o[i].wavelength;
-    const double bc = band_count(&o[i], nuc);
+    // the patches of a group share the sampling: one count per run of equal bands
+    if (!(nuc == last_nuc)) last_count = band_count(&o[i], nuc);
+    last_nuc = nuc;
+    const double bc = last_count;
     if (bc < 1) return WO_EINVAL;
     hst[j] = TuneInit{eta[i], nuc, bc, bhi[1]};
     if (j == 0) {
