@@ -4,7 +4,9 @@
 // linear head to 3 normalised parameters; MSE loss; AdamW.
 //
 // Every convolution (forward, input gradient, weight gradient) is one
-// implicit GEMM on v_mfma_f32_16x16x32_bf16 with FP32 accumulation:
+// implicit GEMM on v_mfma_f32_16x16x32_bf16 with FP32 accumulation (conv.hip
+// for the channel counts whose K steps lie inside one tap, the network's among
+// them; the gathers here for all others):
 //   forward  C[pos_out][co]  = sum_{tap,ci} x(im2col)        * w[co][tap][ci]
 //   dgrad    C[pos_in][ci]   = sum_{tap,co} gz(col2im)       * w[co][tap][ci]
 //   wgrad    C[co][tap,ci]   = sum_{pos_out} gz[pos_out][co] * x(im2col)
@@ -20,32 +22,16 @@
 #include <vector>
 
 #include "../../include/waveorder.h"
+#include "bf16.hpp"
 #include "internal.hpp"
 
 namespace wo {
-
-typedef unsigned short u16;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ u16 f2bf(float f) {  // round to nearest even
-  unsigned u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (u16)(u >> 16);  // inf / nan
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (u16)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(u16 b) { return __uint_as_float(((unsigned)b) << 16); }
 
 // ------------------------------------------------------------------ operand gathers
 //
 // A gather exposes row(i) -> a per-row context computed once per kernel (the
 // thread's row of the tile never changes), then at(ctx, k) for the K index.
 // K indices walk (tap, channel) with the channel fastest.
-
-struct ConvGeom {
-  int D, H, W, C;     // input volume and channels
-  int Do, Ho, Wo;     // output volume
-};
 
 struct TapCh {  // (tap, channel) of a K index, advanced incrementally
   int tap, ch;
@@ -264,15 +250,8 @@ struct ClassRows {
 
 constexpr int kBM = 64, kBN = 64, kBK = 32, kLdsPad = 8;   // kBM x kBN: the default tile
 
-__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad_f(float z) {
-  return 0.5f * (1.f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
-}
-
-// Where a tile's FP32 results go.  StoreC: C_z[orow][n] (z the split-K chunk,
-// Mout rows per chunk).  StoreBiasGelu (forward convolutions): the
-// pre-activation z = v + b[n] in FP32 and a = BF16(GELU(z)), the same
-// arithmetic as a separate bias-GELU pass over C.
+// Where a tile's FP32 results go: C_z[orow][n] (z the split-K chunk, Mout rows
+// per chunk).
 struct StoreC {
   float* C;
   long Mout, N;
@@ -280,19 +259,6 @@ struct StoreC {
     C[((long)zi * Mout + orow) * N + col] = v;
   }
 };
-struct StoreBiasGelu {
-  float* z;
-  u16* a;
-  const float* b;
-  long N;
-  __device__ __forceinline__ void operator()(int, long orow, long col, float v) const {
-    const float t = v + b[col];
-    const long i = orow * N + col;
-    z[i] = t;
-    a[i] = f2bf(gelu_f(t));
-  }
-};
-
 // (tap, channel) of K index k with `ch` channels per tap; K indices stay
 // below 2^31 (checked on the host), so 32-bit arithmetic.
 __device__ __forceinline__ TapCh tapch(long k, int ch) {
@@ -573,6 +539,13 @@ static hipError_t dgrad_classes(const u16* gz, const u16* w, ConvGeom gout, int 
   const long tm = narrow ? 128 : kBM, tn = narrow ? 32 : kBN;
   const int splits = part ? dgrad_splits(pl.tiles, pl.kmax) : 1;
   float* dst = splits > 1 ? part : out;
+  hipError_t e = hipSuccess;
+  bool taken;
+  {
+    ScopedTiming _t(tag, s);
+    taken = conv_dgrad_taps(gz, w, gout, Cin, N, splits, dst, s, &e);
+  }
+  if (!taken) {
   dim3 grid((unsigned)((mmax + tm - 1) / tm), (unsigned)((Cin + tn - 1) / tn), (unsigned)(nc * splits));
   const int am = load_mode(cl.a[0]), bm = load_mode(cl.b[0]);
   {
@@ -592,10 +565,35 @@ static hipError_t dgrad_classes(const u16* gz, const u16* w, ConvGeom gout, int 
   else WO_DG(0, 0);
 #undef WO_DG
   }
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
+  }
   if (e != hipSuccess || splits == 1) return e;
   ScopedTiming _t("k_reduce_parts", s);
   return reduce_parts(part, splits, Mout * Cin, out, s);
+}
+
+// Forward product into partials (out.c) or, in one split, through the bias and
+// GELU (out.z, out.a); and the weight gradient's partials: on tap-sized K steps
+// where the channels allow it, else on the general gathers.
+static hipError_t conv_fwd(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
+                           const ConvFwdOut& out, hipStream_t s, const char* tag) {
+  hipError_t e = hipSuccess;
+  {
+    ScopedTiming _t(tag, s);
+    if (conv_fwd_taps(x, w, g, P, Cout, splits, out, s, &e)) return e;
+  }
+  if (out.a) return hipErrorInvalidValue;   // the network's channels are all of the first kind
+  const long K = 27L * g.C;
+  return gemm(GatherIm2col{x, g}, GatherRows{w, K, g.C}, out.c, P, Cout, K, splits, s, tag);
+}
+static hipError_t conv_wgrad(const u16* x, const u16* gz, const ConvGeom& g, long P, int Cout, int splits,
+                             float* part, hipStream_t s, const char* tag) {
+  hipError_t e = hipSuccess;
+  {
+    ScopedTiming _t(tag, s);
+    if (conv_wgrad_taps(x, gz, g, P, Cout, splits, part, s, &e)) return e;
+  }
+  return gemm(GatherT{gz, Cout}, GatherIm2colT{GatherIm2col{x, g}}, part, Cout, 27L * g.C, P, splits, s, tag);
 }
 
 static int splits_used(long K, int splits) {
@@ -651,7 +649,7 @@ static hipError_t reduce_parts(const float* part, int z, long n, float* out, hip
 // ------------------------------------------------------------------ elementwise
 
 // z = z + b[c] (FP32), a = BF16(GELU(z)): the forward epilogue after a split-K
-// sum (StoreBiasGelu's arithmetic).
+// sum, with the arithmetic of the one-split convolutions' epilogue.
 __global__ void k_bias_gelu(float* __restrict__ z, const float* __restrict__ b, long P, int Co,
                             u16* __restrict__ a) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1004,13 +1002,12 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
     const int fs = fwd_splits(L.P_out, L.Cout, K);
     if (fs == 1) {
       // the GEMM's epilogue adds the bias and applies GELU (z and a written directly)
-      WO_HIP_CHECK(gemm_ep(GatherIm2col{a_in, L.g}, GatherRows{pbf + L.w_off, K, L.Cin},
-                           StoreBiasGelu{z, a, params + L.b_off, L.Cout}, L.P_out, L.Cout, K, 1, s,
-                           kFwdTag[l]));
+      WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, 1,
+                            ConvFwdOut{nullptr, z, a, params + L.b_off}, s, kFwdTag[l]));
     } else {
       // few tiles: split K, sum the partials in a fixed order into z, then bias and GELU
-      WO_HIP_CHECK(gemm(GatherIm2col{a_in, L.g}, GatherRows{pbf + L.w_off, K, L.Cin}, part, L.P_out, L.Cout,
-                        K, fs, s, kFwdTag[l]));
+      WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, fs,
+                            ConvFwdOut{part, nullptr, nullptr, nullptr}, s, kFwdTag[l]));
       { ScopedTiming _tm("k_reduce_parts", s);
       WO_HIP_CHECK(reduce_parts(part, splits_used(K, fs), L.P_out * L.Cout, z, s));
       }
@@ -1048,8 +1045,7 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
     // weight gradient, split over output positions
     const int splits = wgrad_splits(L.P_out, L.Cout, K);
     const int zs = splits_used(L.P_out, splits);
-    WO_HIP_CHECK(gemm(GatherT{gz, L.Cout}, GatherIm2colT{GatherIm2col{a_prev, L.g}}, part, L.Cout, K,
-                      L.P_out, splits, s, kWgradTag[l]));
+    WO_HIP_CHECK(conv_wgrad(a_prev, gz, L.g, L.P_out, L.Cout, splits, part, s, kWgradTag[l]));
     { ScopedTiming _tm("k_reduce_parts", s);
     WO_HIP_CHECK(reduce_parts(part, zs, (long)L.Cout * K, grad + L.w_off, s));
     }
@@ -1081,8 +1077,7 @@ hipError_t conv_fwd_raw(const u16* x, const u16* w, int N, int D, int H, int W, 
                         float* out, hipStream_t s) {
   ConvGeom g{D, H, W, Cin, (D - 1) / 2 + 1, (H - 1) / 2 + 1, (W - 1) / 2 + 1};
   const long P = (long)N * g.Do * g.Ho * g.Wo;
-  return gemm(GatherIm2col{x, g}, GatherRows{w, 27L * Cin, Cin}, out, P, Cout, 27L * Cin, 1, s,
-              "k_gemm_conv_fwd");
+  return conv_fwd(x, w, g, P, Cout, 1, ConvFwdOut{out, nullptr, nullptr, nullptr}, s, "k_gemm_conv_fwd");
 }
 
 hipError_t conv_dgrad_raw(const u16* gz, const u16* w, int N, int D, int H, int W, int Cin, int Cout,
@@ -1100,8 +1095,7 @@ hipError_t conv_wgrad_raw(const u16* x, const u16* gz, int N, int D, int H, int 
   while (splits > 1 && (long)splits_used(P, splits) * Cout * K > part_elems) splits /= 2;
   const int zs = splits_used(P, splits);
   if ((long)zs * Cout * K > part_elems) return hipErrorInvalidValue;
-  hipError_t e = gemm(GatherT{gz, Cout}, GatherIm2colT{GatherIm2col{x, g}}, part, Cout, K, P, splits,
-                      s, "k_gemm_conv_wgrad");
+  hipError_t e = conv_wgrad(x, gz, g, P, Cout, splits, part, s, "k_gemm_conv_wgrad");
   if (e != hipSuccess) return e;
   return reduce_parts(part, zs, (long)Cout * K, out, s);
 }

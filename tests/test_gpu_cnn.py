@@ -224,3 +224,38 @@ def test_cnn_start_call_equals_the_python_path(gpu_lib):
     ref = learned_init.denormalise_theta(y.astype(np.float64))
     assert np.array_equal(got[:, :3], ref)
     assert np.array_equal(got[:, 3], [o.tilt_azimuth for o in opts])
+
+
+# K steps of one tap: a single position, odd extents, channel tiles that are not
+# full (40, 160 columns), a column count no four divide (34), one input channel in
+# one and two channel tiles, three tap-straddling column tiles (96 channels)
+TAP_SHAPES = [(1, 1, 1, 1, 32, 32), (1, 5, 7, 9, 32, 32), (3, 6, 7, 10, 64, 40), (1, 9, 7, 6, 32, 34),
+              (1, 9, 7, 6, 1, 24), (2, 6, 9, 10, 1, 40), (2, 5, 17, 9, 96, 160)]
+
+
+@pytest.mark.parametrize("N,D,H,W,Ci,Co", TAP_SHAPES)
+def test_tap_steps_match_oracle(gpu_lib, N, D, H, W, Ci, Co):
+    test_conv_kernels_match_oracle(gpu_lib, N, D, H, W, Ci, Co)
+
+
+def test_tap_steps_of_a_large_batch(gpu_lib):
+    """Enough rows for 32 per wave; a sample's results depend on that sample alone,
+    so the first and last are compared with the oracle of those two."""
+    import torch
+    N, D, H, W, Ci, Co = 9, 31, 64, 64, 32, 40
+    rng = np.random.default_rng(4)
+    x = cnn.bf16(rng.standard_normal((2, D, H, W, Ci)))
+    w = cnn.bf16(rng.standard_normal((Co, 3, 3, 3, Ci)) / np.sqrt(27 * Ci))
+    pick = [0] + [1] * (N - 2) + [0]
+    xb = torch.from_numpy(to_bits(x)[pick]).cuda()
+    wb = torch.from_numpy(to_bits(w.reshape(Co, -1))).cuda()
+    z = gpu_lib.conv3d_forward(xb, wb, Co).cpu().numpy()
+    ref = cnn.conv3d(x[:1], w)
+    assert rel(z[0], ref[0]) < 1e-5 and np.array_equal(z[0], z[-1])
+    w2 = cnn.bf16(rng.standard_normal((64, 3, 3, 3, Ci)) / np.sqrt(27 * Ci))
+    gz = cnn.bf16(rng.standard_normal((2,) + ref.shape[1:4] + (64,)))
+    gx = gpu_lib.conv3d_input_grad(torch.from_numpy(to_bits(gz)[pick]).cuda(),
+                                   torch.from_numpy(to_bits(w2.reshape(64, -1))).cuda(),
+                                   (N, D, H, W, Ci)).cpu().numpy()
+    assert rel(gx[0], cnn.conv3d_dgrad(gz[:1], w2, (1, D, H, W, Ci))[0]) < 1e-5
+    assert np.array_equal(gx[0], gx[-1])
