@@ -573,7 +573,7 @@ static hipError_t dgrad_classes(const u16* gz, const u16* w, ConvGeom gout, int 
 }
 
 // Forward product into partials (out.c) or, in one split, through the bias and
-// GELU (out.z, out.a); and the weight gradient's partials: on tap-sized K steps
+// GELU (out.d, out.a); and the weight gradient's partials: on tap-sized K steps
 // where the channels allow it, else on the general gathers.
 static hipError_t conv_fwd(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
                            const ConvFwdOut& out, hipStream_t s, const char* tag) {
@@ -646,25 +646,37 @@ static hipError_t reduce_parts(const float* part, int z, long n, float* out, hip
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ elementwise
-
-// z = z + b[c] (FP32), a = BF16(GELU(z)): the forward epilogue after a split-K
-// sum, with the arithmetic of the one-split convolutions' epilogue.
-__global__ void k_bias_gelu(float* __restrict__ z, const float* __restrict__ b, long P, int Co,
-                            u16* __restrict__ a) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P * Co) return;
-  const float v = z[i] + b[i % Co];
-  z[i] = v;
-  a[i] = f2bf(gelu_f(v));
+// out[c] = sum over rows of part[rows][n], for many rows of few columns: past
+// kBiasPartsMax rows in two stages, so that no workgroup walks thousands of
+// rows (8192 rows of 32: two launches of 4.6 us).  The first stage
+// sums rows 0, G, 2G, .. as wide rows of G n columns behind the input.
+constexpr int kBiasPartsMax = 1024, kSumStages = 8;
+static hipError_t sum_rows(float* part, long rows, long n, float* out, hipStream_t s) {
+  if (rows <= kBiasPartsMax || rows % kSumStages != 0) return reduce_parts(part, (int)rows, n, out, s);
+  const hipError_t e = reduce_parts(part, (int)(rows / kSumStages), kSumStages * n, part + rows * n, s);
+  return e != hipSuccess ? e : reduce_parts(part + rows * n, kSumStages, n, out, s);
 }
 
-// gz = BF16(ga * GELU'(z)) over P positions x Co channels (Co divides 256), and
+// ------------------------------------------------------------------ elementwise
+
+// z = z + b[c], a = BF16(GELU(z)) and, d set, z is replaced by GELU'(z): the
+// forward epilogue after a split-K sum, with the arithmetic of the one-split
+// convolutions' epilogue.
+__global__ void k_bias_gelu(float* __restrict__ z, const float* __restrict__ b, long P, int Co,
+                            u16* __restrict__ a, int d) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= P * Co) return;
+  float dv;
+  a[i] = f2bf(gelu_f(z[i] + b[i % Co], dv));
+  if (d) z[i] = dv;
+}
+
+// gz = BF16(ga * d), d = GELU'(z), over P positions x Co channels (Co divides 256), and
 // the bias gradient's first stage: workgroup g sums the rounded gz of its rows
 // [g R, g R + R) per channel in a fixed order into part[g][c].  Lanes run along
 // the channels, so every load and store is coalesced.
 __global__ __launch_bounds__(256) void k_gelu_bwd_bias(const float* __restrict__ ga,
-                                                       const float* __restrict__ z, long P, int Co,
+                                                       const float* __restrict__ d, long P, int Co,
                                                        long R, u16* __restrict__ gz,
                                                        float* __restrict__ part) {
   __shared__ float red[256];
@@ -675,19 +687,19 @@ __global__ __launch_bounds__(256) void k_gelu_bwd_bias(const float* __restrict__
   // four rows per iteration, their loads issued before any is used (the sum
   // still adds the rows in order)
   for (long p = r0 + t / Co; p < r1; p += 4 * step) {
-    float gv[4], zv[4];
+    float gv[4], dv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const long q = p + u * step;
       const long i = q * Co + c;
       gv[u] = q < r1 ? ga[i] : 0.f;
-      zv[u] = q < r1 ? z[i] : 0.f;
+      dv[u] = q < r1 ? d[i] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const long q = p + u * step;
       if (q < r1) {
-        const u16 b = f2bf(gv[u] * gelu_grad_f(zv[u]));
+        const u16 b = f2bf(gv[u] * dv[u]);
         gz[q * Co + c] = b;
         s += bf2f(b);
       }
@@ -704,7 +716,6 @@ __global__ __launch_bounds__(256) void k_gelu_bwd_bias(const float* __restrict__
 
 // Rows per workgroup of k_gelu_bwd_bias: a multiple of 256 / Co, at most
 // kBiasPartsMax workgroups.
-constexpr int kBiasPartsMax = 1024;
 static long bias_rows(long P, int Co) {
   const long step = 256 / Co;
   long R = std::max<long>(4 * step, (P + kBiasPartsMax - 1) / kBiasPartsMax);
@@ -724,6 +735,7 @@ __global__ __launch_bounds__(256) void k_sumsq_slices(const float* __restrict__ 
   const long i0 = blockIdx.x * len, i1 = min(vol, i0 + len);
   const float* xs = x + n * vol;
   double s = 0.0;
+#pragma unroll 8
   for (long i = i0 + threadIdx.x; i < i1; i += blockDim.x) s += (double)xs[i] * xs[i];
   red[threadIdx.x] = s;
   __syncthreads();
@@ -734,21 +746,32 @@ __global__ __launch_bounds__(256) void k_sumsq_slices(const float* __restrict__ 
   if (threadIdx.x == 0) part[n * kNormSlices + blockIdx.x] = red[0];
 }
 
+// Eight elements per thread: a workgroup's wait for its sample's slice sums is
+// spread over 2048 elements (64 stacks of 32x64x64: 23 us at one, 11 us so).
+constexpr int kScaleRun = 8;
 __global__ __launch_bounds__(256) void k_scale_bf16(const float* __restrict__ x, long vol,
                                                     const double* __restrict__ part,
                                                     u16* __restrict__ out) {
   __shared__ float inv_s;
-  const long n = blockIdx.y;
+  __shared__ double ps[kNormSlices];
+  const long n = blockIdx.y, i0 = (long)blockIdx.x * (256 * kScaleRun) + threadIdx.x;
+  float v[kScaleRun];
+#pragma unroll
+  for (int u = 0; u < kScaleRun; ++u) v[u] = i0 + 256 * u < vol ? x[n * vol + i0 + 256 * u] : 0.f;
+  if (threadIdx.x < kNormSlices) ps[threadIdx.x] = part[n * kNormSlices + threadIdx.x];
+  __syncthreads();
   if (threadIdx.x == 0) {
     double ss = 0.0;
-    for (int k = 0; k < kNormSlices; ++k) ss += part[n * kNormSlices + k];
+#pragma unroll
+    for (int k = 0; k < kNormSlices; ++k) ss += ps[k];
     const double rms = sqrt(ss / (double)vol);
     inv_s = rms > 0.0 ? (float)(1.0 / rms) : 1.f;
   }
   __syncthreads();
   const float inv = inv_s;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < vol) out[n * vol + i] = f2bf(x[n * vol + i] * inv);
+#pragma unroll
+  for (int u = 0; u < kScaleRun; ++u)
+    if (i0 + 256 * u < vol) out[n * vol + i0 + 256 * u] = f2bf(v[u] * inv);
 }
 
 // Head per sample: feat = mean over positions of a (BF16), y = Wh feat + bh.
@@ -762,9 +785,12 @@ __global__ __launch_bounds__(256) void k_head(const u16* __restrict__ a, long np
                                               float* __restrict__ ga) {
   __shared__ float feat[256];
   __shared__ float dys[kCnnOut];
+  __shared__ float whs[kCnnOut * 256];   // the chains over the features wait on LDS, not on memory
   const int n = blockIdx.x, c = threadIdx.x;
+  for (int i = c; i < kCnnOut * Cf; i += 256) whs[i] = wh[i];
   if (c < Cf) {
     float s = 0.f;
+#pragma unroll 16
     for (long p = 0; p < npos; ++p) s += bf2f(a[((long)n * npos + p) * Cf + c]);
     feat[c] = s / (float)npos;
     if (feat_out) feat_out[(long)n * Cf + c] = feat[c];
@@ -772,7 +798,8 @@ __global__ __launch_bounds__(256) void k_head(const u16* __restrict__ a, long np
   __syncthreads();
   if (c < kCnnOut) {
     float y = bh[c];
-    for (int k = 0; k < Cf; ++k) y += wh[c * Cf + k] * feat[k];
+#pragma unroll 16
+    for (int k = 0; k < Cf; ++k) y += whs[c * Cf + k] * feat[k];
     y_out[n * kCnnOut + c] = y;
     if (target) {
       const float d = y - target[n * kCnnOut + c];
@@ -792,32 +819,42 @@ __global__ __launch_bounds__(256) void k_head(const u16* __restrict__ a, long np
     }
     if (c < Cf) {
       float g = 0.f;
-      for (int j = 0; j < kCnnOut; ++j) g += wh[j * Cf + c] * dys[j];
+      for (int j = 0; j < kCnnOut; ++j) g += whs[j * Cf + c] * dys[j];
       g /= (float)npos;
       for (long p = 0; p < npos; ++p) ga[((long)n * npos + p) * Cf + c] = g;
     }
   }
 }
 
-// Head gradients (single workgroup): gwh = dy^T feat, gbh = sum dy, loss = mean.
-__global__ __launch_bounds__(256) void k_head_grads(const float* __restrict__ dy,
-                                                    const float* __restrict__ feat,
-                                                    const float* __restrict__ lossp, int N, int Cf,
-                                                    float* __restrict__ gwh, float* __restrict__ gbh,
-                                                    float* __restrict__ loss) {
-  for (int i = threadIdx.x; i < kCnnOut * Cf; i += blockDim.x) {
+// Head gradients: gwh = dy^T feat (a thread per entry), and by the last
+// workgroup gbh = sum dy, loss = mean.  Serial chains over the batch in one
+// order; small workgroups and unrolled loads keep many loads in flight
+// (64 stacks: 36 us as one workgroup, 4 us so).
+constexpr int kHeadThreads = 64;
+__global__ __launch_bounds__(kHeadThreads) void k_head_grads(const float* __restrict__ dy,
+                                                             const float* __restrict__ feat,
+                                                             const float* __restrict__ lossp, int N, int Cf,
+                                                             float* __restrict__ gwh, float* __restrict__ gbh,
+                                                             float* __restrict__ loss) {
+  if (blockIdx.x + 1 < gridDim.x) {
+    const int i = blockIdx.x * kHeadThreads + threadIdx.x;
+    if (i >= kCnnOut * Cf) return;
     const int j = i / Cf, c = i - j * Cf;
     float s = 0.f;
+#pragma unroll 16
     for (int n = 0; n < N; ++n) s += dy[n * kCnnOut + j] * feat[(long)n * Cf + c];
     gwh[i] = s;
+    return;
   }
   if (threadIdx.x < kCnnOut) {
     float s = 0.f;
+#pragma unroll 16
     for (int n = 0; n < N; ++n) s += dy[n * kCnnOut + threadIdx.x];
     gbh[threadIdx.x] = s;
   }
-  if (threadIdx.x == 0 && loss) {
+  if (threadIdx.x == kCnnOut && loss) {
     float s = 0.f;
+#pragma unroll 16
     for (int n = 0; n < N; ++n) s += lossp[n];
     *loss = s / (float)(N * kCnnOut);
   }
@@ -919,6 +956,10 @@ static int fwd_splits(long P, long Co, long K) {
   return (int)std::max<long>(1, std::min<long>({8, (1024 + tiles - 1) / tiles, K / 256}));
 }
 
+// Scratch of sum_rows below: the rows and, past kBiasPartsMax of them, the sums
+// of its first stage.
+static long gelu_sums_elems(long rows, long n) { return (rows + kSumStages) * n; }
+
 static CnnWs cnn_ws(const Net& net) {
   CnnWs w;
   size_t b = 0;
@@ -940,6 +981,7 @@ static CnnWs cnn_ws(const Net& net) {
       gd.C = L.Cout;
       const DgradPlan pl = dgrad_plan(nullptr, nullptr, gd, L.Cin, net.N);
       if (pl.nc > 0) maxpart = std::max(maxpart, (long)dgrad_splits(pl.tiles, pl.kmax) * L.P_in * L.Cin);
+      maxpart = std::max(maxpart, gelu_sums_elems(conv_dgrad_gelu_rows(gd, L.Cin, net.N), L.Cin));
     }
   }
   w.gz = take(maxg * sizeof(u16));
@@ -966,6 +1008,16 @@ static const char* const kWgradTag[kCnnLayers] = {"k_gemm_conv_wgrad_l0", "k_gem
 static const char* const kDgradTag[kCnnLayers] = {"k_gemm_conv_dgrad_l0", "k_gemm_conv_dgrad_l1",
                                                   "k_gemm_conv_dgrad_l2", "k_gemm_conv_dgrad_l3"};
 
+// Row sums of layer l's input gradient where one split takes it through the
+// previous layer's GELU; 0 where one split cannot, -1 where K is split.
+static long gelu_rows(const Net& net, int l) {
+  const Layer& L = net.L[l];
+  ConvGeom gd = L.g;
+  gd.C = L.Cout;
+  const DgradPlan pl = dgrad_plan(nullptr, nullptr, gd, L.Cin, net.N);
+  return dgrad_splits(pl.tiles, pl.kmax) == 1 ? conv_dgrad_gelu_rows(gd, L.Cin, net.N) : -1;
+}
+
 int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, const float* target,
             float* y_out, float* loss_out, float* grad_out, void* ws, hipStream_t s) {
   const Net net = make_net(N, Z, Y, X);
@@ -990,7 +1042,7 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
     double* nrm = (double*)(w + W.nrm);
     ScopedTiming _tm("k_normalise", s);
     hipLaunchKernelGGL(k_sumsq_slices, dim3(kNormSlices, N), dim3(256), 0, s, x, vol, nrm);
-    hipLaunchKernelGGL(k_scale_bf16, dim3(blocks(vol, 256), N), dim3(256), 0, s, x, vol, nrm, xb);
+    hipLaunchKernelGGL(k_scale_bf16, dim3(blocks(vol, 256 * kScaleRun), N), dim3(256), 0, s, x, vol, nrm, xb);
   }
   WO_HIP_CHECK(hipGetLastError());
   const u16* a_in = xb;
@@ -1003,7 +1055,7 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
     if (fs == 1) {
       // the GEMM's epilogue adds the bias and applies GELU (z and a written directly)
       WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, 1,
-                            ConvFwdOut{nullptr, z, a, params + L.b_off}, s, kFwdTag[l]));
+                            ConvFwdOut{nullptr, target ? z : nullptr, a, params + L.b_off}, s, kFwdTag[l]));
     } else {
       // few tiles: split K, sum the partials in a fixed order into z, then bias and GELU
       WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, fs,
@@ -1013,7 +1065,7 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
       }
       { ScopedTiming _tm("k_bias_gelu", s);
       hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(L.P_out * L.Cout, 256)), dim3(256), 0, s, z,
-                         params + L.b_off, L.P_out, L.Cout, a);
+                         params + L.b_off, L.P_out, L.Cout, a, target ? 1 : 0);
       }
     }
     a_in = a;
@@ -1025,14 +1077,15 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
   WO_HIP_CHECK(hipGetLastError());
   if (!target) return WO_OK;
   { ScopedTiming _tm("k_head_grads", s);
-  hipLaunchKernelGGL(k_head_grads, dim3(1), dim3(256), 0, s, dy, feat, lossp, N, Cf,
+  hipLaunchKernelGGL(k_head_grads, dim3(blocks((long)kCnnOut * Cf, kHeadThreads) + 1), dim3(kHeadThreads), 0, s, dy, feat, lossp, N, Cf,
                      grad + net.wh_off, grad + net.bh_off, loss_out);
   }
+  const u16* gcur = nullptr;   // this layer's gz, once an input gradient has written it
   for (int l = kCnnLayers - 1; l >= 0; --l) {
     const Layer& L = net.L[l];
     const long K = 27L * L.Cin;
     const float* z = (const float*)(w + W.z[l]);
-    {
+    if (!gcur) {
       // gz and the bias gradient: partials in part, summed before the weight
       // gradient reuses part
       const long R = bias_rows(L.P_out, L.Cout);
@@ -1040,19 +1093,41 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
       ScopedTiming _tm("k_gelu_bwd_bias", s);
       hipLaunchKernelGGL(k_gelu_bwd_bias, dim3(G), dim3(256), 0, s, ga, z, L.P_out, L.Cout, R, gz, part);
       WO_HIP_CHECK(reduce_parts(part, G, (long)L.Cout, grad + L.b_off, s));
+      gcur = gz;
     }
     const u16* a_prev = l == 0 ? xb : (const u16*)(w + W.a[l - 1]);
     // weight gradient, split over output positions
     const int splits = wgrad_splits(L.P_out, L.Cout, K);
     const int zs = splits_used(L.P_out, splits);
-    WO_HIP_CHECK(conv_wgrad(a_prev, gz, L.g, L.P_out, L.Cout, splits, part, s, kWgradTag[l]));
+    WO_HIP_CHECK(conv_wgrad(a_prev, gcur, L.g, L.P_out, L.Cout, splits, part, s, kWgradTag[l]));
     { ScopedTiming _tm("k_reduce_parts", s);
     WO_HIP_CHECK(reduce_parts(part, zs, (long)L.Cout * K, grad + L.w_off, s));
     }
-    if (l > 0) {
-      ConvGeom gd = L.g;
-      gd.C = L.Cout;
-      WO_HIP_CHECK(dgrad_classes(gz, pbf + L.w_off, gd, L.Cin, net.N, ga, part, s, kDgradTag[l]));
+    if (l == 0) break;
+    ConvGeom gd = L.g;
+    gd.C = L.Cout;
+    // an unsplit gradient that is not fused is written to ga in the pass that
+    // reads gz: gz must not be there then
+    const long rows = gelu_rows(net, l);
+    const bool to_ga = gcur == gz;
+    if (rows > 0 && (!to_ga || l == 1 || gelu_rows(net, l - 1) != 0)) {
+      // one split: straight to the previous layer's gz (in the buffer, gz or ga,
+      // that this layer's does not occupy) and its bias gradient, so the FP32
+      // gradient is neither written nor read back
+      u16* next = to_ga ? (u16*)ga : gz;
+      hipError_t e = hipSuccess;
+      {
+        ScopedTiming _tm(kDgradTag[l], s);
+        if (!conv_dgrad_gelu(gcur, pbf + L.w_off, gd, L.Cin, net.N, (const float*)(w + W.z[l - 1]), next, part, s, &e))
+          return WO_EINVAL;
+      }
+      WO_HIP_CHECK(e);
+      ScopedTiming _tm("k_reduce_parts", s);
+      WO_HIP_CHECK(sum_rows(part, rows, L.Cin, grad + net.L[l - 1].b_off, s));
+      gcur = next;
+    } else {
+      WO_HIP_CHECK(dgrad_classes(gcur, pbf + L.w_off, gd, L.Cin, net.N, ga, part, s, kDgradTag[l]));
+      gcur = nullptr;
     }
   }
   return WO_OK;

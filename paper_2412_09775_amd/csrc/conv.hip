@@ -16,9 +16,11 @@
 //   - the product is taken transposed, so that a lane ends with four
 //     consecutive channels of one position and stores 16 bytes.
 // Measured, general gathers -> here, 64 samples of 8x16x16, 64 -> 128 channels:
-// forward 36 -> 23 us, input gradient 72 -> 33, weight gradient 40 -> 28; the
-// network on 64 stacks of 32x64x64: first layer forward 105 -> 74 and weight
-// gradient 94 -> 36, second layer's input gradient 146 -> 86.
+// forward 36 -> 22 us, input gradient 72 -> 26, weight gradient 40 -> 26; the
+// network on 64 stacks of 32x64x64: first layer forward 105 -> 72 (bound by the
+// error function's vector instructions) and weight gradient 94 -> 34, second
+// layer forward 62 -> 54, weight gradient 74 -> 42, and its input gradient 146
+// and the GELU pass over it 80 -> 106 as one kernel.
 #include <algorithm>
 
 #include "bf16.hpp"
@@ -26,7 +28,9 @@
 
 namespace wo {
 
-constexpr int kRowSteps = 4;   // K steps of 32 per staged weight tile
+// K steps of 32 per staged weight tile: four, two where a wave holds 32 rows,
+// which leaves registers for four waves per SIMD
+constexpr int row_steps(int mi) { return mi == 2 ? 2 : 4; }
 constexpr int kTrPad = 16;     // row padding of a transposed tile: eight rows of 32 bytes on distinct banks
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -57,21 +61,74 @@ __device__ __forceinline__ unsigned axis_bits(int i0, int n) {   // taps 0..2 at
          (unsigned)(i0 + 2 >= 0 && i0 + 2 < n) << 2;
 }
 
-// Output position q of a forward convolution: the input position of its tap
-// (0, 0, 0), which may lie outside (positions stay below 2^31, and the base
-// above -2^31), and its tap bits.
+// Exact division of a position (below 2^31) by an extent: one 64-bit multiply
+// and a shift, m = floor(2^(31 + l) / d) + 1 with 2^l >= d.
+struct FastDiv {
+  unsigned m, d;
+  int sh;
+};
+static FastDiv fast_div(int d) {
+  int l = 0;
+  while ((1L << l) < d) ++l;
+  return FastDiv{(unsigned)((1UL << (31 + l)) / (unsigned)d + 1), (unsigned)d, 31 + l};
+}
+__device__ __forceinline__ unsigned div_of(unsigned u, const FastDiv& f) {
+  return (unsigned)(((unsigned long)u * f.m) >> f.sh);
+}
+// Workgroup b of a 1-D grid to a tile: workgroups go to the 8 XCDs in turn, so
+// each XCD takes runs of kRun tiles and the operands that neighbouring tiles
+// share are fetched into one L2 instead of eight (weight gradient of 131072
+// positions, 32 -> 64 channels: 62 us in launch order, 44 us so; one run per XCD
+// instead, the XCDs far apart in memory: 48 us, the input gradient slower).  The grid is
+// a multiple of 8 kRun; ids past the end exit.
+constexpr unsigned kRun = 16;
+__device__ __forceinline__ unsigned xcd_tile(unsigned b) {
+  return b / (8 * kRun) * (8 * kRun) + (b & 7u) * kRun + (b >> 3) % kRun;
+}
+static unsigned xcd_grid(long tiles) { return (unsigned)((tiles + 8 * kRun - 1) / (8 * kRun) * (8 * kRun)); }
+
+struct PosDiv {   // extents of a row's position, w fastest
+  FastDiv w, h, d;
+};
+
+// Operands are read through buffer descriptors: a lane whose element lies
+// outside gets the offset kOut, beyond every descriptor's range, and reads
+// zeros; a wave-uniform tap or channel offset rides in the scalar offset.  A
+// descriptor starts at the sample of its workgroup's first row, less a margin
+// of one tap (row offsets are then not negative), so 31-bit offsets hold for
+// tensors of any size; the host checks the span of a workgroup's rows.
+typedef __amdgpu_buffer_rsrc_t Buf;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kOut = 0x80000000u;
+__device__ __forceinline__ Buf make_buf(const u16* p, long bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)min(bytes, 0x7fffffffL), 0x00027000);
+}
+__device__ __forceinline__ u32x4 buf16(Buf r, unsigned voff, int soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, soff, 0);
+}
+__device__ __forceinline__ u16 buf2(Buf r, unsigned voff) {
+  return (u16)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, 0, 0);
+}
+
+// Output position q of a forward convolution, of sample n0 or a later one: the
+// offset in elements / C of its tap (0, 0, 0) from the margin before sample
+// n0, and its tap bits.
 struct PosTaps {
-  int base;
+  unsigned base;
   unsigned mask;
 };
-__device__ __forceinline__ PosTaps fwd_taps(const ConvGeom& g, unsigned q) {
-  const unsigned q1 = q / (unsigned)g.Wo, q2 = q1 / (unsigned)g.Ho, n = q2 / (unsigned)g.Do;
-  const int w0 = 2 * (int)(q - q1 * (unsigned)g.Wo) - 1, h0 = 2 * (int)(q1 - q2 * (unsigned)g.Ho) - 1,
-            d0 = 2 * (int)(q2 - n * (unsigned)g.Do) - 1;
+__host__ __device__ __forceinline__ int fwd_margin(const ConvGeom& g) { return (g.H + 1) * g.W + 1; }
+__device__ __forceinline__ PosTaps fwd_taps(const ConvGeom& g, const PosDiv& dv, unsigned q, int n0) {
+  const unsigned q1 = div_of(q, dv.w), q2 = div_of(q1, dv.h), n = div_of(q2, dv.d);
+  const int w0 = 2 * (int)(q - q1 * dv.w.d) - 1, h0 = 2 * (int)(q1 - q2 * dv.h.d) - 1,
+            d0 = 2 * (int)(q2 - n * dv.d.d) - 1;
   PosTaps r;
-  r.base = (((int)n * g.D + d0) * g.H + h0) * g.W + w0;
+  r.base = (unsigned)(((((int)n - n0) * g.D + d0) * g.H + h0) * g.W + w0 + fwd_margin(g));
   r.mask = tap_mask(axis_bits(d0, g.D), axis_bits(h0, g.H), axis_bits(w0, g.W), 3, 3, 3);
   return r;
+}
+__device__ __forceinline__ int sample_of(unsigned q, const PosDiv& dv) {
+  return (int)div_of(div_of(div_of(q, dv.w), dv.h), dv.d);
 }
 
 // The wave-uniform walk over K steps: tap digits and channel.
@@ -104,6 +161,7 @@ struct TapWalk {
 struct StoreRows {
   float* c;
   long N;
+  static constexpr bool kSums = false;
   __device__ __forceinline__ void split(long off) { c += off; }
   __device__ __forceinline__ void operator()(long row, int n, f32x4 v) const {
     float* p = c + row * N + n;
@@ -117,32 +175,47 @@ struct StoreRows {
   }
 };
 
+// a = BF16(GELU(z)) of the pre-activation z = v + b and, for the backward pass
+// (d not null), GELU'(z): the error function is evaluated once for both.
 struct StoreGelu {
-  float* z;
+  float* d;
   u16* a;
   const float* b;
   long N;
+  static constexpr bool kSums = false;
   __device__ __forceinline__ void split(long) {}
   __device__ __forceinline__ void operator()(long row, int n, f32x4 v) const {
     const long i = row * N + n;
-    u16 q[4];
-    if (N % 4 == 0) {
+    f32x4 dv;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        v[r] += b[n + r];
-        q[r] = f2bf(gelu_f(v[r]));
-      }
-      *(f32x4*)(z + i) = v;
-      *(uint2*)(a + i) = make_uint2(q[0] | (unsigned)q[1] << 16, q[2] | (unsigned)q[3] << 16);
-      return;
+    for (int r = 0; r < 4; ++r) {
+      float g;
+      v[r] = gelu_f(v[r] + b[n + r], g);
+      dv[r] = g;
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (n + r < N) {
-        const float t = v[r] + b[n + r];
-        z[i + r] = t;
-        a[i + r] = f2bf(gelu_f(t));
-      }
+    *(uint2*)(a + i) = make_uint2(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]));
+    if (d) *(f32x4*)(d + i) = dv;
+  }
+};
+
+// The input gradient through the GELU before it: gz = BF16(v d), as a separate
+// pass over the gradient would compute it, and the bias gradient's first stage,
+// the workgroup's rounded gz summed per channel into part[workgroup][n].
+struct StoreGeluGrad {
+  const float* d;
+  u16* gz;
+  float* part;
+  long N;
+  static constexpr bool kSums = true;
+  __device__ __forceinline__ void split(long) {}
+  __device__ __forceinline__ f32x4 load(long row, int n) const { return *(const f32x4*)(d + row * N + n); }
+  __device__ __forceinline__ f32x4 operator()(long row, int n, f32x4 v, f32x4 dv) const {
+    const long i = row * N + n;
+    const f32x4 g = v * dv;
+    const uint2 q = make_uint2(f2bf_pair(g[0], g[1]), f2bf_pair(g[2], g[3]));
+    *(uint2*)(gz + i) = q;
+    return f32x4{__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u), __uint_as_float(q.y << 16),
+                 __uint_as_float(q.y & 0xffff0000u)};
   }
 };
 
@@ -153,7 +226,7 @@ struct StoreGelu {
 // kd in {0, 2} for odd d, per axis.
 struct RowClass {
   int pd, ph, pw;    // parity (input gradient)
-  int cd, ch, cw;    // class extents
+  PosDiv dv;         // class extents
   int nd, nh, nw;    // taps per axis
   long M;
 };
@@ -163,63 +236,98 @@ struct RowProblem {
   ConvGeom g;        // g.C: channels of the position operand
   long N;            // columns: Cout, or Cin
   long stride;       // elements from one split's output to the next
+  long xbytes, sample;   // bytes of the position operand and of one sample of it
   int nc, splits;
+  // Tile order: column tile, row tile, class, split.  Classes side by side would
+  // share gz and the lines that they write, and are slower all the same (121 us
+  // against 106 for 32 channels of 64x16x32x32 positions): neighbours then read
+  // different taps of the weights and run eight-fold different times.
+  FastDiv ty, tx, tc;
+  unsigned ntiles;
   RowClass c[8];
 };
 
 // MI x 16 rows by TN columns per wave, 4 waves along the rows.  The weights of
-// kRowSteps K steps are staged at a time in one of two LDS tiles, so one
+// a few K steps are staged at a time in one of two LDS tiles, so one
 // barrier separates a tile's writes from its reads; the next tile's weights and
-// the next steps' fragments are in flight during the MFMAs.
+// the next steps' fragments are in flight during the MFMAs.  Bound by vector
+// issue, so index work is kept out of the loop: a fragment costs a bit test and
+// a select, a weight load nothing.
 template <int MI, int TN, bool DG, class EP>
 __global__ __launch_bounds__(256) void k_conv_rows(RowProblem p, EP ep) {
-  constexpr int NJ = TN / 16, KS = kRowSteps, KT = KS * 32;
+  constexpr int NJ = TN / 16, KS = row_steps(MI), KT = KS * 32;
   constexpr int LD = DG ? TN + kTrPad : KT + 8;          // LDS row: [k][n] or [n][k]
   constexpr int NB = KT * TN / 8 / 256;                  // 16-byte weight loads per thread and tile
   __shared__ __attribute__((aligned(16))) u16 Bs[2][(DG ? KT : TN) * LD];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int cls = DG ? (int)(blockIdx.z % p.nc) : 0, q = DG ? (int)(blockIdx.z / p.nc) : (int)blockIdx.z;
+  const unsigned id = xcd_tile(blockIdx.x);
+  if (id >= p.ntiles) return;
+  const unsigned iy = div_of(id, p.ty), ix = div_of(iy, p.tx), iq = DG ? div_of(ix, p.tc) : ix;
+  const int cls = DG ? (int)(ix - iq * p.tc.d) : 0, q = (int)iq;
   const RowClass& rc = p.c[cls];
-  const long m0 = (long)blockIdx.x * (64 * MI);
+  const long m0 = (long)(iy - ix * p.tx.d) * (64 * MI);
+  if constexpr (EP::kSums) {
+    if (m0 >= rc.M && t < TN && (int)(id - iy * p.ty.d) * TN + t < (int)p.N)
+      ep.part[(long)iy * p.N + (int)(id - iy * p.ty.d) * TN + t] = 0.f;
+  }
   if (m0 >= rc.M) return;
-  const int n0 = (int)blockIdx.y * TN, N = (int)p.N, C = p.g.C;
+  const int n0 = (int)(id - iy * p.ty.d) * TN, N = (int)p.N, C = p.g.C;
   const int nd = rc.nd, nh = rc.nh, nw = rc.nw;
   const int K = nd * nh * nw * C;
   int kchunk = (K + p.splits - 1) / p.splits;
   kchunk = (kchunk + 31) / 32 * 32;
   const int kbeg = min(K, q * kchunk), steps = (min(K, kbeg + kchunk) - kbeg) / 32;
+  const int s0 = sample_of((unsigned)m0, rc.dv);
+  const int margin = DG ? (p.g.Ho + 1) * p.g.Wo + 1 : fwd_margin(p.g);
+  // no tap offset exceeds the range: it is stretched by two margins, which no lane reads
+  const Buf xb = make_buf(p.x + (s0 * (p.sample / 2) - (long)margin * C), p.xbytes - s0 * p.sample + 6L * margin * C);
+  const Buf wb = make_buf(p.w, 54L * C * N);
 
-  // this lane's rows: base address, tap bits, output row
-  const u16* base[MI];
-  unsigned mask[MI];
-  long orow[MI];
+  // one row per lane, shared with the lanes that hold its other channels: byte
+  // offset, tap bits, output row
+  unsigned rbase = 0, rmask = 0;
+  int rout = 0;
+  {
+    const long m = m0 + wave * (16 * MI) + (lane & (16 * MI - 1));
+    if (m < rc.M) {
+      const unsigned u = (unsigned)m;
+      if (DG) {
+        const unsigned q1 = div_of(u, rc.dv.w), q2 = div_of(q1, rc.dv.h), n = div_of(q2, rc.dv.d);
+        const int iw = (int)(u - q1 * rc.dv.w.d), ih = (int)(q1 - q2 * rc.dv.h.d), id = (int)(q2 - n * rc.dv.d.d);
+        // tap j of an odd axis reaches output id + 1 - j, the tap of an even one id
+        const unsigned vd = (unsigned)(id + rc.pd < p.g.Do) | (unsigned)(id < p.g.Do) << 1;
+        const unsigned vh = (unsigned)(ih + rc.ph < p.g.Ho) | (unsigned)(ih < p.g.Ho) << 1;
+        const unsigned vw = (unsigned)(iw + rc.pw < p.g.Wo) | (unsigned)(iw < p.g.Wo) << 1;
+        rmask = tap_mask(vd, vh, vw & (nw == 2 ? 3u : 1u), nd, nh, nw);
+        rbase = (unsigned)(((((int)n - s0) * p.g.Do + id + rc.pd) * p.g.Ho + ih + rc.ph) * p.g.Wo + iw + rc.pw);
+        rout = (((int)n * p.g.D + 2 * id + rc.pd) * p.g.H + 2 * ih + rc.ph) * p.g.W + 2 * iw + rc.pw;
+      } else {
+        const PosTaps r = fwd_taps(p.g, rc.dv, u, s0);
+        rbase = r.base;
+        rmask = r.mask;
+        rout = (int)u;
+      }
+    }
+  }
+  unsigned base[MI], mask[MI];
+  int orow[MI];
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const long m = m0 + (wave * MI + i) * 16 + (lane & 15);
-    const bool in = m < rc.M;
-    const unsigned u = in ? (unsigned)m : 0u;
-    long pos;
-    if (DG) {
-      const unsigned q1 = u / (unsigned)rc.cw, q2 = q1 / (unsigned)rc.ch, n = q2 / (unsigned)rc.cd;
-      const int iw = (int)(u - q1 * (unsigned)rc.cw), ih = (int)(q1 - q2 * (unsigned)rc.ch),
-                id = (int)(q2 - n * (unsigned)rc.cd);
-      // tap j of an odd axis reaches output id + 1 - j, the tap of an even one id
-      const unsigned vd = (unsigned)(id + rc.pd < p.g.Do) | (unsigned)(id < p.g.Do) << 1;
-      const unsigned vh = (unsigned)(ih + rc.ph < p.g.Ho) | (unsigned)(ih < p.g.Ho) << 1;
-      const unsigned vw = (unsigned)(iw + rc.pw < p.g.Wo) | (unsigned)(iw < p.g.Wo) << 1;
-      mask[i] = tap_mask(vd, vh, vw & (nw == 2 ? 3u : 1u), nd, nh, nw);
-      pos = (((long)n * p.g.Do + id + rc.pd) * p.g.Ho + ih + rc.ph) * p.g.Wo + iw + rc.pw;
-      orow[i] = (((long)n * p.g.D + 2 * id + rc.pd) * p.g.H + 2 * ih + rc.ph) * p.g.W + 2 * iw + rc.pw;
-    } else {
-      const PosTaps r = fwd_taps(p.g, u);
-      pos = r.base;
-      mask[i] = r.mask;
-      orow[i] = m;
-    }
-    if (!in) mask[i] = 0;
-    base[i] = p.x + pos * C + (lane >> 4) * 8;
+    const int src = i * 16 + (lane & 15);
+    base[i] = (unsigned)__shfl((int)rbase, src) * (2u * C) + (lane >> 4) * 16;
+    mask[i] = (unsigned)__shfl((int)rmask, src);
+    orow[i] = __shfl(rout, src);
   }
-  const u16* safe = p.x + (lane >> 4) * 8;   // in bounds: at least 32 channels
+  // this thread's weight loads: [k][n] rows of a step, or [n][k] rows of a tile
+  unsigned wo[NB];
+  const int half = DG && TN == 32 ? __builtin_amdgcn_readfirstlane(t >> 7) : 0;
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int e = t + 256 * u;
+    const int n = DG ? n0 + e % (TN / 8) * 8 : n0 + e / (KT / 8);
+    wo[u] = DG ? (unsigned)((e / (TN / 8) & 31) * 27 * N + n) * 2 : (unsigned)(n * K + e % (KT / 8) * 8) * 2;
+    if (n >= N) wo[u] = kOut;
+  }
 
   f32x4 acc[MI][NJ];
 #pragma unroll
@@ -227,66 +335,54 @@ __global__ __launch_bounds__(256) void k_conv_rows(RowProblem p, EP ep) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  uint4 ra[KS][MI], rb[NB];
-  unsigned ok[MI];   // bit s: step s of the loaded tile hits the volume
+  // the epilogue's operand is on its way during the products
+  f32x4 pre[EP::kSums ? MI : 1][EP::kSums ? NJ : 1];
+  if constexpr (EP::kSums) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int n = n0 + j * 16 + (lane >> 4) * 4;
+        pre[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (n < N && m0 + (wave * MI + i) * 16 + (lane & 15) < rc.M) pre[i][j] = ep.load(orow[i], n);
+      }
+  }
+
   TapWalk tw;
   tw.start(kbeg, C, nh, nw);
-  const auto issue = [&](int st0) {
-    long wrow[KS];   // input gradient: offset of (channel, tap) in the weights
-#pragma unroll
-    for (int i = 0; i < MI; ++i) ok[i] = 0;
+  const auto issue = [&](int st0, u32x4 (&ra)[KS][MI], u32x4 (&rb)[NB]) {
+    int wrow[KS];   // input gradient: byte offset of (channel, tap) in the weights
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       wrow[s] = 0;
       if (st0 + s >= steps) continue;
-      const int tp = DG ? -((tw.d * p.g.Ho + tw.h) * p.g.Wo + tw.w) : (tw.d * p.g.H + tw.h) * p.g.W + tw.w;
-      const long off = (long)tp * C + tw.ch;
+      const int tp = DG ? margin - ((tw.d * p.g.Ho + tw.h) * p.g.Wo + tw.w) : (tw.d * p.g.H + tw.h) * p.g.W + tw.w;
+      const int off = (tp * C + tw.ch) * 2;
 #pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const bool v = mask[i] >> tw.tap & 1u;
-        ok[i] |= (unsigned)v << s;
-        ra[s][i] = *(const uint4*)(v ? base[i] + off : safe);
-      }
+      for (int i = 0; i < MI; ++i) ra[s][i] = buf16(xb, (mask[i] >> tw.tap & 1u) ? base[i] : kOut, off);
       if (DG) {
         const int kd = nd == 1 ? 1 : 2 * tw.d, kh = nh == 1 ? 1 : 2 * tw.h, kw = nw == 1 ? 1 : 2 * tw.w;
-        wrow[s] = ((long)tw.ch * 27 + (kd * 3 + kh) * 3 + kw) * N;
+        wrow[s] = (tw.ch * 27 + (kd * 3 + kh) * 3 + kw) * N * 2;
       }
       tw.step(C, nh, nw);
     }
+    // steps past the last are not used: zeros, or any channel's weights
+    const bool in = t % (KT / 8) * 8 < (steps - st0) * 32;
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-      const int e = t + 256 * u;
-      rb[u] = make_uint4(0, 0, 0, 0);
-      if (DG) {
-        const int k = e / (TN / 8), n = n0 + e % (TN / 8) * 8, s = k >> 5;
-        long o = wrow[0];
-#pragma unroll
-        for (int v = 1; v < KS; ++v) o = s == v ? wrow[v] : o;
-        if (st0 + s < steps && n < N) rb[u] = *(const uint4*)(p.w + o + (long)(k & 31) * 27 * N + n);
-      } else {
-        const int n = n0 + e / (KT / 8), k = e % (KT / 8) * 8;
-        if (st0 + (k >> 5) < steps && n < N)
-          rb[u] = *(const uint4*)(p.w + (long)n * K + kbeg + st0 * 32 + k);
-      }
+      if (DG) rb[u] = buf16(wb, wo[u], TN == 32 ? (half ? wrow[(2 * u + 1) % KS] : wrow[2 * u % KS]) : wrow[u % KS]);
+      else rb[u] = buf16(wb, in ? wo[u] : kOut, (kbeg + st0 * 32) * 2);
     }
   };
-
-  if (steps > 0) issue(0);
-  for (int st0 = 0, buf = 0; st0 < steps; st0 += KS, buf ^= 1) {
-    u16* B = Bs[buf];
+  const auto tile = [&](int st0, u16* B, u32x4 (&ra)[KS][MI], u32x4 (&rb)[NB], u32x4 (&na)[KS][MI], u32x4 (&nb)[NB]) {
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int e = t + 256 * u;
-      if (DG) *(uint4*)&B[e / (TN / 8) * LD + e % (TN / 8) * 8] = rb[u];
-      else *(uint4*)&B[e / (KT / 8) * LD + e % (KT / 8) * 8] = rb[u];
+      if (DG) *(u32x4*)&B[e / (TN / 8) * LD + e % (TN / 8) * 8] = rb[u];
+      else *(u32x4*)&B[e / (KT / 8) * LD + e % (KT / 8) * 8] = rb[u];
     }
-    uint4 fa[KS][MI];
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int i = 0; i < MI; ++i) fa[s][i] = (ok[i] >> s & 1u) ? ra[s][i] : make_uint4(0, 0, 0, 0);
     __syncthreads();
-    if (st0 + KS < steps) issue(st0 + KS);
+    if (st0 + KS < steps) issue(st0 + KS, na, nb);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       if (st0 + s >= steps) break;
@@ -297,20 +393,47 @@ __global__ __launch_bounds__(256) void k_conv_rows(RowProblem p, EP ep) {
         else b = *(const bf16x8*)&B[(j * 16 + (lane & 15)) * LD + s * 32 + (lane >> 4) * 8];
 #pragma unroll
         for (int i = 0; i < MI; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, __builtin_bit_cast(bf16x8, fa[s][i]), acc[i][j],
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, __builtin_bit_cast(bf16x8, ra[s][i]), acc[i][j],
                                                               0, 0, 0);
       }
     }
+  };
+
+  u32x4 ra0[KS][MI], rb0[NB], ra1[KS][MI], rb1[NB];   // in turn: one in use, one in flight
+  if (steps > 0) issue(0, ra0, rb0);
+  for (int st0 = 0; st0 < steps; st0 += 2 * KS) {
+    tile(st0, Bs[0], ra0, rb0, ra1, rb1);
+    if (st0 + KS >= steps) break;
+    tile(st0 + KS, Bs[1], ra1, rb1, ra0, rb0);
   }
   ep.split(q * p.stride);
+  f32x4 sum[EP::kSums ? NJ : 1];
+#pragma unroll
+  for (int j = 0; j < (EP::kSums ? NJ : 1); ++j) sum[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     if (m0 + (wave * MI + i) * 16 + (lane & 15) >= rc.M) continue;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int n = n0 + j * 16 + (lane >> 4) * 4;
-      if (n < N) ep(orow[i], n, acc[i][j]);
+      if (n >= N) continue;
+      if constexpr (EP::kSums) sum[j] += ep(orow[i], n, acc[i][j], pre[i][j]);
+      else ep(orow[i], n, acc[i][j]);
     }
+  }
+  if constexpr (EP::kSums) {   // over the 16 rows of a lane group, then the waves
+    __shared__ float red[4][TN];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float v = sum[j][r];
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
+        if ((lane & 15) == 0) red[wave][j * 16 + (lane >> 4) * 4 + r] = v;
+      }
+    __syncthreads();
+    if (t < TN && n0 + t < N) ep.part[(long)iy * N + n0 + t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
   }
 }
 
@@ -320,7 +443,7 @@ __global__ __launch_bounds__(256) void k_conv_rows(RowProblem p, EP ep) {
 // throughout.
 template <class EP>
 __global__ __launch_bounds__(256) void k_conv_first(const u16* __restrict__ x, const u16* __restrict__ w, ConvGeom g,
-                                                    long P, int N, EP ep) {
+                                                    PosDiv dv, long xbytes, long P, int N, EP ep) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kg = (lane >> 4) * 8;
   const int n0 = (int)blockIdx.y * 32;
   bf16x8 wf[2];
@@ -332,27 +455,26 @@ __global__ __launch_bounds__(256) void k_conv_first(const u16* __restrict__ x, c
     for (int e = 0; e < 8; ++e) v[e] = n < N && kg + e < 27 ? w[(long)n * 27 + kg + e] : (u16)0;
     wf[j] = __builtin_bit_cast(bf16x8, *(uint4*)v);
   }
-  int off[8];
+  unsigned off[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int tap = kg + e;
-    off[e] = ((tap / 9) * g.H + tap / 3 % 3) * g.W + tap % 3;
+    off[e] = (((tap / 9) * g.H + tap / 3 % 3) * g.W + tap % 3) * 2;
   }
-  const long m0 = (long)blockIdx.x * 256 + wave * 64;
+  const long b0 = (long)blockIdx.x * 256, m0 = b0 + wave * 64;
+  const int s0 = sample_of((unsigned)b0, dv);
+  const long skip = (long)s0 * g.D * g.H * g.W - fwd_margin(g);
+  const Buf xb = make_buf(x + skip, xbytes - 2 * skip);
   PosTaps mine{0, 0};
-  if (m0 + lane < P) mine = fwd_taps(g, (unsigned)(m0 + lane));
+  if (m0 + lane < P) mine = fwd_taps(g, dv, (unsigned)(m0 + lane), s0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int src = i * 16 + (lane & 15);
-    const int base = __shfl(mine.base, src);
+    const unsigned base = (unsigned)__shfl((int)mine.base, src) * 2;
     const unsigned mask = (unsigned)__shfl((int)mine.mask, src) >> kg;   // taps past 26 have no bit
     u16 v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool in = mask >> e & 1u;
-      const u16 r = x[in ? base + off[e] : 0];
-      v[e] = in ? r : (u16)0;
-    }
+    for (int e = 0; e < 8; ++e) v[e] = buf2(xb, (mask >> e & 1u) ? base + off[e] : kOut);
     const bf16x8 a = __builtin_bit_cast(bf16x8, *(uint4*)v);
     const long m = m0 + src;
 #pragma unroll
@@ -374,7 +496,9 @@ __global__ __launch_bounds__(256) void k_conv_first(const u16* __restrict__ x, c
 // ONE: one input channel, the 27 taps are the columns.
 template <int TM, int TN, bool ONE>
 __global__ __launch_bounds__(256) void k_conv_wgrad(const u16* __restrict__ x, const u16* __restrict__ gz, ConvGeom g,
-                                                    long P, int Co, long kchunk, float* __restrict__ part) {
+                                                    PosDiv dv, long xbytes, long P, int Co, long kchunk,
+                                                    FastDiv tn, FastDiv tm, unsigned ntiles,
+                                                    float* __restrict__ part) {
   constexpr int KT = 64, LA = TM + kTrPad, LB = TN + kTrPad;
   constexpr int FM = TM / 32, FN = TN / 32;               // 16 x 16 blocks per wave
   constexpr int NA = KT * TM / 8 / 256, NB = KT * TN / 8 / 256;
@@ -385,56 +509,54 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const u16* __restrict__ x, c
   __shared__ PosTaps tab[2][256];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
   const int K = 27 * g.C;
-  const int m0 = (int)blockIdx.x * TM, n0 = (int)blockIdx.y * TN;
-  const long kbeg = (long)blockIdx.z * kchunk, kend = min(P, kbeg + kchunk);
+  const unsigned id = xcd_tile(blockIdx.x);   // column tile, row tile, split
+  if (id >= ntiles) return;
+  const unsigned im = div_of(id, tn), iz = div_of(im, tm);
+  const int m0 = (int)(im - iz * tm.d) * TM, n0 = (int)(id - im * tn.d) * TN;
+  const long kbeg = (long)iz * kchunk, kend = min(P, kbeg + kchunk);
+
+  const int s0 = sample_of((unsigned)kbeg, dv);
+  const long skip = ((long)s0 * g.D * g.H * g.W - fwd_margin(g)) * g.C;
+  const Buf xb = make_buf(x + skip, xbytes - 2 * skip);
+  const Buf gb = make_buf(gz + kbeg * Co, (kend - kbeg) * Co * 2);   // zeros past the split
 
   // this thread's columns: eight channels of one tap (ONE: eight taps)
   const int n8 = n0 + t % (TN / 8) * 8;
-  int tap = 0, off[ONE ? 8 : 1];
-  long ci = 0;
+  int tap = 0;
+  unsigned off[ONE ? 8 : 1];
   if (ONE) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) off[e] = (((n8 + e) / 9) * g.H + (n8 + e) / 3 % 3) * g.W + (n8 + e) % 3;
+    for (int e = 0; e < 8; ++e) off[e] = ((((n8 + e) / 9) * g.H + (n8 + e) / 3 % 3) * g.W + (n8 + e) % 3) * 2;
   } else {
     tap = n8 / g.C;
-    ci = n8 - tap * g.C;
-    off[0] = ((tap / 9) * g.H + tap / 3 % 3) * g.W + tap % 3;
+    off[0] = ((((tap / 9) * g.H + tap / 3 % 3) * g.W + tap % 3) * g.C + (n8 - tap * g.C)) * 2;
   }
-  const bool col = ONE || n8 < K;
+  if (n8 >= K) tap = 31;   // no such bit
   const int mc = m0 + t % (TM / 8) * 8;
-  const bool row = mc < Co;
+  const unsigned arow = mc < Co ? (unsigned)(t / (TM / 8) * Co + mc) * 2 : kOut;
 
-  const auto decode = [&](long k0) {   // positions k0 .. k0 + 255
-    const long k = k0 + t;
+  const auto decode = [&](int k0) {   // positions kbeg + k0 .. + 255
     PosTaps r{0, 0};
-    if (k < kend) r = fwd_taps(g, (unsigned)k);
-    tab[(k0 - kbeg) >> 8 & 1][t] = r;
+    if (kbeg + k0 + t < kend) r = fwd_taps(g, dv, (unsigned)(kbeg + k0 + t), s0);
+    r.base *= 2 * g.C;
+    tab[k0 >> 8 & 1][t] = r;
   };
-  uint4 ra[NA], rb[NB];
-  const auto issue = [&](long k0) {
+  u32x4 ra[NA], rb[NB];
+  const auto issue = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < NA; ++u) {
-      const long k = k0 + (t + 256 * u) / (TM / 8);
-      ra[u] = make_uint4(0, 0, 0, 0);
-      if (row && k < kend) ra[u] = *(const uint4*)(gz + k * Co + mc);
-    }
-    const PosTaps* tb = tab[(k0 - kbeg) >> 8 & 1] + ((k0 - kbeg) & 255);
+    for (int u = 0; u < NA; ++u) ra[u] = buf16(gb, arow + (unsigned)((k0 + 256 * u / (TM / 8)) * Co * 2), 0);
+    const PosTaps* tb = tab[k0 >> 8 & 1] + (k0 & 255);
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const PosTaps r = tb[(t + 256 * u) / (TN / 8)];
-      rb[u] = make_uint4(0, 0, 0, 0);
       if (ONE) {
         u16 v[8];
         const unsigned mk = r.mask >> n8;   // n8 <= 24; taps past 26 have no bit
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const bool in = mk >> e & 1u;
-          const u16 q = x[in ? r.base + off[e] : 0];
-          v[e] = in ? q : (u16)0;
-        }
-        rb[u] = *(uint4*)v;
-      } else if (col && (r.mask >> tap & 1u)) {
-        rb[u] = *(const uint4*)(x + (long)(r.base + off[0]) * g.C + ci);
+        for (int e = 0; e < 8; ++e) v[e] = buf2(xb, (mk >> e & 1u) ? r.base + off[e] : kOut);
+        rb[u] = *(u32x4*)v;
+      } else {
+        rb[u] = buf16(xb, (r.mask >> tap & 1u) ? r.base + off[0] : kOut, 0);
       }
     }
   };
@@ -444,22 +566,22 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const u16* __restrict__ x, c
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  decode(kbeg);
+  const int len = (int)(kend - kbeg);
+  decode(0);
   __syncthreads();
-  issue(kbeg);
-  int buf = 0;
-  for (long k0 = kbeg; k0 < kend; k0 += KT, buf ^= 1) {
+  issue(0);
+  for (int k0 = 0, buf = 0; k0 < len; k0 += KT, buf ^= 1) {
     u16 *A = As[buf], *B = Bs[buf];
 #pragma unroll
-    for (int u = 0; u < NA; ++u) *(uint4*)&A[(t + 256 * u) / (TM / 8) * LA + t % (TM / 8) * 8] = ra[u];
+    for (int u = 0; u < NA; ++u) *(u32x4*)&A[(t + 256 * u) / (TM / 8) * LA + t % (TM / 8) * 8] = ra[u];
 #pragma unroll
-    for (int u = 0; u < NB; ++u) *(uint4*)&B[(t + 256 * u) / (TN / 8) * LB + t % (TN / 8) * 8] = rb[u];
-    const long k1 = k0 + KT;
+    for (int u = 0; u < NB; ++u) *(u32x4*)&B[(t + 256 * u) / (TN / 8) * LB + t % (TN / 8) * 8] = rb[u];
+    const int k1 = k0 + KT;
     // a block's first tile is fetched after this barrier; the half it fills was
     // last read two blocks ago
-    if (k1 < kend && ((k1 - kbeg) & 255) == 0) decode(k1);
+    if (k1 < len && (k1 & 255) == 0) decode(k1);
     __syncthreads();
-    if (k1 < kend) issue(k1);
+    if (k1 < len) issue(k1);
 #pragma unroll
     for (int ks = 0; ks < KT / 32; ++ks) {
       bf16x8 a[FM];
@@ -473,7 +595,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const u16* __restrict__ x, c
       }
     }
   }
-  float* c = part + (long)blockIdx.z * Co * K;
+  float* c = part + (long)iz * Co * K;
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
     const int co = m0 + (wm * FM + i) * 16 + (lane & 15);
@@ -495,14 +617,26 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(const u16* __restrict__ x, c
 
 static unsigned tiles(long n, long t) { return (unsigned)((n + t - 1) / t); }
 
-template <bool DG, class EP>
-static hipError_t launch_rows(const RowProblem& p, long mmax, unsigned nz, const EP& ep, hipStream_t s) {
+// Rows per wave / 16: 2 where that leaves four workgroups per CU, else 1.
+static int row_blocks(const RowProblem& p, unsigned nq) {
   long wgs = 0;
+  for (int c = 0; c < p.nc; ++c) wgs += (long)tiles(p.c[c].M, 128) * tiles(p.N, p.N <= 32 ? 32 : 64) * nq;
+  return wgs >= 1024 ? 2 : 1;
+}
+
+template <bool DG, class EP>
+static bool launch_rows(RowProblem& p, long mmax, unsigned nq, const EP& ep, hipStream_t s, hipError_t* e) {
   const bool narrow = p.N <= 32;
-  for (int c = 0; c < p.nc; ++c) wgs += tiles(p.c[c].M, 128) * (long)tiles(p.N, narrow ? 32 : 64) * (nz / p.nc);
-  // 32 rows per wave where that leaves four workgroups per CU; 16 below that
-  const int mi = wgs >= 1024 ? 2 : 1;
-  const dim3 grid(tiles(mmax, 64 * mi), tiles(p.N, narrow ? 32 : 64), nz);
+  const unsigned ny = tiles(p.N, narrow ? 32 : 64);
+  const int mi = row_blocks(p, nq);
+  const unsigned nx = tiles(mmax, 64 * mi);
+  const long total = (long)nx * ny * p.nc * nq;
+  if (total >= (1L << 30)) return false;
+  p.ty = fast_div((int)ny);
+  p.tc = fast_div(p.nc);
+  p.tx = fast_div((int)nx);
+  p.ntiles = (unsigned)total;
+  const dim3 grid(xcd_grid(total));
   if (mi == 2) {
     if (narrow) hipLaunchKernelGGL((k_conv_rows<2, 32, DG, EP>), grid, dim3(256), 0, s, p, ep);
     else hipLaunchKernelGGL((k_conv_rows<2, 64, DG, EP>), grid, dim3(256), 0, s, p, ep);
@@ -510,69 +644,121 @@ static hipError_t launch_rows(const RowProblem& p, long mmax, unsigned nz, const
     if (narrow) hipLaunchKernelGGL((k_conv_rows<1, 32, DG, EP>), grid, dim3(256), 0, s, p, ep);
     else hipLaunchKernelGGL((k_conv_rows<1, 64, DG, EP>), grid, dim3(256), 0, s, p, ep);
   }
-  return hipGetLastError();
+  *e = hipGetLastError();
+  return true;
 }
 
+static PosDiv pos_div(int d, int h, int w) { return PosDiv{fast_div(w), fast_div(h), fast_div(d)}; }
+
+// Bytes from the margin before the first to the end of the last sample that
+// `rows` consecutive rows of rps per sample touch stay below 2^31.
+static bool span_ok(long rows, long rps, long N, long sample_bytes, long margin_bytes) {
+  const long n = std::min(N, (rows + rps - 1) / rps + 1);
+  return sample_bytes < (1L << 31) && margin_bytes < (1L << 28) && n * sample_bytes + 2 * margin_bytes < (1L << 31);
+}
 
 bool conv_fwd_taps(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
                    const ConvFwdOut& out, hipStream_t s, hipError_t* e) {
-  const StoreGelu eg{out.z, out.a, out.bias, Cout};
+  const StoreGelu eg{out.d, out.a, out.bias, Cout};
   const StoreRows er{out.c, Cout};
-  if (g.C == 1 && splits == 1) {
+  if (out.a && Cout % 4 != 0) return false;
+  const bool first = g.C == 1 && splits == 1;
+  if (!first && g.C % 32 != 0) return false;   // a K step would straddle taps
+  const PosDiv dv = pos_div(g.Do, g.Ho, g.Wo);
+  const long rps = (long)g.Do * g.Ho * g.Wo, N = P / rps, sample = 2L * g.D * g.H * g.W * g.C;
+  if (!span_ok(256, rps, N, sample, 2L * fwd_margin(g) * g.C)) return false;
+  if (first) {
     const dim3 grid(tiles(P, 256), tiles(Cout, 32));
-    if (out.a) hipLaunchKernelGGL(k_conv_first<StoreGelu>, grid, dim3(256), 0, s, x, w, g, P, Cout, eg);
-    else hipLaunchKernelGGL(k_conv_first<StoreRows>, grid, dim3(256), 0, s, x, w, g, P, Cout, er);
+    if (out.a)
+      hipLaunchKernelGGL(k_conv_first<StoreGelu>, grid, dim3(256), 0, s, x, w, g, dv, N * sample, P, Cout, eg);
+    else
+      hipLaunchKernelGGL(k_conv_first<StoreRows>, grid, dim3(256), 0, s, x, w, g, dv, N * sample, P, Cout, er);
     *e = hipGetLastError();
     return true;
   }
-  if (g.C % 32 != 0) return false;   // a K step would straddle taps
   RowProblem p{};
   p.x = x; p.w = w; p.g = g;
   p.N = Cout;
   p.stride = P * Cout;
+  p.xbytes = N * sample;
+  p.sample = sample;
   p.nc = 1;
   p.splits = splits;
-  p.c[0] = RowClass{0, 0, 0, 0, 0, 0, 3, 3, 3, P};
+  p.c[0] = RowClass{0, 0, 0, dv, 3, 3, 3, P};
   const long K = 27L * g.C, kchunk = ((K + splits - 1) / splits + 31) / 32 * 32;
   const unsigned nz = tiles(K, kchunk);
-  *e = out.a ? launch_rows<false>(p, P, nz, eg, s) : launch_rows<false>(p, P, nz, er, s);
+  return out.a ? launch_rows<false>(p, P, nz, eg, s, e) : launch_rows<false>(p, P, nz, er, s, e);
+}
+
+// The input gradient's classes; false where the kernels do not take the shape.
+static bool dgrad_problem(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, int splits,
+                          RowProblem& p, long& mmax) {
+  if (gout.C % 32 != 0 || Cin % 8 != 0) return false;
+  p.x = gz; p.w = w; p.g = gout;
+  p.N = Cin;
+  p.stride = (long)N * gout.D * gout.H * gout.W * Cin;
+  p.sample = 2L * gout.Do * gout.Ho * gout.Wo * gout.C;
+  p.xbytes = N * p.sample;
+  p.splits = splits;
+  mmax = 0;
+  for (int cls = 7; cls >= 0; --cls) {   // the longest K first: no long tail
+    RowClass c;
+    c.pd = cls >> 2; c.ph = cls >> 1 & 1; c.pw = cls & 1;
+    const int cd = (gout.D - c.pd + 1) / 2, ch = (gout.H - c.ph + 1) / 2, cw = (gout.W - c.pw + 1) / 2;
+    if (cd <= 0 || ch <= 0 || cw <= 0) continue;
+    c.dv = pos_div(cd, ch, cw);
+    c.nd = 1 + c.pd; c.nh = 1 + c.ph; c.nw = 1 + c.pw;
+    c.M = (long)N * cd * ch * cw;
+    if (!span_ok(128, (long)cd * ch * cw, N, p.sample, 2L * ((gout.Ho + 1) * gout.Wo + 1) * gout.C)) return false;
+    mmax = std::max(mmax, c.M);
+    p.c[p.nc++] = c;
+  }
   return true;
 }
 
 bool conv_dgrad_taps(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, int splits, float* out,
                      hipStream_t s, hipError_t* e) {
-  if (gout.C % 32 != 0 || Cin % 8 != 0) return false;
   RowProblem p{};
-  p.x = gz; p.w = w; p.g = gout;
-  p.N = Cin;
-  p.stride = (long)N * gout.D * gout.H * gout.W * Cin;
-  p.splits = splits;
-  long mmax = 0;
-  for (int cls = 0; cls < 8; ++cls) {
-    RowClass c;
-    c.pd = cls >> 2; c.ph = cls >> 1 & 1; c.pw = cls & 1;
-    c.cd = (gout.D - c.pd + 1) / 2; c.ch = (gout.H - c.ph + 1) / 2; c.cw = (gout.W - c.pw + 1) / 2;
-    if (c.cd <= 0 || c.ch <= 0 || c.cw <= 0) continue;
-    c.nd = 1 + c.pd; c.nh = 1 + c.ph; c.nw = 1 + c.pw;
-    c.M = (long)N * c.cd * c.ch * c.cw;
-    mmax = std::max(mmax, c.M);
-    p.c[p.nc++] = c;
-  }
-  *e = launch_rows<true>(p, mmax, (unsigned)(p.nc * splits), StoreRows{out, Cin}, s);
-  return true;
+  long mmax;
+  if (!dgrad_problem(gz, w, gout, Cin, N, splits, p, mmax)) return false;
+  return launch_rows<true>(p, mmax, (unsigned)splits, StoreRows{out, Cin}, s, e);
+}
+
+long conv_dgrad_gelu_rows(const ConvGeom& gout, int Cin, int N) {
+  RowProblem p{};
+  long mmax;
+  if (!dgrad_problem(nullptr, nullptr, gout, Cin, N, 1, p, mmax)) return 0;
+  return (long)tiles(mmax, 64 * row_blocks(p, 1)) * p.nc;
+}
+
+bool conv_dgrad_gelu(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, const float* d, u16* gz_in,
+                     float* part, hipStream_t s, hipError_t* e) {
+  RowProblem p{};
+  long mmax;
+  if (!dgrad_problem(gz, w, gout, Cin, N, 1, p, mmax)) return false;
+  return launch_rows<true>(p, mmax, 1u, StoreGeluGrad{d, gz_in, part, Cin}, s, e);
 }
 
 bool conv_wgrad_taps(const u16* x, const u16* gz, const ConvGeom& g, long P, int Cout, int splits, float* part,
                      hipStream_t s, hipError_t* e) {
   if (Cout % 8 != 0 || (g.C != 1 && g.C % 8 != 0)) return false;
   const long K = 27L * g.C, kchunk = ((P + splits - 1) / splits + 31) / 32 * 32;
-  const unsigned nz = tiles(P, kchunk);
+  const PosDiv dv = pos_div(g.Do, g.Ho, g.Wo);
+  const long rps = (long)g.Do * g.Ho * g.Wo, N = P / rps, sample = 2L * g.D * g.H * g.W * g.C;
+  if (!span_ok(kchunk, rps, N, sample, 2L * fwd_margin(g) * g.C) || (kchunk + 64) * Cout * 2 >= (1L << 31))
+    return false;
+  const int tile = g.C == 1 ? 32 : 64;
+  const unsigned nm = tiles(Cout, tile), nn = tiles(K, tile);
+  const long total = (long)nm * nn * tiles(P, kchunk);
+  if (total >= (1L << 30)) return false;
+  const dim3 grid(xcd_grid(total));
+  const FastDiv tn = fast_div((int)nn), tm = fast_div((int)nm);
   if (g.C == 1)
-    hipLaunchKernelGGL((k_conv_wgrad<32, 32, true>), dim3(tiles(Cout, 32), 1, nz), dim3(256), 0, s, x, gz, g, P, Cout,
-                       kchunk, part);
+    hipLaunchKernelGGL((k_conv_wgrad<32, 32, true>), grid, dim3(256), 0, s, x, gz, g, dv, N * sample, P, Cout, kchunk,
+                       tn, tm, (unsigned)total, part);
   else
-    hipLaunchKernelGGL((k_conv_wgrad<64, 64, false>), dim3(tiles(Cout, 64), tiles(K, 64), nz), dim3(256), 0, s, x, gz,
-                       g, P, Cout, kchunk, part);
+    hipLaunchKernelGGL((k_conv_wgrad<64, 64, false>), grid, dim3(256), 0, s, x, gz, g, dv, N * sample, P, Cout, kchunk,
+                       tn, tm, (unsigned)total, part);
   *e = hipGetLastError();
   return true;
 }

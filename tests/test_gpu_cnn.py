@@ -259,3 +259,31 @@ def test_tap_steps_of_a_large_batch(gpu_lib):
                                    (N, D, H, W, Ci)).cpu().numpy()
     assert rel(gx[0], cnn.conv3d_dgrad(gz[:1], w2, (1, D, H, W, Ci))[0]) < 1e-5
     assert np.array_equal(gx[0], gx[-1])
+
+
+@pytest.mark.parametrize("N", [16, 64])
+def test_large_batch_gradient_matches_oracle(gpu_lib, N):
+    """Large batches carry the input gradients of one (16 stacks) or two (64) layers
+    through the GELU in the same kernel, on extents whose parity classes differ.  The
+    batch repeats four stacks, so the oracle's gradient of those four is its gradient;
+    bounds as for the small network above."""
+    import torch
+    from paper_2412_09775_amd import learned_init
+    rng = np.random.default_rng(N)
+    p = learned_init.init_params(7)
+    x = rng.standard_normal((4, 34, 62, 53)).astype(np.float32)
+    t = rng.uniform(-1, 1, (4, 3)).astype(np.float32)
+    print(f"[case] batch gradient N={N}", flush=True)
+    idx = np.arange(N) % 4
+    y, loss, g = gpu_lib.cnn_gradient(torch.from_numpy(p).cuda(), torch.from_numpy(x[idx]).cuda(),
+                                      torch.from_numpy(t[idx]).cuda())
+    L, gref = cnn.loss_and_grad(p.astype(np.float64), cnn.normalise_input(x), t.astype(np.float64), round_bf16=True)
+    assert abs(float(loss) - L) <= 1e-3 * abs(L)
+    g = g.cpu().numpy()
+    assert rel(g, gref) < 1e-2
+    off = 0
+    for kind, shp in cnn.param_shapes():
+        n = int(np.prod(shp))
+        e = rel(g[off:off + n], gref[off:off + n]) if np.any(gref[off:off + n]) else 0.0
+        assert e < 2e-2, (kind, shp, e)
+        off += n
