@@ -168,8 +168,9 @@ long loss_blocks(const Sampling& sm) {
 
 // ------------------------------------------------------------------ gradient of a loss of the 3D reconstruction
 
-// One thread per 3D half-spectrum frequency (kz, m) of patch v (grid y).  bank:
-// [v][Z][2][M] the label-free pair after its Z transform (POL: the 5 x 4 bank is
+// One thread per 3D half-spectrum frequency (kz, m) of patch v (grid y), m over
+// the Y x KT plane of the kept columns; rows outside the band (KY) are left as
+// they are.  bank: [v][Z][2][M] the label-free pair after its Z transform (POL: the 5 x 4 bank is
 // pol5_entry(coupling, pair)); D: [v][C][Z][M] the data spectrum; G: [v][P][Z][M]
 // the spectrum of dL/df.  Per frequency, with x = D - N b delta,
 // M = H^H H (+ eta I), F = M^-1 H^H x, Y = M^-1 G, R = x - H F:
@@ -181,8 +182,9 @@ template <bool POL>
 __global__ __launch_bounds__(256) void k_recon_grad(float2* __restrict__ bank, float2* __restrict__ D,
                                                     const float2* __restrict__ G,
                                                     const float* __restrict__ bg,
-                                                    const Coupling* __restrict__ cpl, int Z, long M,
+                                                    const Coupling* __restrict__ cpl, int Z, int Y, int KT, int KY,
                                                     float eta, float n_full, int want_dd) {
+  const long M = (long)Y * KT;
   constexpr int C = POL ? 5 : 1, P = POL ? 4 : 2;
   const long per = (long)Z * M;
   const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -190,6 +192,8 @@ __global__ __launch_bounds__(256) void k_recon_grad(float2* __restrict__ bank, f
   if (gid >= per) return;
   const int z = (int)(gid / M);
   const long m = gid - (long)z * M;
+  const int y = (int)((unsigned)m / (unsigned)KT);
+  if (y > KY && y < Y - KY) return;
   float2* hp = bank + ((v * Z + z) * 2) * M + m;
   const float2 u = hp[0], w = hp[M];
   float2 H[C][P];
@@ -253,19 +257,19 @@ __global__ __launch_bounds__(256) void k_recon_grad(float2* __restrict__ bank, f
 }
 
 hipError_t launch_recon_grad(float2* bank, float2* D, const float2* G, const float* bg, const Coupling* cpl,
-                             const Sampling& sm, int npatch, float eta, double n_full, int want_dd,
-                             hipStream_t s) {
-  const long M = (long)sm.ny * (sm.nx / 2 + 1);
+                             const Sampling& sm, int npatch, float eta, double n_full, int want_dd, int kt,
+                             int ky, hipStream_t s) {
+  const long M = (long)sm.ny * kt;
   const long per = (long)sm.nz * M;
   const long blocks = (per + 255) / 256;
   if (npatch < 1 || npatch > 65535 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
   ScopedTiming _t("k_recon_grad", s);
   if (cpl)
     hipLaunchKernelGGL(k_recon_grad<true>, dim3((unsigned)blocks, (unsigned)npatch), dim3(256), 0, s, bank,
-                       D, G, bg, cpl, sm.nz, M, eta, (float)n_full, want_dd);
+                       D, G, bg, cpl, sm.nz, sm.ny, kt, ky, eta, (float)n_full, want_dd);
   else
     hipLaunchKernelGGL(k_recon_grad<false>, dim3((unsigned)blocks, (unsigned)npatch), dim3(256), 0, s, bank,
-                       D, G, bg, cpl, sm.nz, M, eta, (float)n_full, want_dd);
+                       D, G, bg, cpl, sm.nz, sm.ny, kt, ky, eta, (float)n_full, want_dd);
   return hipGetLastError();
 }
 

@@ -267,10 +267,11 @@ hipError_t launch_loss_grad(const TuneState* st, const Sampling& sm, const BandP
 // Gradient of a loss of the 3D reconstruction per frequency (bank [v][Z][2][M]
 // the label-free pair after its Z transform, D [v][C][Z][M] the data spectrum,
 // G [v][P][Z][M] the spectrum of dL/df; cpl: the polarisation bank): the pair
-// becomes dL/dH*, and D the spectrum of dL/dd if want_dd.
+// becomes dL/dH*, and D the spectrum of dL/dd if want_dd.  Planes of ny x kt,
+// rows y <= ky or y >= ny - ky.
 hipError_t launch_recon_grad(float2* bank, float2* D, const float2* G, const float* bg, const Coupling* cpl,
-                             const Sampling& sm, int npatch, float eta, double n_full, int want_dd,
-                             hipStream_t s);
+                             const Sampling& sm, int npatch, float eta, double n_full, int want_dd, int kt,
+                             int ky, hipStream_t s);
 // The backward kernels and Adam take the fields' compact columns (sup; NULL:
 // every column), as the field kernel wrote them; the backward rows read the
 // columns k < sup->kt of g (row pitch sup->kt).

@@ -156,3 +156,29 @@ def test_unsupported_models_are_rejected_on_the_host(gpu_lib):
     out = (ctypes.c_double * 6)()
     assert lib.wo_reconstruct_grad(arr, 1, one, None, ctypes.c_double(1e-3), one, out, None, one, 1 << 40,
                                    None) == -2
+
+
+SUPPORT_CASES = {
+    "wide_edge": labelfree(nz=6, ny=90, nx=120, edge_width=2.5, na_det=0.9, tilt_zenith=0.3, tilt_azimuth=2.4),
+    "few_columns": labelfree(nz=5, ny=80, nx=160, na_ill=0.2, na_det=0.5, tilt_zenith=0.02),
+    "pol5": pol5(nz=6, ny=108, nx=90, edge_width=1.5),
+    "oblique": labelfree(nz=6, ny=100, nx=120, na_det=0.8, det_tilt=0.3, det_azimuth=-2.0),
+}
+
+
+@pytest.mark.parametrize("name", list(SUPPORT_CASES))
+def test_gradients_on_the_lateral_support_match_the_oracle(gpu_lib, name):
+    """Supports of a part of the columns and rows (the spectra keep that part only),
+    with pupils, edges and axes that reach their bounds differently; tolerances as above."""
+    import torch
+    o = SUPPORT_CASES[name]
+    print(f"[case] reconstruct grad on the support {name}", flush=True)
+    sup = gpu_lib.lateral_support([o])
+    assert sup["tf_cols"] < o.nx // 2 + 1 and sup["band_rows"] < o.ny
+    d, w, eta = inputs([o], 300)
+    b = np.full((1, d.shape[1]), 0.1, np.float32)
+    gth, gd = gpu_lib.reconstruct_grad([o], torch.from_numpy(d).cuda(), eta, torch.from_numpy(w).cuda(),
+                                       b=torch.from_numpy(b).cuda())
+    ref_th, ref_dd = at.recon_gradient(o, d[0], eta, w[0], b=b[0])
+    assert rel_vec(gth[0], ref_th) < TOL_THETA
+    assert float(np.linalg.norm(gd.cpu().numpy()[0] - ref_dd) / np.linalg.norm(ref_dd)) < TOL_DATA
