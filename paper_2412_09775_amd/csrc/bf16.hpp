@@ -32,7 +32,8 @@ struct ConvGeom {
 };
 
 // The three convolution products on tap-sized K steps (conv.hip).  Each
-// returns false where it does not take the shape; *e is the launch's status.
+// returns false where it does not take the shape; *e is the launch's status, tag
+// its name in the timing report.
 //   forward: C_q[p][co] partials of split q, or (a, bias not null) from the
 //     pre-activation z = sum + bias the activation a = BF16(GELU(z)) and, d not
 //     null, GELU'(z), with one split
@@ -45,16 +46,16 @@ struct ConvFwdOut {
   const float* bias;
 };
 bool conv_fwd_taps(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
-                   const ConvFwdOut& out, hipStream_t s, hipError_t* e);
+                   const ConvFwdOut& out, hipStream_t s, const char* tag, hipError_t* e);
 bool conv_dgrad_taps(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, int splits, float* out,
-                     hipStream_t s, hipError_t* e);
+                     hipStream_t s, const char* tag, hipError_t* e);
 // The unsplit input gradient carried through the GELU of the layer before:
 // gz_in = BF16(gradient * d), d = GELU'(z), and its sums per workgroup and channel, part
 // (conv_dgrad_gelu_rows x Cin; 0 rows: shape not taken).
 long conv_dgrad_gelu_rows(const ConvGeom& gout, int Cin, int N);
 bool conv_dgrad_gelu(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, const float* d, u16* gz_in,
-                     float* part, hipStream_t s, hipError_t* e);
+                     float* part, hipStream_t s, const char* tag, hipError_t* e);
 bool conv_wgrad_taps(const u16* x, const u16* gz, const ConvGeom& g, long P, int Cout, int splits, float* part,
-                     hipStream_t s, hipError_t* e);
+                     hipStream_t s, const char* tag, hipError_t* e);
 
 }  // namespace wo

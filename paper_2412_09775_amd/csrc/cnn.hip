@@ -540,12 +540,7 @@ static hipError_t dgrad_classes(const u16* gz, const u16* w, ConvGeom gout, int 
   const int splits = part ? dgrad_splits(pl.tiles, pl.kmax) : 1;
   float* dst = splits > 1 ? part : out;
   hipError_t e = hipSuccess;
-  bool taken;
-  {
-    ScopedTiming _t(tag, s);
-    taken = conv_dgrad_taps(gz, w, gout, Cin, N, splits, dst, s, &e);
-  }
-  if (!taken) {
+  if (!conv_dgrad_taps(gz, w, gout, Cin, N, splits, dst, s, tag, &e)) {
   dim3 grid((unsigned)((mmax + tm - 1) / tm), (unsigned)((Cin + tn - 1) / tn), (unsigned)(nc * splits));
   const int am = load_mode(cl.a[0]), bm = load_mode(cl.b[0]);
   {
@@ -578,10 +573,7 @@ static hipError_t dgrad_classes(const u16* gz, const u16* w, ConvGeom gout, int 
 static hipError_t conv_fwd(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
                            const ConvFwdOut& out, hipStream_t s, const char* tag) {
   hipError_t e = hipSuccess;
-  {
-    ScopedTiming _t(tag, s);
-    if (conv_fwd_taps(x, w, g, P, Cout, splits, out, s, &e)) return e;
-  }
+  if (conv_fwd_taps(x, w, g, P, Cout, splits, out, s, tag, &e)) return e;
   if (out.a) return hipErrorInvalidValue;   // the network's channels are all of the first kind
   const long K = 27L * g.C;
   return gemm(GatherIm2col{x, g}, GatherRows{w, K, g.C}, out.c, P, Cout, K, splits, s, tag);
@@ -589,10 +581,7 @@ static hipError_t conv_fwd(const u16* x, const u16* w, const ConvGeom& g, long P
 static hipError_t conv_wgrad(const u16* x, const u16* gz, const ConvGeom& g, long P, int Cout, int splits,
                              float* part, hipStream_t s, const char* tag) {
   hipError_t e = hipSuccess;
-  {
-    ScopedTiming _t(tag, s);
-    if (conv_wgrad_taps(x, gz, g, P, Cout, splits, part, s, &e)) return e;
-  }
+  if (conv_wgrad_taps(x, gz, g, P, Cout, splits, part, s, tag, &e)) return e;
   return gemm(GatherT{gz, Cout}, GatherIm2colT{GatherIm2col{x, g}}, part, Cout, 27L * g.C, P, splits, s, tag);
 }
 
@@ -1116,11 +1105,9 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
       // gradient is neither written nor read back
       u16* next = to_ga ? (u16*)ga : gz;
       hipError_t e = hipSuccess;
-      {
-        ScopedTiming _tm(kDgradTag[l], s);
-        if (!conv_dgrad_gelu(gcur, pbf + L.w_off, gd, L.Cin, net.N, (const float*)(w + W.z[l - 1]), next, part, s, &e))
-          return WO_EINVAL;
-      }
+      if (!conv_dgrad_gelu(gcur, pbf + L.w_off, gd, L.Cin, net.N, (const float*)(w + W.z[l - 1]), next, part, s,
+                           kDgradTag[l], &e))
+        return WO_EINVAL;
       WO_HIP_CHECK(e);
       ScopedTiming _tm("k_reduce_parts", s);
       WO_HIP_CHECK(sum_rows(part, rows, L.Cin, grad + net.L[l - 1].b_off, s));

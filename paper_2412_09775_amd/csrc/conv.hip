@@ -625,7 +625,8 @@ static int row_blocks(const RowProblem& p, unsigned nq) {
 }
 
 template <bool DG, class EP>
-static bool launch_rows(RowProblem& p, long mmax, unsigned nq, const EP& ep, hipStream_t s, hipError_t* e) {
+static bool launch_rows(RowProblem& p, long mmax, unsigned nq, const EP& ep, hipStream_t s, const char* tag,
+                        hipError_t* e) {
   const bool narrow = p.N <= 32;
   const unsigned ny = tiles(p.N, narrow ? 32 : 64);
   const int mi = row_blocks(p, nq);
@@ -637,6 +638,7 @@ static bool launch_rows(RowProblem& p, long mmax, unsigned nq, const EP& ep, hip
   p.tx = fast_div((int)nx);
   p.ntiles = (unsigned)total;
   const dim3 grid(xcd_grid(total));
+  ScopedTiming _t(tag, s);
   if (mi == 2) {
     if (narrow) hipLaunchKernelGGL((k_conv_rows<2, 32, DG, EP>), grid, dim3(256), 0, s, p, ep);
     else hipLaunchKernelGGL((k_conv_rows<2, 64, DG, EP>), grid, dim3(256), 0, s, p, ep);
@@ -648,6 +650,10 @@ static bool launch_rows(RowProblem& p, long mmax, unsigned nq, const EP& ep, hip
   return true;
 }
 
+// Buffer loads of several words want word-aligned operands; a caller's
+// others take the general gathers (the network's lie in its workspace).
+static bool words(const u16* a, const u16* b) { return (((uintptr_t)a | (uintptr_t)b) & 3) == 0; }
+
 static PosDiv pos_div(int d, int h, int w) { return PosDiv{fast_div(w), fast_div(h), fast_div(d)}; }
 
 // Bytes from the margin before the first to the end of the last sample that
@@ -658,17 +664,18 @@ static bool span_ok(long rows, long rps, long N, long sample_bytes, long margin_
 }
 
 bool conv_fwd_taps(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
-                   const ConvFwdOut& out, hipStream_t s, hipError_t* e) {
+                   const ConvFwdOut& out, hipStream_t s, const char* tag, hipError_t* e) {
   const StoreGelu eg{out.d, out.a, out.bias, Cout};
   const StoreRows er{out.c, Cout};
   if (out.a && Cout % 4 != 0) return false;
   const bool first = g.C == 1 && splits == 1;
-  if (!first && g.C % 32 != 0) return false;   // a K step would straddle taps
+  if (!first && (g.C % 32 != 0 || (!out.a && !words(x, w)))) return false;   // 32: a K step in one tap
   const PosDiv dv = pos_div(g.Do, g.Ho, g.Wo);
   const long rps = (long)g.Do * g.Ho * g.Wo, N = P / rps, sample = 2L * g.D * g.H * g.W * g.C;
   if (!span_ok(256, rps, N, sample, 2L * fwd_margin(g) * g.C)) return false;
   if (first) {
     const dim3 grid(tiles(P, 256), tiles(Cout, 32));
+    ScopedTiming _t(tag, s);
     if (out.a)
       hipLaunchKernelGGL(k_conv_first<StoreGelu>, grid, dim3(256), 0, s, x, w, g, dv, N * sample, P, Cout, eg);
     else
@@ -687,7 +694,7 @@ bool conv_fwd_taps(const u16* x, const u16* w, const ConvGeom& g, long P, int Co
   p.c[0] = RowClass{0, 0, 0, dv, 3, 3, 3, P};
   const long K = 27L * g.C, kchunk = ((K + splits - 1) / splits + 31) / 32 * 32;
   const unsigned nz = tiles(K, kchunk);
-  return out.a ? launch_rows<false>(p, P, nz, eg, s, e) : launch_rows<false>(p, P, nz, er, s, e);
+  return out.a ? launch_rows<false>(p, P, nz, eg, s, tag, e) : launch_rows<false>(p, P, nz, er, s, tag, e);
 }
 
 // The input gradient's classes; false where the kernels do not take the shape.
@@ -717,11 +724,11 @@ static bool dgrad_problem(const u16* gz, const u16* w, const ConvGeom& gout, int
 }
 
 bool conv_dgrad_taps(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, int splits, float* out,
-                     hipStream_t s, hipError_t* e) {
+                     hipStream_t s, const char* tag, hipError_t* e) {
   RowProblem p{};
   long mmax;
-  if (!dgrad_problem(gz, w, gout, Cin, N, splits, p, mmax)) return false;
-  return launch_rows<true>(p, mmax, (unsigned)splits, StoreRows{out, Cin}, s, e);
+  if (!words(gz, w) || !dgrad_problem(gz, w, gout, Cin, N, splits, p, mmax)) return false;
+  return launch_rows<true>(p, mmax, (unsigned)splits, StoreRows{out, Cin}, s, tag, e);
 }
 
 long conv_dgrad_gelu_rows(const ConvGeom& gout, int Cin, int N) {
@@ -732,16 +739,16 @@ long conv_dgrad_gelu_rows(const ConvGeom& gout, int Cin, int N) {
 }
 
 bool conv_dgrad_gelu(const u16* gz, const u16* w, const ConvGeom& gout, int Cin, int N, const float* d, u16* gz_in,
-                     float* part, hipStream_t s, hipError_t* e) {
+                     float* part, hipStream_t s, const char* tag, hipError_t* e) {
   RowProblem p{};
   long mmax;
   if (!dgrad_problem(gz, w, gout, Cin, N, 1, p, mmax)) return false;
-  return launch_rows<true>(p, mmax, 1u, StoreGeluGrad{d, gz_in, part, Cin}, s, e);
+  return launch_rows<true>(p, mmax, 1u, StoreGeluGrad{d, gz_in, part, Cin}, s, tag, e);
 }
 
 bool conv_wgrad_taps(const u16* x, const u16* gz, const ConvGeom& g, long P, int Cout, int splits, float* part,
-                     hipStream_t s, hipError_t* e) {
-  if (Cout % 8 != 0 || (g.C != 1 && g.C % 8 != 0)) return false;
+                     hipStream_t s, const char* tag, hipError_t* e) {
+  if (Cout % 8 != 0 || (g.C != 1 && g.C % 8 != 0) || !words(g.C == 1 ? gz : x, gz)) return false;
   const long K = 27L * g.C, kchunk = ((P + splits - 1) / splits + 31) / 32 * 32;
   const PosDiv dv = pos_div(g.Do, g.Ho, g.Wo);
   const long rps = (long)g.Do * g.Ho * g.Wo, N = P / rps, sample = 2L * g.D * g.H * g.W * g.C;
@@ -753,6 +760,7 @@ bool conv_wgrad_taps(const u16* x, const u16* gz, const ConvGeom& g, long P, int
   if (total >= (1L << 30)) return false;
   const dim3 grid(xcd_grid(total));
   const FastDiv tn = fast_div((int)nn), tm = fast_div((int)nm);
+  ScopedTiming _t(tag, s);
   if (g.C == 1)
     hipLaunchKernelGGL((k_conv_wgrad<32, 32, true>), grid, dim3(256), 0, s, x, gz, g, dv, N * sample, P, Cout, kchunk,
                        tn, tm, (unsigned)total, part);
