@@ -567,16 +567,15 @@ static hipError_t dgrad_classes(const u16* gz, const u16* w, ConvGeom gout, int 
   return reduce_parts(part, splits, Mout * Cin, out, s);
 }
 
-// Forward product into partials (out.c) or, in one split, through the bias and
-// GELU (out.d, out.a); and the weight gradient's partials: on tap-sized K steps
-// where the channels allow it, else on the general gathers.
-static hipError_t conv_fwd(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits,
-                           const ConvFwdOut& out, hipStream_t s, const char* tag) {
+// Forward product into c (one block per split) and the weight gradient's
+// partials: on tap-sized K steps where the shape allows it, else on the general
+// gathers.
+static hipError_t conv_fwd(const u16* x, const u16* w, const ConvGeom& g, long P, int Cout, int splits, float* c,
+                           hipStream_t s, const char* tag) {
   hipError_t e = hipSuccess;
-  if (conv_fwd_taps(x, w, g, P, Cout, splits, out, s, tag, &e)) return e;
-  if (out.a) return hipErrorInvalidValue;   // the network's channels are all of the first kind
+  if (conv_fwd_taps(x, w, g, P, Cout, splits, ConvFwdOut{c, nullptr, nullptr, nullptr}, s, tag, &e)) return e;
   const long K = 27L * g.C;
-  return gemm(GatherIm2col{x, g}, GatherRows{w, K, g.C}, out.c, P, Cout, K, splits, s, tag);
+  return gemm(GatherIm2col{x, g}, GatherRows{w, K, g.C}, c, P, Cout, K, splits, s, tag);
 }
 static hipError_t conv_wgrad(const u16* x, const u16* gz, const ConvGeom& g, long P, int Cout, int splits,
                              float* part, hipStream_t s, const char* tag) {
@@ -1041,16 +1040,19 @@ int cnn_run(const float* params, const float* x, int N, int Z, int Y, int X, con
     float* z = (float*)(w + W.z[l]);
     u16* a = (u16*)(w + W.a[l]);
     const int fs = fwd_splits(L.P_out, L.Cout, K);
-    if (fs == 1) {
-      // the GEMM's epilogue adds the bias and applies GELU (z and a written directly)
-      WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, 1,
-                            ConvFwdOut{nullptr, target ? z : nullptr, a, params + L.b_off}, s, kFwdTag[l]));
+    hipError_t e = hipSuccess;
+    // one split: the GEMM's epilogue adds the bias and applies GELU
+    if (fs == 1 && conv_fwd_taps(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, 1,
+                                 ConvFwdOut{nullptr, target ? z : nullptr, a, params + L.b_off}, s, kFwdTag[l], &e)) {
+      WO_HIP_CHECK(e);
     } else {
-      // few tiles: split K, sum the partials in a fixed order into z, then bias and GELU
-      WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, fs,
-                            ConvFwdOut{part, nullptr, nullptr, nullptr}, s, kFwdTag[l]));
-      { ScopedTiming _tm("k_reduce_parts", s);
-      WO_HIP_CHECK(reduce_parts(part, splits_used(K, fs), L.P_out * L.Cout, z, s));
+      // few tiles: split K, sum the partials in a fixed order into z; then (as
+      // for a volume past the tap kernels' offsets) bias and GELU
+      float* c = fs == 1 ? z : part;
+      WO_HIP_CHECK(conv_fwd(a_in, pbf + L.w_off, L.g, L.P_out, L.Cout, fs, c, s, kFwdTag[l]));
+      if (fs > 1) {
+        ScopedTiming _tm("k_reduce_parts", s);
+        WO_HIP_CHECK(reduce_parts(part, splits_used(K, fs), L.P_out * L.Cout, z, s));
       }
       { ScopedTiming _tm("k_bias_gelu", s);
       hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(L.P_out * L.Cout, 256)), dim3(256), 0, s, z,
@@ -1139,7 +1141,7 @@ hipError_t conv_fwd_raw(const u16* x, const u16* w, int N, int D, int H, int W, 
                         float* out, hipStream_t s) {
   ConvGeom g{D, H, W, Cin, (D - 1) / 2 + 1, (H - 1) / 2 + 1, (W - 1) / 2 + 1};
   const long P = (long)N * g.Do * g.Ho * g.Wo;
-  return conv_fwd(x, w, g, P, Cout, 1, ConvFwdOut{out, nullptr, nullptr, nullptr}, s, "k_gemm_conv_fwd");
+  return conv_fwd(x, w, g, P, Cout, 1, out, s, "k_gemm_conv_fwd");
 }
 
 hipError_t conv_dgrad_raw(const u16* gz, const u16* w, int N, int D, int H, int W, int Cin, int Cout,

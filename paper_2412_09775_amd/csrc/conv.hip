@@ -650,8 +650,8 @@ static bool launch_rows(RowProblem& p, long mmax, unsigned nq, const EP& ep, hip
   return true;
 }
 
-// Buffer loads of several words want word-aligned operands; a caller's
-// others take the general gathers (the network's lie in its workspace).
+// Buffer loads of several words want word-aligned operands; others take the
+// general gathers.
 static bool words(const u16* a, const u16* b) { return (((uintptr_t)a | (uintptr_t)b) & 3) == 0; }
 
 static PosDiv pos_div(int d, int h, int w) { return PosDiv{fast_div(w), fast_div(h), fast_div(d)}; }
@@ -669,7 +669,7 @@ bool conv_fwd_taps(const u16* x, const u16* w, const ConvGeom& g, long P, int Co
   const StoreRows er{out.c, Cout};
   if (out.a && Cout % 4 != 0) return false;
   const bool first = g.C == 1 && splits == 1;
-  if (!first && (g.C % 32 != 0 || (!out.a && !words(x, w)))) return false;   // 32: a K step in one tap
+  if (!first && (g.C % 32 != 0 || !words(x, w))) return false;   // 32: a K step in one tap
   const PosDiv dv = pos_div(g.Do, g.Ho, g.Wo);
   const long rps = (long)g.Do * g.Ho * g.Wo, N = P / rps, sample = 2L * g.D * g.H * g.W * g.C;
   if (!span_ok(256, rps, N, sample, 2L * fwd_margin(g) * g.C)) return false;

@@ -287,3 +287,34 @@ def test_large_batch_gradient_matches_oracle(gpu_lib, N):
         e = rel(g[off:off + n], gref[off:off + n]) if np.any(gref[off:off + n]) else 0.0
         assert e < 2e-2, (kind, shp, e)
         off += n
+
+
+def test_plane_past_the_tap_kernels(gpu_lib):
+    """A 4096 x 4096 plane: the second layer's rows lie further apart than the tap
+    kernels' offsets reach, so it takes the general gathers and a separate bias-GELU
+    pass.  The network against the same layers called one by one (BF16 flips only, as
+    for the small network), and that layer against a crop, whose inner rows are the
+    same sums in the same order."""
+    import torch
+    import torch.nn.functional as F
+    from paper_2412_09775_amd import learned_init
+    print("[case] network forward 1 x 1 x 4096 x 4096", flush=True)
+    p = learned_init.init_params(11)
+    x = torch.randn((1, 1, 4096, 4096), device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    pt = torch.from_numpy(p).cuda()
+    y = gpu_lib.cnn_forward(pt, x)
+    a = (x / x.double().square().mean().sqrt().float()).to(torch.bfloat16).unsqueeze(-1).contiguous()
+    off = 0
+    for ci, co in zip(cnn.CHANNELS[:-1], cnn.CHANNELS[1:]):
+        w = pt[off:off + co * 27 * ci].to(torch.bfloat16).view(co, 27 * ci)
+        b = pt[off + co * 27 * ci:off + co * (27 * ci + 1)]
+        off += co * (27 * ci + 1)
+        bits = a.view(torch.int16)
+        z = gpu_lib.conv3d_forward(bits, w.view(torch.int16), co)
+        if ci == 32:
+            crop = gpu_lib.conv3d_forward(bits[:, :, :64].contiguous(), w.view(torch.int16), co)
+            assert torch.equal(crop[:, :, :31], z[:, :, :31])
+        a = F.gelu(z + b).to(torch.bfloat16)
+    feat = a.float().reshape(-1, cnn.CHANNELS[-1]).double().mean(0)
+    wh, bh = pt[off:off + 3 * 256].view(3, 256).double(), pt[off + 3 * 256:].double()
+    assert rel(y.cpu().numpy()[0], (wh @ feat + bh).cpu().numpy()) < 1e-3
