@@ -118,17 +118,15 @@ def kernel_bytes(name, Z, Y, X, sup, C=1, P=2, E=None, F=None):
         # Z pass writes the full half-spectrum bank
         half_full = Z * Y * Xh
         # the fused path works on the support's shortened transforms ly x lx
-        sl = Z * ly * sup["tf_lengths"][1]
         rows_kt_s = Z * ly * kt
         table.update({
             "k_vec_spectra": F * cplx * Z * ly * fb,
             "k_cols_vec": 2 * F * cplx * Z * ly * fb,
             "k_rows_c2c": F * cplx * (Z * Y * fb + full),
             "k_vec_products": F * cplx * full + C * P * 4 * full,
-            # fused X pass + responses: per row the F spectra lines of fb kept
-            # columns read once, C P response rows of lx written
-            "k_vec_rows_resp": Z * ly * (F * cplx * fb + C * P * 4 * sup["tf_lengths"][1]),
-            "k_rows_r2c_tf": C * P * (4 * sl + cplx * rows_kt_s),
+            # fused row pass: per row the F spectra lines of fb kept columns read
+            # once, C P response rows' kt columns written
+            "k_vec_rows": Z * ly * cplx * (F * fb + C * P * kt),
             "k_cols_y_tf": C * P * cplx * (rows_kt_s + band),
             "k_cols_expand": C * P * cplx * (band + half_full),
             "k_cols_z_band": 2 * C * P * cplx * band,
@@ -152,12 +150,12 @@ def counter_symbols(sup, Z, X, P, C, ns=None):
     zop = f"wo::k_zop<{P}, {ct}, {Z}, true>" if C == 5 and P == 4 else f"wo::k_zop<{P}, {ct}, {Z}, false>"
     if ns is not None:   # the vector bank's synthesis (ns illumination states)
         return {"k_vec_products": f"wo::k_vec_products<{ns}>", "k_vec_spectra": f"wo::k_vec_spectra<{ns}>",
-                "k_vec_rows_resp": f"wo::k_vec_rows_resp<{ns}, {X}>",
+                "k_vec_rows": f"wo::k_vec_rows<{ns}, {lx}>",
                 "k_rows_c2c": f"wo::k_rows_c2c<{X}>", f"k_zop<{P}>": f"wo::k_zop<{P}, {ct}, {Z}, false>",
                 "k_rows_r2c": f"wo::k_rows_r2c<{X}>", "k_rows_c2r": f"wo::k_rows_c2r<{X}>"}
     return {f"k_zop<{P}>": zop, "k_rows_r2c": f"wo::k_rows_r2c<{X}>",
             "k_rows_c2r": f"wo::k_rows_c2r<{X}>", "k_tf_rows_lf": f"wo::k_tf_rows_lf<{lx}>",
-            "k_tf_fields_y": f"wo::k_tf_fields_y<{ly}, 2, false>",
+            "k_tf_fields_y": f"wo::k_tf_fields_y<{ly}, 2, false, false>",
             "k_cols_z_band": f"wo::k_cols_expand<{Z}, {min(16, 8192 // Z)}>"}
 
 
@@ -584,7 +582,7 @@ def linear_section(api, torch, dev, args, key, parity=True):
     ms_rec = timed(step_rec, args.steps)      # cached transfer function
 
     E = 2 if key == "pol5" else None
-    F = 6 + 3 * (5 if o.vec_channels == 1 else 1) if key == "vector" else None
+    F = (10 if o.vec_channels == 1 else 8) if key == "vector" else None
     # the fluorescence workload (about 10 MB) stays in the caches and its kernels
     # last a few microseconds each: launch- and latency-bound, no HBM roofline
     hbm = key != "fluor"
