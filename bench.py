@@ -150,7 +150,7 @@ def counter_symbols(sup, Z, X, P, C, ns=None):
     zop = f"wo::k_zop<{P}, {ct}, {Z}, true>" if C == 5 and P == 4 else f"wo::k_zop<{P}, {ct}, {Z}, false>"
     if ns is not None:   # the vector bank's synthesis (ns illumination states)
         return {"k_vec_products": f"wo::k_vec_products<{ns}>", "k_vec_spectra": f"wo::k_vec_spectra<{ns}>",
-                "k_vec_rows": f"wo::k_vec_rows<{ns}, {lx}>",
+                "k_vec_rows": f"wo::k_vec_rows<{ns}, {lx}, false>",
                 "k_rows_c2c": f"wo::k_rows_c2c<{X}>", f"k_zop<{P}>": f"wo::k_zop<{P}, {ct}, {Z}, false>",
                 "k_rows_r2c": f"wo::k_rows_r2c<{X}>", "k_rows_c2r": f"wo::k_rows_c2r<{X}>"}
     return {f"k_zop<{P}>": zop, "k_rows_r2c": f"wo::k_rows_r2c<{X}>",

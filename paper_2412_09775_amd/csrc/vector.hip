@@ -324,11 +324,18 @@ hipError_t launch_vec_products(const VecRec* rec, const float2* fields, float* o
 // issue (about 20 transforms and C N contractions of 160 instructions a row).
 // 5 states x 4 properties, 64 x 512 x 512 (rows of 256): 21 fields, responses
 // through HBM and a row pass 328 + 111 us, 308 us so.
-// More lines than a workgroup owns at once go in batches.
-template <int NS, int N>
+// More lines than a workgroup owns at once go in batches.  BATCH: the responses
+// of every channel do not fit LDS (five states, seven or eight properties, rows of
+// 1024: 18 or 20 lines where 17 fit), so cb channels at a time are formed and
+// transformed in the lines behind the fields, which stay; as many as fit, because
+// a batch costs two barriers and a pass over the fields (8 x 512 x 1024, the bank:
+// 7 properties 758 us, 8 849 us; per-channel rows and a row pass of their own
+// took 808 and 879).
+template <int NS, int N, bool BATCH = false>
 __global__ __launch_bounds__(1024) void k_vec_rows(const VecRec* __restrict__ rec,
                                                    const float2* __restrict__ spec,
-                                                   float2* __restrict__ out, int XC, int KP, int KT, long zy) {
+                                                   float2* __restrict__ out, int XC, int KP, int KT, long zy,
+                                                   int cb) {
   constexpr int C = NS == 1 ? 4 : 5, F = VecFields<NS>::kF;
   constexpr bool SPLIT = F * N > kMaxElems;             // the fields in two batches
   constexpr int NB = SPLIT ? 5 : F;                      // lines of the first batch
@@ -356,41 +363,48 @@ __global__ __launch_bounds__(1024) void k_vec_rows(const VecRec* __restrict__ re
         [&] { if (l0 == 0) tw_end(twf, tw, N, tid, nthr); });
     static_passes<N, 0, false, kEmax, true, false, 1, NP>(buf + l0 * LS, nl, 1, LS, -1, tw, 1.f, tid, nthr);
   }
-  // Response q = c P + p is the real (q even) or imaginary part of line q / 2.
+  // Response q = c P + p is the real (q even) or imaginary part of line q / 2
+  // (BATCH: q counts from the batch's first response).
   // One thread owns point x of every line, so it may replace the fields there as
   // soon as it has read them; the channel index is uniform, so the constants of
   // a channel stay in scalar registers.
-  const int P = rv.P;
+  const int P = rv.P, CB = BATCH ? cb : C;
   const float sc = 2.f * rv.scale_short;
-  const int nq = C * P, nlo = (nq + 1) / 2;
-  for (int x = tid; x < N; x += nthr) {
-    const int sl = row_slot(x, PS);
-    float2 f[F];
-#pragma unroll
-    for (int a = 0; a < F; ++a) f[a] = buf[a * LS + sl];
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-      vec_channel<NS>(rv, c, P, sc, [&](int a) { return f[a]; }, [&](int a) { return f[5 + a]; },
-                      [&](int p, float v) {
-                        const int q = c * P + p;
-                        ((float*)(buf + (q >> 1) * LS + sl))[q & 1] = v;
-                      });
-    if (nq & 1) ((float*)(buf + (nlo - 1) * LS + sl))[1] = 0.f;
-  }
-  __syncthreads();
   const int LB = nthr * kEmax / N;   // lines a workgroup owns at once
-  for (int l0 = 0; l0 < nlo; l0 += LB)
-    static_passes<N, 0, false, kEmax, true, false, 0, NP>(buf + l0 * LS, min(LB, nlo - l0), 1, LS, -1, tw, -1.f,
-                                                          tid, nthr);
-  float2* op = out + (patch * (long)nq * zy + r) * KT;
   const float inv_kt = 1.0f / (float)KT;
-  for (int e = tid; e < nlo * KT; e += nthr) {
-    const int l = div_small(e, inv_kt), k = e - l * KT;
-    const float2 zk = buf[l * LS + row_slot(k, PS)];
-    const float2 zm = buf[l * LS + row_slot(k == 0 ? 0 : N - k, PS)];
-    op[(long)(2 * l) * zy * KT + k] = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
-    if (2 * l + 1 < nq)
-      op[(long)(2 * l + 1) * zy * KT + k] = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
+  float2* rb = BATCH ? buf + F * LS : buf;   // the responses' lines
+  for (int c0 = 0; c0 < C; c0 += CB) {
+    const int nq = min(CB, C - c0) * P, nlo = (nq + 1) / 2;
+    for (int x = tid; x < N; x += nthr) {
+      const int sl = row_slot(x, PS);
+      float2 f[F];
+#pragma unroll
+      for (int a = 0; a < F; ++a) f[a] = buf[a * LS + sl];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        if (BATCH && (c < c0 || c >= c0 + CB)) continue;
+        vec_channel<NS>(rv, c, P, sc, [&](int a) { return f[a]; }, [&](int a) { return f[5 + a]; },
+                        [&](int p, float v) {
+                          const int q = (BATCH ? c - c0 : c) * P + p;
+                          ((float*)(rb + (q >> 1) * LS + sl))[q & 1] = v;
+                        });
+      }
+      if (nq & 1) ((float*)(rb + (nlo - 1) * LS + sl))[1] = 0.f;
+    }
+    __syncthreads();
+    for (int l0 = 0; l0 < nlo; l0 += LB)
+      static_passes<N, 0, false, kEmax, true, false, 0, NP>(rb + l0 * LS, min(LB, nlo - l0), 1, LS, -1, tw, -1.f,
+                                                            tid, nthr);
+    float2* op = out + ((patch * C + c0) * (long)P * zy + r) * KT;
+    for (int e = tid; e < nlo * KT; e += nthr) {
+      const int l = div_small(e, inv_kt), k = e - l * KT;
+      const float2 zk = rb[l * LS + row_slot(k, PS)];
+      const float2 zm = rb[l * LS + row_slot(k == 0 ? 0 : N - k, PS)];
+      op[(long)(2 * l) * zy * KT + k] = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
+      if (2 * l + 1 < nq)
+        op[(long)(2 * l + 1) * zy * KT + k] = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
+    }
+    if (BATCH) __syncthreads();   // the next batch writes the lines just read
   }
 }
 
@@ -414,18 +428,29 @@ hipError_t launch_vec_rows(const VecRec* rec, const float2* spec, float2* out, i
   const long nwg = (long)npatch * zy;
   if (nwg > 0x7fffffffL) return hipErrorInvalidValue;
   const int thr = threads_for((long)((long)F * X > kMaxElems ? 5 : F) * X);
-  const long lines = std::max(F, (C * P + 1) / 2);
+  // every channel's responses in place of the fields where they fit LDS, else as
+  // many channels at a time as fit behind the fields (rows of 1024 only: the lines
+  // of shorter rows always fit)
+  const long most = (lds_limit_bytes() / (long)sizeof(float2) - X) / row_stride(X);   // lines
+  const bool batch = (C * P + 1) / 2 > most;
+  const int cb = batch ? (int)std::min<long>(C, std::max<long>(0, 2 * (most - F) / P)) : C;
+  if (most < F || cb < 1 || (batch && (NS != 5 || X != 1024))) return hipErrorInvalidValue;
+  const long lines = batch ? F + (cb * P + 1) / 2 : std::max(F, (C * P + 1) / 2);
   const size_t lds = (size_t)(X + lines * row_stride(X)) * sizeof(float2);
-  if ((long)lds > lds_limit_bytes()) return hipErrorInvalidValue;
   ScopedTiming _t("k_vec_rows", s);
+  if (batch) {
+    hipLaunchKernelGGL((k_vec_rows<5, 1024, true>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, KP,
+                       KT, zy, cb);
+    return hipGetLastError();
+  }
 #define X_(NN)                                                                                       \
   case NN:                                                                                           \
     if (NS == 1)                                                                                     \
       hipLaunchKernelGGL((k_vec_rows<1, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, KP, \
-                         KT, zy);                                                                    \
+                         KT, zy, cb);                                                                \
     else                                                                                             \
       hipLaunchKernelGGL((k_vec_rows<5, NN>), dim3((unsigned)nwg), dim3(thr), lds, s, rec, spec, out, XC, KP, \
-                         KT, zy);                                                                    \
+                         KT, zy, cb);                                                                \
     return hipGetLastError();
   switch (X) {
     WO_LATERAL_SIZES(X_)

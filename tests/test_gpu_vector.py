@@ -128,3 +128,28 @@ def test_row_kernel_edges(gpu_lib, name, channels, props, shape):
     err = np.max(np.abs(got - ref)) / np.max(np.abs(ref))
     print(f"  max abs / max {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("props,shape,n", [
+    (tuple(range(7)), (3, 48, 1280), 1),            # 18 lines of two responses
+    ((0, 1, 2, 5, 8, 11, 14, 17), (3, 48, 1280), 1),   # 20
+    (tuple(range(8)), (2, 40, 1024), 2),            # the largest set on the grid's own rows, two patches
+    ((0, 16, 8, 1, 2, 3), (2, 40, 1024), 1),        # the most that share the fields' lines
+])
+def test_many_properties_on_rows_of_1024(gpu_lib, props, shape, n):
+    """Five states with up to eight properties on rows of 1024: more lines of
+    responses than a workgroup's LDS holds (17 of 1024 points).  Bound as above."""
+    nz, ny, nx = shape
+    base = dict(model=op.VECTOR_3D, nz=nz, ny=ny, nx=nx, dz=0.25, dy=0.1, dx=0.1, wavelength=0.532, na_ill=0.5,
+                na_det=1.2 if nx == 1024 else 1.1, n_medium=1.33, tilt_zenith=0.1, defocus=0.2, swing=0.1,
+                vec_channels=1, vec_props=props)
+    print(f"[case] vector rows of 1024, {len(props)} properties {shape} x {n}", flush=True)
+    from paper_2412_09775_amd import api
+    optics = [api.Optics(**dict(base, defocus=0.2 - 0.3 * i)) for i in range(n)]
+    assert api.lateral_support(optics)["tf_lengths"][1] == 1024
+    got = gpu_lib.transfer_function(optics, device="cuda:0").cpu().numpy()
+    for i in range(n):
+        ref = tfm.transfer_function(op.Optics(**dict(base, defocus=0.2 - 0.3 * i)))[..., : nx // 2 + 1]
+        err = np.max(np.abs(got[i] - ref)) / np.max(np.abs(ref))
+        print(f"  patch {i}: max abs / max {err:.2e}", flush=True)
+        assert err <= 1e-5
