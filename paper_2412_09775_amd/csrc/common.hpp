@@ -586,6 +586,14 @@ constexpr bool listed_length(int n) {
   return false;
 }
 
+// Twiddles from the table (see twiddles) for the lengths whose plans hold radices
+// 9, 10 or 12: with powers their transforms round worse than the runtime plans of
+// radices up to 8 (1.04 to 1.7 times over these lengths, 0.69 to 0.99 times with
+// the table, by emulation); the listed lengths keep the powers (5x4 step on 64 x
+// 1024 x 1024: 1540 us, 1620 with the table).
+template <int N>
+constexpr bool kTableTwiddles = !listed_length(N) || N == 80 || N == 480;
+
 // Row padding of a compiled length: none but for those.
 template <int N>
 constexpr int kStaticPad = listed_length(N) ? pad_shift(N) : kNoPad;
@@ -628,6 +636,22 @@ __device__ __forceinline__ void twiddle_powers(float2 (&w)[R], float2 w1) {
   if constexpr (R > 1) w[1] = w1;
 #pragma unroll
   for (int r = 2; r < R; ++r) w[r] = cmul(w[r / 2], w[r - r / 2]);
+}
+
+// The same twiddles, tw[m r] from the table (TB) or as powers of tw[m].  Each table
+// entry is rounded once; the powers carry up to four roundings, the same ones in
+// every line, which a sum over planes does not average: rms error of one 120-point
+// transform 0.95e-7 from the table and 1.6e-7 from powers, of its matrix 0.4e-7
+// and 1.4e-7.  The table costs R - 1 LDS reads a butterfly.
+template <int R, bool TB>
+__device__ __forceinline__ void twiddles(float2 (&w)[R], const float2* tw, int m, bool conj) {
+  w[0] = make_float2(1.f, 0.f);
+#pragma unroll
+  for (int r = 1; r < (TB ? R : 2); ++r) {
+    w[r] = tw[m * r];
+    if (conj) w[r].y = -w[r].y;
+  }
+  if constexpr (!TB && R > 2) twiddle_powers<R>(w, w[1]);
 }
 
 template <int R>
@@ -1181,7 +1205,7 @@ struct StaticPlan {
   }
 };
 
-template <int N, int R, int NS, int NL, bool LF, int EM, bool PD>
+template <int N, int R, int NS, int NL, bool LF, int EM, bool PD, bool TB = kTableTwiddles<N>>
 __device__ __forceinline__ void static_pass(float2* lds, int nl_rt, int es, int ls, int shift,
                                             const float2* tw, float s, int tid, int nthr) {
   constexpr int NB = N / R;
@@ -1207,9 +1231,7 @@ __device__ __forceinline__ void static_pass(float2* lds, int nl_rt, int es, int 
       kk[b] = k;
       float2 w[R];
       if constexpr (NS > 1) {
-        float2 w1 = tw[km * TWS];
-        if (s > 0.f) w1.y = -w1.y;
-        twiddle_powers<R>(w, w1);
+        twiddles<R, TB>(w, tw, km * TWS, s > 0.f);
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -1238,13 +1260,13 @@ __device__ __forceinline__ void static_pass(float2* lds, int nl_rt, int es, int 
   __syncthreads();
 }
 
-template <int N, int NL, bool LF, int EM, bool PD, int Q = 0>
+template <int N, int NL, bool LF, int EM, bool PD, bool TB, int Q = 0>
 __device__ __forceinline__ void static_fft(float2* lds, int nl_rt, int es, int ls, int shift,
                                            const float2* tw, float s, int tid, int nthr) {
   if constexpr (Q < StaticPlan<N>::passes()) {
-    static_pass<N, StaticPlan<N>::radix(Q), StaticPlan<N>::span(Q), NL, LF, EM, PD>(
+    static_pass<N, StaticPlan<N>::radix(Q), StaticPlan<N>::span(Q), NL, LF, EM, PD, TB>(
         lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
-    static_fft<N, NL, LF, EM, PD, Q + 1>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
+    static_fft<N, NL, LF, EM, PD, TB, Q + 1>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
   }
 }
 
@@ -1265,14 +1287,15 @@ struct OrderedPlan {
 };
 
 // Passes [Q, QE) of the compiled transform of length N in the given order.
-template <int N, int NL, bool LF, int EM, bool PD, bool REV, int Q, int QE, bool W16 = false>
+template <int N, int NL, bool LF, int EM, bool PD, bool REV, int Q, int QE, bool W16 = false,
+          bool TB = kTableTwiddles<N>>
 __device__ __forceinline__ void static_passes(float2* lds, int nl_rt, int es, int ls, int shift,
                                               const float2* tw, float s, int tid, int nthr) {
   if constexpr (Q < QE) {
     using PL = OrderedPlan<N, REV, W16>;
-    static_pass<N, PL::radix(Q), PL::span(Q), NL, LF, EM, PD>(lds, nl_rt, es, ls, shift, tw, s, tid,
-                                                             nthr);
-    static_passes<N, NL, LF, EM, PD, REV, Q + 1, QE, W16>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
+    static_pass<N, PL::radix(Q), PL::span(Q), NL, LF, EM, PD, TB>(lds, nl_rt, es, ls, shift, tw, s, tid,
+                                                                 nthr);
+    static_passes<N, NL, LF, EM, PD, REV, Q + 1, QE, W16, TB>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
   }
 }
 
@@ -1379,7 +1402,8 @@ __device__ __forceinline__ void first_pass_in(float2* lds, int nl_rt, int es, in
                                          [](int, int, float2 v) { return v; }, mid);
 }
 
-template <int N, int NL, bool LF, int EM, bool PD, bool REV, bool W16 = false, typename ST>
+template <int N, int NL, bool LF, int EM, bool PD, bool REV, bool W16 = false, bool TB = kTableTwiddles<N>,
+          typename ST>
 __device__ __forceinline__ void last_pass_out(const float2* lds, int nl_rt, int es, int ls, int shift,
                                               const float2* tw, float s, int tid, int nthr, ST store) {
   using PL = OrderedPlan<N, REV, W16>;
@@ -1400,9 +1424,7 @@ __device__ __forceinline__ void last_pass_out(const float2* lds, int nl_rt, int 
       int l, k;
       line_of<N, NL, LF, PD>(j, nl, NSL, shift, l, k);
       float2 w[RL];
-      float2 w1 = tw[k];   // span NSL = N / RL: twiddle stride 1
-      if (s > 0.f) w1.y = -w1.y;
-      twiddle_powers<RL>(w, w1);
+      twiddles<RL, TB>(w, tw, k, s > 0.f);   // span NSL = N / RL: twiddle stride 1
 #pragma unroll
       for (int r = 0; r < RL; ++r) {
         const int i = k + r * NSL;
@@ -1440,11 +1462,11 @@ __device__ __forceinline__ void fft_direct(float2* lds, int nl_rt, int es, int l
 // EM bounds the elements a thread owns (lines * n <= threads * EM) for the
 // compiled stages; the runtime plan assumes kEmax.
 // PD must equal L.pad (the padded row layout).
-template <int NSTAT, int NL, bool LF, int EM = kEmax, bool PD = false>
+template <int NSTAT, int NL, bool LF, int EM = kEmax, bool PD = false, bool TB = kTableTwiddles<NSTAT>>
 __device__ __forceinline__ void fft_lines(float2* lds, const LdsLines& L, const FftPlan& p,
                                           const float2* tw, float s, int tid, int nthr) {
   if constexpr (NSTAT > 0)
-    static_fft<NSTAT, NL, LF, EM, PD>(lds, L.nl, L.es, L.ls, L.shift, tw, s, tid, nthr);
+    static_fft<NSTAT, NL, LF, EM, PD, TB>(lds, L.nl, L.es, L.ls, L.shift, tw, s, tid, nthr);
   else
     lds_fft(lds, L, p, tw, s, tid, nthr);
 }

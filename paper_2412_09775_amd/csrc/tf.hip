@@ -330,9 +330,7 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
         if (j < nl * NSL) {
           const int l = j & (nl - 1), k = j >> lsh;
           float2 w[RL];
-          float2 w1 = tw[k];   // span NSL = NS / RL: twiddle stride 1; conjugate for the inverse
-          w1.y = -w1.y;
-          twiddle_powers<RL>(w, w1);
+          twiddles<RL, kTableTwiddles<NS>>(w, tw, k, true);   // span NSL = NS / RL: stride 1; the inverse
           float2 v[RL];
 #pragma unroll
           for (int r = 0; r < RL; ++r) {
@@ -620,11 +618,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ 
       if (j < nr * NB) {
         const int r = j / NB, k = j - r * NB;
         float2 w[R0];
-        if constexpr (NP > 1) {
-          float2 w1 = tw[k];   // span NB, twiddle stride 1; conjugate for the inverse
-          w1.y = -w1.y;
-          twiddle_powers<R0>(w, w1);
-        }
+        if constexpr (NP > 1) twiddles<R0, kTableTwiddles<NS>>(w, tw, k, true);   // span NB: stride 1; the inverse
         float2 va[R0], vb[R0];
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
