@@ -146,15 +146,16 @@ def counter_symbols(sup, Z, X, P, C, ns=None):
     (the column passes share one symbol across launches and are not listed); the
     TF kernels are compiled for the synthesis' transform lengths (ly, lx)."""
     ly, lx = sup["tf_lengths"]
+    tb = lambda n: "true" if n in (80, 480) else "false"   # noqa: E731  (kTableTwiddles of the lateral lengths)
     ct = 1 if C == 1 else (5 if C == 5 else 0)
     zop = f"wo::k_zop<{P}, {ct}, {Z}, true>" if C == 5 and P == 4 else f"wo::k_zop<{P}, {ct}, {Z}, false>"
     if ns is not None:   # the vector bank's synthesis (ns illumination states)
         return {"k_vec_products": f"wo::k_vec_products<{ns}>", "k_vec_spectra": f"wo::k_vec_spectra<{ns}>",
                 "k_vec_rows": f"wo::k_vec_rows<{ns}, {lx}, false>",
                 "k_rows_c2c": f"wo::k_rows_c2c<{X}>", f"k_zop<{P}>": f"wo::k_zop<{P}, {ct}, {Z}, false>",
-                "k_rows_r2c": f"wo::k_rows_r2c<{X}>", "k_rows_c2r": f"wo::k_rows_c2r<{X}>"}
-    return {f"k_zop<{P}>": zop, "k_rows_r2c": f"wo::k_rows_r2c<{X}>",
-            "k_rows_c2r": f"wo::k_rows_c2r<{X}>", "k_tf_rows_lf": f"wo::k_tf_rows_lf<{lx}>",
+                "k_rows_r2c": f"wo::k_rows_r2c<{X}, {tb(X)}>", "k_rows_c2r": f"wo::k_rows_c2r<{X}>"}
+    return {f"k_zop<{P}>": zop, "k_rows_r2c": f"wo::k_rows_r2c<{X}, {tb(X)}>",
+            "k_rows_c2r": f"wo::k_rows_c2r<{X}>", "k_tf_rows_lf": f"wo::k_tf_rows_lf<{lx}, {tb(lx)}>",
             "k_tf_fields_y": f"wo::k_tf_fields_y<{ly}, 2, false, false>",
             "k_cols_z_band": f"wo::k_cols_expand<{Z}, {min(16, 8192 // Z)}>"}
 

@@ -43,7 +43,10 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
 // carry nothing else.  ZS lanes share a frequency, each summing every ZS-th
 // plane (a fixed shuffle tree adds them); lane = slice * (64 / ZS) + frequency,
 // so a wave still reads runs of 64 / ZS consecutive columns.  Bound by the
-// latency of its strided plane loads; four slices quarter the chain.
+// latency of its strided plane loads; four slices quarter the chain, and the
+// normal matrix, its inverse and F in FP64 hide behind them (256 patches of 32 x
+// 128 x 128, loss and gradient: 2.20 ms with both; error of the loss 1.4e-7 in
+// FP32, 1.1e-7 so, of 16 x 64 x 64 patches 1.4e-7 and 0.6e-7).
 // D: [n][Z][DY][DP] (patch v reads data patch v / data_div), bank:
 // [v][Z][2][Y][kt], the band rows overwritten with dL/dH*.
 // lpart[v * bpp + block] = sum of w |F_phase|^2.
@@ -70,49 +73,52 @@ __global__ __launch_bounds__(256) void k_loss_grad(const TuneState* __restrict__
   const double r = sqrt(fy * fy + fx * fx);
   const TuneState& s = st[v];
   const bool band = on && r >= s.nu_c / 8.0 && r <= s.nu_c / 4.0;
-  const float eta = (float)s.eta;
   const long M = (long)Y * bp.kt, DM = (long)bp.DY * bp.DP;
   const float2* dp = D + (v / data_div) * (long)Z * DM + (long)(neg ? bp.DY + sy : sy) * bp.DP + kx;
   float2* hp = bank + v * (long)Z * 2 * M + (long)(neg ? Y + sy : sy) * bp.kt + kx;
   // pass 1: normal matrix and right-hand side
-  float m00 = 0.f, m11 = 0.f;
-  float2 m10 = make_float2(0.f, 0.f), r0 = make_float2(0.f, 0.f), r1 = make_float2(0.f, 0.f);
+  double m00 = 0.0, m11 = 0.0, m10x = 0.0, m10y = 0.0, r0x = 0.0, r0y = 0.0, r1x = 0.0, r1y = 0.0;
   if (band) {
 #pragma unroll 4
     for (int c = zq; c < Z; c += ZS) {
-      const float2 h0 = hp[(long)(2 * c) * M], h1 = hp[(long)(2 * c + 1) * M];
-      const float2 x = dp[(long)c * DM];
-      m00 += h0.x * h0.x + h0.y * h0.y;
-      m11 += h1.x * h1.x + h1.y * h1.y;
-      m10 = cadd(m10, cmul(cconj(h1), h0));
-      r0 = cadd(r0, cmul(cconj(h0), x));
-      r1 = cadd(r1, cmul(cconj(h1), x));
+      const float2 g0 = hp[(long)(2 * c) * M], g1 = hp[(long)(2 * c + 1) * M];
+      const float2 xf = dp[(long)c * DM];
+      const double h0x = g0.x, h0y = g0.y, h1x = g1.x, h1y = g1.y, xx = xf.x, xy = xf.y;
+      m00 += h0x * h0x + h0y * h0y;
+      m11 += h1x * h1x + h1y * h1y;
+      m10x += h1x * h0x + h1y * h0y;   // conj(h1) h0
+      m10y += h1x * h0y - h1y * h0x;
+      r0x += h0x * xx + h0y * xy;
+      r0y += h0x * xy - h0y * xx;
+      r1x += h1x * xx + h1y * xy;
+      r1y += h1x * xy - h1y * xx;
     }
   }
 #pragma unroll
   for (int o = FW; o < 64; o <<= 1) {
     m00 += __shfl_xor(m00, o, 64);
     m11 += __shfl_xor(m11, o, 64);
-    m10.x += __shfl_xor(m10.x, o, 64);
-    m10.y += __shfl_xor(m10.y, o, 64);
-    r0.x += __shfl_xor(r0.x, o, 64);
-    r0.y += __shfl_xor(r0.y, o, 64);
-    r1.x += __shfl_xor(r1.x, o, 64);
-    r1.y += __shfl_xor(r1.y, o, 64);
+    m10x += __shfl_xor(m10x, o, 64);
+    m10y += __shfl_xor(m10y, o, 64);
+    r0x += __shfl_xor(r0x, o, 64);
+    r0y += __shfl_xor(r0y, o, 64);
+    r1x += __shfl_xor(r1x, o, 64);
+    r1y += __shfl_xor(r1y, o, 64);
   }
   if (band) {
-    const float a00 = m00 + eta, a11 = m11 + eta;
-    const float det = a00 * a11 - (m10.x * m10.x + m10.y * m10.y);
-    const float idet = __builtin_amdgcn_rcpf(det);   // hardware reciprocal (about 1 ulp)
+    const double a00 = m00 + s.eta, a11 = m11 + s.eta;
+    const double idet = 1.0 / (a00 * a11 - (m10x * m10x + m10y * m10y));
     // F = M^-1 r with M = [[a00, conj(m10)], [m10, a11]]
-    const float2 F0 = cscale(csub(cscale(r0, a11), cmul(cconj(m10), r1)), idet);
-    const float2 F1 = cscale(csub(cscale(r1, a00), cmul(m10, r0)), idet);
+    const double F0x = (r0x * a11 - (m10x * r1x + m10y * r1y)) * idet;
+    const double F0y = (r0y * a11 - (m10x * r1y - m10y * r1x)) * idet;
+    const double F1x = (r1x * a00 - (m10x * r0x - m10y * r0y)) * idet;
+    const double F1y = (r1y * a00 - (m10x * r0y + m10y * r0x)) * idet;
+    const float2 F0 = make_float2((float)F0x, (float)F0y), F1 = make_float2((float)F1x, (float)F1y);
     const double w = (kx == 0 || 2 * kx == sm.nx) ? 1.0 : 2.0;
-    if (zq == 0) lsum = w * ((double)F0.x * F0.x + (double)F0.y * F0.y);
-    const float ib = (float)(1.0 / s.band_count);
-    const float2 g0 = cscale(F0, -ib);                  // dL/dF_phase*
-    const float2 Y0 = cscale(cscale(g0, a11), idet);    // Y = M^-1 (g0, 0)
-    const float2 Y1 = cscale(cmul(m10, g0), -idet);
+    if (zq == 0) lsum = w * (F0x * F0x + F0y * F0y);
+    const double ib = 1.0 / s.band_count, gx = -ib * F0x, gy = -ib * F0y;   // g0 = dL/dF_phase*
+    const float2 Y0 = make_float2((float)(gx * a11 * idet), (float)(gy * a11 * idet));   // Y = M^-1 (g0, 0)
+    const float2 Y1 = make_float2((float)(-idet * (m10x * gx - m10y * gy)), (float)(-idet * (m10x * gy + m10y * gx)));
 #pragma unroll 4
     for (int c = zq; c < Z; c += ZS) {
       const float2 h0 = hp[(long)(2 * c) * M], h1 = hp[(long)(2 * c + 1) * M];
@@ -286,7 +292,7 @@ hipError_t launch_recon_grad(float2* bank, float2* D, const float2* G, const flo
 // field 0 by the inverse X transform of u_A = conj(Gamma b)/(N I_bg) and field 1
 // by that of u_B = Gamma conj(a)/(N I_bg); dpart[v * wpp + wg] =
 // sum Re(Gamma b conj(a)).
-template <int NS>
+template <int NS, bool TB>
 __global__ __launch_bounds__(1024) void k_tf_rows_bwd(const double* __restrict__ partials,
                                                       long tiles_x, Sampling sm,
                                                       float2* __restrict__ ab,
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_bwd(const double* __restrict__
   __syncthreads();
   const float k = (float)(1.0 / ((double)X * (double)Y * ibg_s));
   double dsum = 0.0;
-  fft_lines<NS, 0, false, kEmax, true>(buf, LdsLines{3 * nr, 1, LS, false, -1, true}, plan, tw, 1.f,
+  fft_lines<NS, 0, false, kEmax, true, TB>(buf, LdsLines{3 * nr, 1, LS, false, -1, true}, plan, tw, 1.f,
                                        tid, nthr);
   for (int e = tid; e < nr * X; e += nthr) {
     const int r = e / X, i = e - r * X;
@@ -404,9 +410,9 @@ __global__ __launch_bounds__(1024) void k_tf_rows_bwd(const double* __restrict__
   };
   if constexpr (NS > 0) {
     // last pass straight to memory
-    static_passes<NS, 0, false, kEmax, true, false, 0, StaticPlan<NS>::passes() - 1>(
+    static_passes<NS, 0, false, kEmax, true, false, 0, StaticPlan<NS>::passes() - 1, false, TB>(
         buf, 2 * nr, 1, LS, -1, tw, 1.f, tid, nthr);
-    last_pass_out<NS, 0, false, kEmax, true, false>(buf, 2 * nr, 1, LS, -1, tw, 1.f, tid, nthr, store);
+    last_pass_out<NS, 0, false, kEmax, true, false, false, TB>(buf, 2 * nr, 1, LS, -1, tw, 1.f, tid, nthr, store);
   } else {
     fft_lines<NS, 0, false, kEmax, true>(buf, LdsLines{2 * nr, 1, LS, false, -1, true}, plan, tw, 1.f,
                                          tid, nthr);
@@ -447,10 +453,13 @@ hipError_t launch_tf_rows_bwd(const double* partials, const Sampling& sm, int nv
   const int thr = threads_for(3L * R * sm.nx);
   const size_t lds = (size_t)(sm.nx + 3L * R * row_stride(sm.nx)) * sizeof(float2);
   ScopedTiming _t("k_tf_rows_bwd", s);
+#define WO_BWD(NN, TB)                                                                           \
+  hipLaunchKernelGGL((k_tf_rows_bwd<NN, TB>), dim3((unsigned)(wpp * nv)), dim3(thr), lds, s, partials, \
+                     tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, KT, plan)
 #define X_(NN)                                                                                   \
   case NN:                                                                                       \
-    hipLaunchKernelGGL((k_tf_rows_bwd<NN>), dim3((unsigned)(wpp * nv)), dim3(thr), lds, s, partials, \
-                       tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, KT, plan);             \
+    if (sm.model == kLabelFreeThin) WO_BWD(NN, true);                                            \
+    else WO_BWD(NN, kTableTwiddles<NN>);                                                         \
     return hipGetLastError();
   switch (sm.nx) {
     WO_LATERAL_SIZES(X_)
@@ -458,8 +467,8 @@ hipError_t launch_tf_rows_bwd(const double* partials, const Sampling& sm, int nv
       break;
   }
 #undef X_
-  hipLaunchKernelGGL((k_tf_rows_bwd<0>), dim3((unsigned)(wpp * nv)), dim3(thr), lds, s, partials,
-                     tiles_x, sm, ab, g, dpart, R, wpp, ls.xc, ls.kp, KT, plan);
+  WO_BWD(0, false);
+#undef WO_BWD
   return hipGetLastError();
 }
 
@@ -610,7 +619,7 @@ __global__ __launch_bounds__(1024) void k_tf_grad_y(const DevOptics* __restrict_
     }
     __syncthreads();
     if (z + 1 < zend) load_plane(z + 1, nxt);
-    fft_lines<NS, 0, true, 2 * EPT>(buf, LdsLines{2 * W, 2 * W, 1, true, pow2_shift(2 * W)}, plan, tw,
+    fft_lines<NS, 0, true, 2 * EPT, false, !DT || kTableTwiddles<NS>>(buf, LdsLines{2 * W, 2 * W, 1, true, pow2_shift(2 * W)}, plan, tw,
                                     1.f, tid, nthr);
     const double dzr = plane_z(z, sm) - o.defocus;
 #pragma unroll

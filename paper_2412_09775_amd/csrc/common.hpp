@@ -590,7 +590,10 @@ constexpr bool listed_length(int n) {
 // 9, 10 or 12: with powers their transforms round worse than the runtime plans of
 // radices up to 8 (1.04 to 1.7 times over these lengths, 0.69 to 0.99 times with
 // the table, by emulation); the listed lengths keep the powers (5x4 step on 64 x
-// 1024 x 1024: 1540 us, 1620 with the table).
+// 1024 x 1024: 1540 us, 1620 with the table), but for the transforms of the
+// auto-tune, whose grids of fewer points average the rounding of fewer points:
+// 256 patches of 32 x 128 x 128, gradient against FP64 5.5e-7 with powers, 2.4e-7
+// with the table (the tile's own 128 points, powers: 4.7e-7), 2.17 and 2.20 ms.
 template <int N>
 constexpr bool kTableTwiddles = !listed_length(N) || N == 80 || N == 480;
 
@@ -1446,15 +1449,16 @@ __device__ __forceinline__ void last_pass_out(const float2* lds, int nl_rt, int 
   __syncthreads();
 }
 
-template <int N, int NL, bool LF, int EM, bool PD, typename LD, typename MID, typename ST>
+template <int N, int NL, bool LF, int EM, bool PD, bool TB = kTableTwiddles<N>, typename LD, typename MID,
+          typename ST>
 __device__ __forceinline__ void fft_direct(float2* lds, int nl_rt, int es, int ls, int shift,
                                            const float2* tw, float s, int tid, int nthr, LD load,
                                            MID mid, ST store) {
   constexpr int NP = StaticPlan<N>::passes();
   static_assert(NP >= 2, "fft_direct needs at least two passes");
   first_pass_in<N, NL, LF, EM, PD, false>(lds, nl_rt, es, ls, shift, s, tid, nthr, load, mid);
-  static_passes<N, NL, LF, EM, PD, false, 1, NP - 1>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
-  last_pass_out<N, NL, LF, EM, PD, false>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr, store);
+  static_passes<N, NL, LF, EM, PD, false, 1, NP - 1, false, TB>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr);
+  last_pass_out<N, NL, LF, EM, PD, false, false, TB>(lds, nl_rt, es, ls, shift, tw, s, tid, nthr, store);
 }
 
 // FFT of the lines described by L: static length NSTAT (> 0) or the runtime plan

@@ -40,7 +40,7 @@ static bool compiled_length(int n) {
 // band: 0 every row; 1 stores only the band rows (ky, nb) of the transform;
 // 2 loads only the band rows (the others are taken as zero).  At most 64
 // VGPRs (8 waves per SIMD), so that two 1024-thread workgroups share a CU.
-template <int NS, int WS>
+template <int NS, int WS, bool TB = kTableTwiddles<NS>>
 __global__ __launch_bounds__(1024, 8) void k_cols(float2* __restrict__ data, int N, long M, int Wrt,
                                                long tiles_m, long planes_per_group,
                                                long group_stride, FftPlan plan, float sign,
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(1024, 8) void k_cols(float2* __restrict__ data, int
     // product (about 9 VALU instructions per load or store before)
     const unsigned um = (unsigned)M, uc = (unsigned)m0;
     auto off = [&](int l, int n) { return __umul24((unsigned)n, um) + uc + (unsigned)l; };
-    fft_direct<NS, WS, true, kEmax, false>(
+    fft_direct<NS, WS, true, kEmax, false, TB>(
         buf, W, W, 1, wsh, tw, sign, tid, nthr,
         [&](int l, int n) { return ld_ok(l, n) ? base[off(l, n)] : make_float2(0.f, 0.f); },
         [&] { tw_end(twf, tw, Nc, tid, nthr); },
@@ -199,13 +199,13 @@ static FftChoice cols_default(int N) {
 }
 
 hipError_t launch_cols(float2* data, int N, long M, long planes_per_group, long group_stride,
-                       long ngroups, float sign, hipStream_t s, const char* tag, int band, int ky) {
+                       long ngroups, float sign, hipStream_t s, const char* tag, int band, int ky, bool table) {
   if (band < 0 || band > 2 || (band != 0 && ky < 0)) return hipErrorInvalidValue;
   const int nb = band == 0 || 2L * ky + 1 >= N ? N : 2 * ky + 1;
   const FftKey key{kFftCols, N, M, planes_per_group * ngroups, band};
   if (fft_recording())
     fft_record(key, [=] {
-      return launch_cols(data, N, M, planes_per_group, group_stride, ngroups, sign, s, tag, band, ky);
+      return launch_cols(data, N, M, planes_per_group, group_stride, ngroups, sign, s, tag, band, ky, table);
     });
   FftChoice c;
   if (!fft_lookup(key, &c) || !cols_choice_ok(N, c)) c = cols_default(N);
@@ -234,6 +234,18 @@ hipError_t launch_cols(float2* data, int N, long M, long planes_per_group, long 
     return hipGetLastError();
   // the compiled kernels index a plane in 32 bits
   const bool small_plane = M < (1L << 24) && (long)N * M < (1L << 32);
+#define T_(NN)                                                                                  \
+  case NN:                                                                                      \
+    hipLaunchKernelGGL((k_cols<NN, static_tile_width(NN), true>), dim3((unsigned)nwg), dim3(thr), lds, \
+                       s, data, N, M, W, tiles, planes_per_group, group_stride, plan, sign, band, \
+                       ky, nb);                                                                 \
+    return hipGetLastError();
+  if (table && c.plan == 0 && small_plane && W == static_tile_width(N)) switch (N) {
+      WO_LATERAL_SIZES(T_)
+      default:
+        break;
+    }
+#undef T_
   if ((c.plan == 0 || c.plan == kPlanColsLoop) && small_plane) switch (N) {
       WO_ALL_SIZES(X_)
 #undef X_

@@ -116,7 +116,7 @@ struct RowGroups {
 // Real rows -> half-spectrum rows (forward, unnormalised): the columns k < kt
 // (0: all X/2 + 1) of each output row, row pitch `pitch` (0: X/2 + 1).
 hipError_t launch_rows_r2c(const float* in, float2* out, int X, const RowGroups& g, hipStream_t s,
-                           int kt = 0, int pitch = 0, const char* tag = "k_rows_r2c");
+                           int kt = 0, int pitch = 0, const char* tag = "k_rows_r2c", bool table = false);
 // Half-spectrum rows -> real rows times `scale` (inverse); input rows of
 // pitch `pitch` hold the columns k < kt, the others are taken as zero.
 hipError_t launch_rows_c2r(const float2* in, float* out, int X, const RowGroups& g, float scale,
@@ -134,9 +134,11 @@ __device__ __forceinline__ bool in_band(int y, int ky, int nb, int Y) {
 // starts at data + (g * group_stride + p) * N * M.
 // band: 0 every row; 1 stores only the band rows n <= ky or n >= N - ky of
 // the transform; 2 loads only those (the others are taken as zero).
+// table (here and in launch_rows_r2c): twiddles from the table at every lateral
+// length (the auto-tune's passes; schedules other than the default keep theirs).
 hipError_t launch_cols(float2* data, int N, long M, long planes_per_group, long group_stride,
                        long ngroups, float sign, hipStream_t s, const char* tag = "k_cols",
-                       int band = 0, int ky = -1);
+                       int band = 0, int ky = -1, bool table = false);
 // FFT along N of the band rows (y <= ky or y >= rows - ky) of compact planes
 // src [g][N][Ys][kt] into the full half-spectrum planes dst [g][N][Y][Xh];
 // every other value of dst (rows outside the band, columns kx >= kt) is set

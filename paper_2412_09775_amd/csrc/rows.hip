@@ -14,7 +14,7 @@ __device__ __forceinline__ long group_row(long r, long rpg, long stride) {
   return g * stride + (r - g * rpg);
 }
 
-template <int NS>
+template <int NS, bool TB = kTableTwiddles<NS>>
 __global__ __launch_bounds__(1024) void k_rows_r2c(const float* __restrict__ in,
                                                    float2* __restrict__ out, int X, RowGroups g,
                                                    FftPlan plan, int lines_per_wg, long nlines,
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(1024) void k_rows_r2c(const float* __restrict__ in,
     static_assert(OrderedPlan<NS, false, true>::radix(0) == OrderedPlan<NS, false>::radix(0), "first pass");
     first_pass_in2<NS, 0, false, kEmax, true, false>(buf, nl, 1, LS, -1, -1.f, tid, nthr, load, finish,
                                                      [&] { tw_end(twf, tw, Xc, tid, nthr); });
-    static_passes<NS, 0, false, kEmax, true, false, 1, StaticPlan<NS, true>::passes(), true>(
+    static_passes<NS, 0, false, kEmax, true, false, 1, StaticPlan<NS, true>::passes(), true, TB>(
         buf, nl, 1, LS, -1, tw, -1.f, tid, nthr);
   } else {
     tw_end(twf, tw, Xc, tid, nthr);
@@ -210,13 +210,13 @@ static FftChoice rows_choice(const FftKey& k) {
     return hipGetLastError();
 
 hipError_t launch_rows_r2c(const float* in, float2* out, int X, const RowGroups& g, hipStream_t s,
-                           int kt, int pitch, const char* tag) {
+                           int kt, int pitch, const char* tag, bool table) {
   const int Xh = X / 2 + 1;
   const int KT = kt > 0 ? kt : Xh, OP = pitch > 0 ? pitch : Xh;
   if (KT > Xh || OP < KT) return hipErrorInvalidValue;
   const long nrows = g.rows_per_group * g.ngroups;
   const FftKey key{kFftRowsR2C, X, 0, nrows, 0};
-  if (fft_recording()) fft_record(key, [=] { return launch_rows_r2c(in, out, X, g, s, KT, OP, tag); });
+  if (fft_recording()) fft_record(key, [=] { return launch_rows_r2c(in, out, X, g, s, KT, OP, tag, table); });
   const FftChoice c = rows_choice(key);
   FftPlan plan;
   if (!make_plan_variant(X, c.plan, &plan)) return hipErrorInvalidValue;
@@ -227,6 +227,16 @@ hipError_t launch_rows_r2c(const float* in, float2* out, int X, const RowGroups&
   const size_t lds = (size_t)(X + (long)L * row_stride(X)) * sizeof(float2);
   ScopedTiming _t(tag, s);
 #define WO_ROWS_ARGS in, out, X, g, plan, L, nlines, KT, OP
+#define X_(NN)                                                                                   \
+  case NN:                                                                                       \
+    hipLaunchKernelGGL((k_rows_r2c<NN, true>), dim3((unsigned)nwg), dim3(thr), lds, s, WO_ROWS_ARGS); \
+    return hipGetLastError();
+  if (table && c.plan == 0) switch (X) {
+      WO_LATERAL_SIZES(X_)
+      default:
+        break;
+    }
+#undef X_
 #define X_(NN) WO_CASE_ROWS(k_rows_r2c, NN)
   if (c.plan == 0) switch (X) {
       WO_LATERAL_SIZES(X_)

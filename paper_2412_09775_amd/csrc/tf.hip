@@ -205,6 +205,7 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
     constexpr int NP = StaticPlan<NS>::passes();
     constexpr int R0 = StaticPlan<NS>::radix(0), NB0 = NS / R0;
     constexpr int RL = StaticPlan<NS>::radix(NP - 1), NSL = NS / RL;
+    constexpr bool TB = CS || kTableTwiddles<NS>;   // the thin model's transforms (kTableTwiddles)
     constexpr int B0 = (kEmax + R0 - 1) / R0, BL = (kEmax + RL - 1) / RL;
     static_assert(NP >= 2, "compiled lateral lengths have at least two passes");
     double tkz[B0][R0];
@@ -269,7 +270,8 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
     // is held as its rounded value and the remainder, as the rounded step alone
     // is off by up to 3e-8 rad in every plane (256 patches of 32 x 128 x 128:
     // gradient error against FP64 8.3e-7 without the remainder, 5.2e-7 with
-    // it, 223 and 285 us; the 3D models keep the plain step, 55 against 57 us).
+    // it, both with twiddles as powers, 223 and 285 us; the 3D models keep the
+    // plain step, 55 against 57 us).
     float2 ph[B0][R0], st[B0][R0], sl[CS ? B0 : 1][CS ? R0 : 1];
     {
       const double dzr = plane_z(zbeg, sm) - o.defocus;
@@ -323,14 +325,14 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
         }
       }
       __syncthreads();
-      static_passes<NS, 0, true, kEmax, false, false, 1, NP - 1>(buf, nl, nl, 1, lsh, tw, 1.f, tid, nthr);
+      static_passes<NS, 0, true, kEmax, false, false, 1, NP - 1, false, TB>(buf, nl, nl, 1, lsh, tw, 1.f, tid, nthr);
 #pragma unroll
       for (int b = 0; b < BL; ++b) {
         const int j = tid + b * nthr;
         if (j < nl * NSL) {
           const int l = j & (nl - 1), k = j >> lsh;
           float2 w[RL];
-          twiddles<RL, kTableTwiddles<NS>>(w, tw, k, true);   // span NSL = NS / RL: stride 1; the inverse
+          twiddles<RL, TB>(w, tw, k, true);   // span NSL = NS / RL: stride 1; the inverse
           float2 v[RL];
 #pragma unroll
           for (int r = 0; r < RL; ++r) {
@@ -548,9 +550,9 @@ hipError_t launch_tf_fields_y(const DevOptics* opt, const Sampling& sm, int npat
 // y < LY, p = 0 phase, 1 absorption (pstride < 0: phase only).  The fields are
 // read in the compact column layout of the field kernel (XC columns, last
 // non-negative column KP) and placed on an LX-point transform (frequency kx
-// at index kx or LX + kx); the columns it does not store are zero.
-
-template <int NS>
+// at index kx or LX + kx); the columns it does not store are zero.  TB: twiddles
+// from the table (the thin model).
+template <int NS, bool TB>
 __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ partials,
                                                      long tiles_x, Sampling sm,
                                                      const float2* __restrict__ ab,
@@ -607,8 +609,8 @@ __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ 
         buf, 2 * nr, 1, LS, -1, 1.f, tid, nthr, load, kept,
         [&] { wave0_sum(partials + patch * tiles_x, tiles_x, &ibg_s); });   // sum S P^2
     const float cs = (float)(1.0 / ((double)X * (double)Y * ibg_s));
-    static_passes<NS, 0, false, kEmax, true, true, 1, NP - 1>(buf, 2 * nr, 1, LS, -1, tw, 1.f, tid,
-                                                              nthr);
+    static_passes<NS, 0, false, kEmax, true, true, 1, NP - 1, false, TB>(buf, 2 * nr, 1, LS, -1, tw, 1.f, tid,
+                                                                         nthr);
     float2 cv[BPF][R0];
     int cr[BPF], ck[BPF];
 #pragma unroll
@@ -618,7 +620,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ 
       if (j < nr * NB) {
         const int r = j / NB, k = j - r * NB;
         float2 w[R0];
-        if constexpr (NP > 1) twiddles<R0, kTableTwiddles<NS>>(w, tw, k, true);   // span NB: stride 1; the inverse
+        if constexpr (NP > 1) twiddles<R0, TB>(w, tw, k, true);   // span NB: stride 1; the inverse
         float2 va[R0], vb[R0];
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
@@ -651,7 +653,7 @@ __global__ __launch_bounds__(1024) void k_tf_rows_lf(const double* __restrict__ 
       }
     }
     __syncthreads();
-    static_passes<NS, 0, false, kEmax, true, false, 1, NP>(buf, nr, 1, 2 * LS, -1, tw, -1.f, tid, nthr);
+    static_passes<NS, 0, false, kEmax, true, false, 1, NP, false, TB>(buf, nr, 1, 2 * LS, -1, tw, -1.f, tid, nthr);
   } else {
     gather_to_lds_map(buf, nr * 2 * X, tid, nthr, [&](int e) {
       const int t = e / X, i = e - t * X;
@@ -734,11 +736,14 @@ hipError_t launch_tf_rows_labelfree(const double* partials, const Sampling& sm, 
   const int thr = c.threads;
   const size_t lds = (size_t)(LX + 2L * R * row_stride(LX)) * sizeof(float2);
   ScopedTiming _t("k_tf_rows_lf", s);
+#define WO_ROWS_LF(NN, TB)                                                                       \
+  hipLaunchKernelGGL((k_tf_rows_lf<NN, TB>), dim3((unsigned)nwg), dim3(thr), lds, s, partials, tiles_x, \
+                     sm, ab, out, patch_stride, pstride, zstride, R, wpp, ls.xc, ls.kp, ls.kt, OP, \
+                     LY, LX, ls.xa, ls.kpa, plan)
 #define X_(NN)                                                                                   \
   case NN:                                                                                       \
-    hipLaunchKernelGGL((k_tf_rows_lf<NN>), dim3((unsigned)nwg), dim3(thr), lds, s, partials, tiles_x, \
-                       sm, ab, out, patch_stride, pstride, zstride, R, wpp, ls.xc, ls.kp, ls.kt, OP, \
-                       LY, LX, ls.xa, ls.kpa, plan);                                             \
+    if (sm.model == kLabelFreeThin) WO_ROWS_LF(NN, true);                                        \
+    else WO_ROWS_LF(NN, kTableTwiddles<NN>);                                                     \
     return hipGetLastError();
   if (c.plan == 0) switch (LX) {
       WO_LATERAL_SIZES(X_)
@@ -746,9 +751,8 @@ hipError_t launch_tf_rows_labelfree(const double* partials, const Sampling& sm, 
         break;
     }
 #undef X_
-  hipLaunchKernelGGL((k_tf_rows_lf<0>), dim3((unsigned)nwg), dim3(thr), lds, s, partials, tiles_x, sm,
-                     ab, out, patch_stride, pstride, zstride, R, wpp, ls.xc, ls.kp, ls.kt, OP, LY, LX,
-                     ls.xa, ls.kpa, plan);
+  WO_ROWS_LF(0, false);
+#undef WO_ROWS_LF
   return hipGetLastError();
 }
 
