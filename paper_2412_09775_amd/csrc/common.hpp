@@ -338,16 +338,17 @@ constexpr TwTable<N> make_tw_table() {
 template <int N>
 static __device__ const TwTable<N> kTwTable = make_tw_table<N>();
 
-// cos and sin of (pi / 4) t, 0 <= t <= 1, in FP64 to 1e-11 (Taylor sums about 0:
-// the next terms are x^14 / 14! and x^13 / 13! at x = pi / 4), for entries rounded
-// to FP32.  About 20 instructions, where a full FP64 sine-cosine pair takes more
-// than a hundred.
-__device__ __forceinline__ void eighth_sincos(double t, double* sn, double* cs) {
+// cos and sin of (pi / 4) t, 0 <= t <= 1, in FP64 to 3e-16 (Taylor sums about 0:
+// the next terms, x^18 / 18! and x^19 / 19! at x = pi / 4, are below 3e-18).
+// About 25 instructions, where a full FP64 sine-cosine pair takes more than a
+// hundred.
+__host__ __device__ __forceinline__ void eighth_sincos(double t, double* sn, double* cs) {
   const double x = 0.78539816339744830962 * t, x2 = x * x;
   *cs = 1.0 + x2 * (-1.0 / 2 + x2 * (1.0 / 24 + x2 * (-1.0 / 720 + x2 * (1.0 / 40320 + x2 * (-1.0 / 3628800 +
-        x2 * (1.0 / 479001600))))));
+        x2 * (1.0 / 479001600 + x2 * (-1.0 / 87178291200 + x2 * (1.0 / 20922789888000))))))));
   *sn = x * (1.0 + x2 * (-1.0 / 6 + x2 * (1.0 / 120 + x2 * (-1.0 / 5040 + x2 * (1.0 / 362880 +
-        x2 * (-1.0 / 39916800))))));
+        x2 * (-1.0 / 39916800 + x2 * (1.0 / 6227020800 + x2 * (-1.0 / 1307674368000 +
+        x2 * (1.0 / 355687428096000)))))))));
 }
 
 // Twiddles tw[m] = exp(-2 pi i m / n), m < n, from FP64 sines and cosines.
