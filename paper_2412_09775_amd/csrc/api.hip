@@ -591,8 +591,8 @@ LatSupport tf_support(const wo_optics* o, int32_t n, const Shape& s, bool* compa
 
 // Vector model: the optics, the per-patch constants, the field spectra on the
 // detection pupil's columns (later the bank's columns k < kt before its Z
-// pass), the fields on the grid (6 + 3 per illumination state each) and the
-// real channel responses.
+// pass), the fields on the grid (8 for one illumination state, 10 for five) and
+// the real channel responses.
 // Transform lengths of the vector synthesis: with a compiled row length the
 // fused X pass runs on the support's shortened transforms LY x LX (they hold
 // the responses' band without wrap-around, as for the label-free bank);
@@ -606,14 +606,13 @@ VecLengths vec_lengths(const Shape& s, const LatSupport& sup) {
   return VecLengths{false, (int)s.Y, (int)s.X};
 }
 
-// Fields the workspace has room for (the model needs vec_fields of them).
-long vec_space_fields(const wo_optics* o) { return 6 + 3 * (o->vec_channels == 0 ? 1 : 5); }
+int vec_states(const wo_optics* o) { return o->vec_channels == 0 ? 1 : 5; }
 size_t vec_full_fields_bytes(const wo_optics* o, int32_t n, size_t vox) {
-  return align_up((size_t)n * vec_space_fields(o) * vox * sizeof(float2));
+  return align_up((size_t)n * vec_fields(vec_states(o)) * vox * sizeof(float2));
 }
 
 size_t vec_compact_elems(const wo_optics* o, int32_t n, const Shape& s, const LatSupport& sup, int LY) {
-  const long F = vec_space_fields(o);
+  const long F = vec_fields(vec_states(o));
   return (size_t)n * s.Z * LY * std::max(F * sup.xc, (long)s.C * s.P * sup.kt);
 }
 
@@ -1532,7 +1531,7 @@ int wo_lateral_support(const wo_optics* o, int32_t n, wo_support* out) {
 // and the forward 3D transform of each response into tf [patch][C][P][Z][Y][Xh].
 static int run_vector_tf(const wo_optics* o, int32_t n, const Shape& s, float2* tf, void* ws, hipStream_t hs,
                          bool band_out) {
-  const int NS = o->vec_channels == 0 ? 1 : 5;
+  const int NS = vec_states(o);
   const int F = vec_fields(NS);
   const LatSupport sup = lateral_support(o, n);   // the detection pupils' columns: sup.xc, sup.kp
   const VecLengths L = vec_lengths(s, sup);

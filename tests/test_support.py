@@ -104,3 +104,25 @@ def test_bench_volume_runs_on_384_point_transforms():
     o = lf(nz=96, ny=512, nx=512)
     assert api.lateral_support([o]) == {"field_cols": (112, 240), "tf_cols": 176, "band_rows": 331,
                                         "tf_lengths": (384, 384)}
+
+
+@pytest.mark.parametrize("channels,nx,lx", [(0, 256, 256), (1, 256, 256), (1, 100, None), (0, 100, None)])
+def test_vector_workspace_holds_the_fields_it_writes(channels, nx, lx):
+    """Eight fields of a single state, ten of five: their spectra on the kept columns
+    and, for rows without compiled stages (lx None), the fields on the grid; the
+    responses; a few kilobytes of records."""
+    from paper_2412_09775_amd import api
+    nz, ny = 40, 96
+    props = (0, 16, 8, 1)
+    o = api.Optics(model=api.MODEL_VECTOR_3D, nz=nz, ny=ny, nx=nx, dz=0.2, dy=0.1, dx=0.1, wavelength=0.532,
+                   na_ill=0.5, na_det=1.2, n_medium=1.33, vec_channels=channels, vec_props=props)
+    sup = api.lateral_support([o])
+    F, C, P = (10, 5, len(props)) if channels == 1 else (8, 4, len(props))
+    fused = lx is not None
+    ly, lx = sup["tf_lengths"] if fused else (ny, nx)
+    spectra = 8 * nz * ly * max(F * sup["field_cols"][1], C * P * sup["tf_cols"])
+    grid = 0 if fused else 8 * F * nz * ly * lx
+    responses = C * P * max(4 * nz * ly * lx, 8 * nz * ly * sup["tf_cols"] if fused else 0)
+    need = spectra + grid + responses
+    got = api.workspace_size([o], api.OP_TRANSFER_FUNCTION)
+    assert need <= got <= need + 16384
