@@ -1118,9 +1118,16 @@ namespace wo {
 // Radices of the other compiled lengths: the fewest passes (each is an LDS round
 // trip and two barriers) from radices up to 12, the most even split among equals;
 // odd radices first, then those with the fewest factors of two.  The first pass
-// writes its outputs with a stride of its radix: an odd stride spreads over the
-// LDS banks, so rows of these lengths are not padded and every element of a pass
-// is a constant offset from its first.
+// writes its outputs with a stride of its radix.  27 of the 42 row lengths have an
+// odd radix for it, which spreads over the LDS banks; the others (36, 60, 100, 120,
+// 144, 216, 288, 360, 432, 600, 640, 768, 800, 960, 1000) begin with 6, 10 or 12.
+// Rows of all of them are not padded, so that every element of a pass is a constant
+// offset from its first.  Bank conflict cycles per LDS cycle of the R2C and C2R
+// rows: 450 points (9 5 10) 0.28 and 0.45, 1000 (10 10 10) 0.29 and 0.43, 640 (10 8
+// 8) 0.35 and 0.50, 768 (12 8 8) 0.46 and 0.59; padded 512 points 0.18 and 0.19.
+// The times do not show it: on 256 x 32 rows R2C 2.06 to 2.31 ps a voxel at 768 to
+// 1000 points, 2.07 to 2.46 at 720, 900 and 972 with an odd first radix, C2R 1.62
+// to 1.73 and 1.60 to 1.77 (runtime plans 4.4 to 5.9 and 4.4 to 5.8).
 struct Radices {
   int r[8];
   int n;

@@ -151,8 +151,10 @@ struct ZopGeom {
   int R, ky, nb, tiles_row, bank_band;
 };
 
-// With compiled stages at most 72 VGPRs (7 waves per SIMD, no spills); the
-// runtime-plan instances keep their allocation (they would spill).
+// With compiled stages at most 72 VGPRs (7 waves per SIMD); no instance spills
+// but the unreduced 5 x 4 bank's at 16, 18, 24, 27, 75, 96 and 128 planes (one or
+// two registers each); the runtime-plan instances keep their allocation (they
+// would spill).
 // RED: tf holds the polarisation bank in reduced form, [2][Z][..] per patch
 // (H_phase, H_abs), and the coupling cpl[patch] forms H_cp per frequency.
 template <int P, int CT, int NS, bool RED>

@@ -1,10 +1,11 @@
-"""Transforms of lengths without compiled stages, through the linear calls.
+"""Transforms of ragged lengths through the linear calls.
 
 The forward model and the reconstruction of random volumes against numpy FP64
 transforms with the same bank (the library's own, so only the transforms and the
-per-frequency step are compared).  Lengths over every radix of the runtime plans
-(2 to 12), one to four passes, odd and even first radices, several rows a
-workgroup and one, powers of two beyond the compiled lengths.  Relative L2 <= 1e-5
+per-frequency step are compared).  Row and column lengths with compiled stages over
+every radix of their plans (2 to 12), one to four passes, odd and even first radices,
+several rows a workgroup and one; a few shapes (Z below 16, rows of 30, 1152, 2048 and
+4096 points) take the runtime plans, of radices 2, 3, 4, 5 and 8.  Relative L2 <= 1e-5
 (FP32 transforms) and 1e-4 (solve), the bounds of the parity suite."""
 
 import numpy as np
