@@ -1589,7 +1589,7 @@ static int run_tf(const wo_optics* o, int32_t n, const Shape& s, void* tf_out, v
   LatSupport sup = tf_support(o, n, s, &compact_out);
   // the nine apertures through their shared scattered arm: direct arms of the
   // sectors first (patch i, sector c at 8 i + c), then B of every patch
-  const bool shared_arm = fs == 9 && tf_rows_sectors_fits(sup.lx);
+  const bool shared_arm = fs == 9 && tf_rows_sectors_fits(sup.lx, (long)n * s.Z * sup.ly);
   std::vector<DevOptics> h(nv);
   for (int i = 0; i < n; ++i)
     for (int c = 0; c < fs; ++c) {

@@ -221,9 +221,9 @@ hipError_t launch_tf_fields_y(const DevOptics* opt, const Sampling& sm, int npat
 // The nine apertures' phase responses from the sectors' direct arms a
 // [patch][8][z][y][xa], the shared scattered arm b [patch][z][y][xc] (field
 // kernel, one_arm) and the sectors' pupil-sum partials: columns k < kt of
-// out[(patch 9 + c) set_stride + z zstride + y pitch + k]; rows up to
-// tf_rows_sectors_fits.
-bool tf_rows_sectors_fits(int X);
+// out[(patch 9 + c) set_stride + z zstride + y pitch + k]; where
+// tf_rows_sectors_fits (row length, rows of all patches' planes).
+bool tf_rows_sectors_fits(int X, long rows);
 hipError_t launch_tf_rows_sectors(const double* partials, const Sampling& sm, int npatch, const float2* a,
                                   const float2* b, float2* out, long set_stride, long zstride, int pitch,
                                   const LatSupport& ls, hipStream_t s);

@@ -767,11 +767,14 @@ hipError_t launch_tf_rows_labelfree(const double* partials, const Sampling& sm, 
 // two to a complex line; out + (patch 9 + c) set_stride + z zstride + y OP + k,
 // k < KT.  Nine inverse and five forward transforms a row, where the pairwise
 // pass takes eighteen and nine and the fields' Y pass eighteen columns instead
-// of nine: 48 x 512 x 512 (rows of 384) fields and rows 240 + 379 us, 76 + 339 us so;
+// of nine: 48 x 512 x 512 (rows of 384) fields and rows 240 + 379 us, 76 + 321 us so;
 // bound by VALU issue.  LDS line j nr + r: b (j = 0) or a_{j-1} of row r, then
-// the packed responses 2j and 2j + 1.
+// the packed responses 2j and 2j + 1.  72 VGPRs, seven waves a SIMD, in spite of up
+// to 17 spills: a workgroup is five to nine waves, of which one or two more fit a CU
+// (rows of 240, 12288 of them: 97 VGPRs 156 us, 72 98 us; 480: 313 and 244; 320: 159
+// and 132); at 1024 points LDS holds one workgroup a CU whatever the registers.
 template <int NS>
-__global__ __launch_bounds__(1024) void k_tf_rows_sectors(const double* __restrict__ partials, long tiles_x,
+__global__ __launch_bounds__(1024, NS > 0 && NS < 1024 ? 7 : 1) void k_tf_rows_sectors(const double* __restrict__ partials, long tiles_x,
                                                           Sampling sm, const float2* __restrict__ a,
                                                           const float2* __restrict__ b,
                                                           float2* __restrict__ out, long set_stride,
@@ -899,7 +902,41 @@ static int sectors_rows(int X) {
   int R = std::max(1, 2048 / (9 * X));
   return (long)(X + 9L * R * row_stride(X)) * (long)sizeof(float2) + 128 <= lds_limit_bytes() ? R : 0;
 }
-bool tf_rows_sectors_fits(int X) { return sectors_rows(X) > 0; }
+// Elements a workgroup owns at once, at most kMaxElems: every line, or five lines of
+// longer rows and then the other four.
+static long sectors_elems(int X, int R) {
+  return 9L * R * X <= kMaxElems ? 9L * R * X : std::min<long>(5L * X, kMaxElems);
+}
+
+// Whether `rows` rows of X points take the shared arm.  Its second field launch and
+// few, long workgroups cost a small bank more than the transforms saved (whole bank,
+// shared and pairwise: 64 rows of 64 to 512 points 40-45 and 27-34 us, 512 rows of 160
+// to 256 41-44 and 35-41, of 480 55 and 60; 1536 rows of 64 39 and 34, of 160 to 256
+// 56-67 and 64-74, of 1024 149 and 142; 2048 rows of 64 to 512 40-107 and 40-106;
+// 5120 to 6144 rows 57-280 and 64-293): from 2048 rows, or from 200000 points of rows
+// up to 512.  Lengths on the runtime plan, whose 128 registers leave four waves a
+// SIMD, take it where the workgroups that fit keep 85 % of those lanes busy (4096
+// rows, shared to pairwise: 0.73 to 0.97 times at the eighteen such lengths, from 20
+// to 900 points; of the others 1.26 at 250 points, 1.25 at 288, 1.22 at 500, but 0.73
+// at 720), and beyond 1024 points, where the pairwise rows hold one pair a workgroup
+// (1200 points 0.64, 1500 0.65 times).
+bool tf_rows_sectors_fits(int X, long rows) {
+  const int R = sectors_rows(X);
+  if (R < 1) return false;
+  if (X > 1024) return true;
+  if (rows < 2048 && (X > 512 || rows * X < 200000)) return false;
+  switch (X) {
+#define X_(NN) case NN:
+    WO_LATERAL_SIZES(X_)
+#undef X_
+    return true;
+    default:
+      break;
+  }
+  const long own = sectors_elems(X, R);
+  const int waves = threads_for(own) / 64, groups = 4 / ((waves + 3) / 4);   // spread over four SIMDs
+  return groups * own >= 85L * kMaxElems / 100;
+}
 
 hipError_t launch_tf_rows_sectors(const double* partials, const Sampling& sm, int npatch, const float2* a,
                                   const float2* b, float2* out, long set_stride, long zstride, int pitch,
@@ -915,9 +952,7 @@ hipError_t launch_tf_rows_sectors(const double* partials, const Sampling& sm, in
   const long wpp = ((long)sm.nz * LY + R - 1) / R;
   const int W = tf_tile_width(sm, LY, 1);
   const long tiles = (ls.xa + W - 1) / W;
-  // at most kMaxElems at once: five lines of longer rows, then the other four
-  const long own = 9L * R * LX <= kMaxElems ? 9L * R * LX : std::min<long>(5L * LX, kMaxElems);
-  const int thr = threads_for(own);
+  const int thr = threads_for(sectors_elems(LX, R));
   const size_t lds = (size_t)(LX + 9L * R * row_stride(LX)) * sizeof(float2);
   ScopedTiming _t("k_tf_rows_sectors", s);
 #define X_(NN)                                                                                      \
