@@ -1744,10 +1744,12 @@ int wo_transfer_function_band(const wo_optics* o, int32_t n, void* tf_out, void*
   Shape s;
   bank_shape(o, &s);
   // the band layout is the full one where the support fills the grid; else it
-  // comes from the compact Z pass of the label-free 3D models
+  // comes from the compact Z pass of the label-free 3D models (the fluorescence
+  // bank has none: it would be written in full, past the end of tf_out)
   bool compact_out = false;
-  const LatSupport sup = tf_support(o, n, s, &compact_out);
-  if (o->model != WO_MODEL_VECTOR_3D && !compact_out && (s.thin || sup.kt < s.Xh || sup.ky < s.Y))
+  (void)tf_support(o, n, s, &compact_out);
+  const LatSupport lat = lateral_support(o, n);
+  if (o->model != WO_MODEL_VECTOR_3D && !compact_out && (s.thin || lat.kt < s.Xh || lat.ky < s.Y))
     return WO_EUNSUPPORTED;
   if (ws_bytes < tf_ws(o, n, s)) return WO_ENOMEM;
   return run_tf(o, n, s, tf_out, ws, (hipStream_t)stream, true);
