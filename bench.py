@@ -156,7 +156,7 @@ def counter_symbols(sup, Z, X, P, C, ns=None):
                 "k_rows_r2c": f"wo::k_rows_r2c<{X}, {tb(X)}>", "k_rows_c2r": f"wo::k_rows_c2r<{X}>"}
     return {f"k_zop<{P}>": zop, "k_rows_r2c": f"wo::k_rows_r2c<{X}, {tb(X)}>",
             "k_rows_c2r": f"wo::k_rows_c2r<{X}>", "k_tf_rows_lf": f"wo::k_tf_rows_lf<{lx}, {tb(lx)}>",
-            "k_tf_fields_y": f"wo::k_tf_fields_y<{ly}, 2, false, false>",
+            "k_tf_fields_y": f"wo::k_tf_fields_y<{ly}, 2, false, false, false>",
             "k_cols_z_band": f"wo::k_cols_expand<{Z}, {min(16, 8192 // Z)}>"}
 
 

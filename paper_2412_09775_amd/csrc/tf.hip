@@ -150,10 +150,11 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // are evaluated once into registers; each plane then only needs its phase.
 // The workgroup of the first chunk also writes the tile's share of the pupil
 // sum (sum S P^2 for label-free, sum P^2 for fluorescence) to
-// partials[patch * tiles_x + tile].  NF = 1 also serves one arm of the label-free
-// pair alone (the nine-aperture model, whose apertures share B): B for
-// opt.sector = kScatteredArm, else A.
-template <int NS, int NF, bool AB, bool CS>
+// partials[patch * tiles_x + tile].  ARM (NF = 1): one arm of the label-free pair
+// alone (the nine-aperture model, whose apertures share B), B for opt.sector =
+// kScatteredArm, else A; an instance of its own, because the choice at run time cost
+// the fluorescence fields 2 us of 17 (96 x 128 x 160).
+template <int NS, int NF, bool AB, bool CS, bool ARM>
 __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restrict__ opt,
                                                       Sampling sm, float2* __restrict__ ab,
                                                       double* __restrict__ partials, int W,
@@ -188,8 +189,8 @@ __global__ __launch_bounds__(1024) void k_tf_fields_y(const DevOptics* __restric
   z_chunk_range(Z, zsplit, ZC, zc, &zbeg, &zend);
   const DevOptics o = opt[patch];
   // one field (fluorescence, or one label-free arm) or A and B
-  const bool fluor = NF == 1 && sm.model == kFluor3D;
-  const bool arm_b = NF == 1 && o.sector == kScatteredArm;
+  constexpr bool fluor = NF == 1 && !ARM;
+  const bool arm_b = ARM && o.sector == kScatteredArm;
   constexpr int nf = NF;
   constexpr int EPT = kEmax / NF;   // elements of a thread: Y * W * NF <= threads * kEmax
   const int x0 = (int)(tile * W);
@@ -517,16 +518,17 @@ hipError_t launch_tf_fields_y(const DevOptics* opt, const Sampling& sm, int npat
   const int thr = threads_for((long)LY * nf * W);
   const size_t lds = (size_t)(LY + LY * nf * W) * sizeof(float2);
   ScopedTiming _t("k_tf_fields_y", s);
-#define WO_FIELDS_(NN, FF, AA, CC)                                                               \
-  hipLaunchKernelGGL((k_tf_fields_y<NN, FF, AA, CC>), dim3((unsigned)nwg), dim3(thr), lds, s, opt, sm, \
+#define WO_FIELDS_(NN, FF, AA, CC, RR)                                                           \
+  hipLaunchKernelGGL((k_tf_fields_y<NN, FF, AA, CC, RR>), dim3((unsigned)nwg), dim3(thr), lds, s, opt, sm, \
                      ab, partials, W, tiles, ZC, ls.xc, ls.kp, LY, xa, kpa, plan)
   // compensated steps for the compiled lengths of the thin model
   const bool cs = sm.model == kLabelFreeThin;
 #define WO_FIELDS(NN, AA)                                                                        \
   do {                                                                                           \
-    if (nf == 1) WO_FIELDS_(NN, 1, AA, false);                                                   \
-    else if (cs && NN > 0) WO_FIELDS_(NN, 2, AA, (NN > 0));                                      \
-    else WO_FIELDS_(NN, 2, AA, false);                                                           \
+    if (one_arm) WO_FIELDS_(NN, 1, AA, false, true);                                             \
+    else if (nf == 1) WO_FIELDS_(NN, 1, AA, false, false);                                       \
+    else if (cs && NN > 0) WO_FIELDS_(NN, 2, AA, (NN > 0), false);                               \
+    else WO_FIELDS_(NN, 2, AA, false, false);                                                    \
   } while (0)
 #define X_(NN)                                                                                   \
   case NN:                                                                                       \
